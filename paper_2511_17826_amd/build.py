@@ -18,7 +18,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtbik.so")
 
 SOURCES = ["tbik_api.hip", "gemm_reference.hip", "gemm_tiled.hip", "gemm_f32.hip", "gemm_fp8.hip", "gemm_mxfp4.hip", "gemm_mxfp6.hip", "combine.hip", "activation.hip", "rmsnorm.hip", "row_reduce.hip",
-           "attention.hip"]
+           "attention.hip", "attention_decode.hip"]
 
 # -ffp-contract=off: a tree addition or an RMSNorm multiply must never be fused into an FMA.
 # packed-fp32 ops are switched off for the device pass (known-bad forms on the test machines).

@@ -37,25 +37,12 @@
 #include <cstdint>
 #include <type_traits>
 
-#include "tbik_device.hpp"
-#include "tbik_internal.hpp"
+#include "attention_common.hpp"
 
 namespace tbik {
 
-constexpr int ATT_D = 128;    // head dimension
-constexpr int ATT_BQ = 128;   // queries per workgroup
-constexpr int ATT_KV = 64;    // keys per tile: part of the result, never tuned per call
-constexpr int ATT_TILE_BYTES = ATT_KV * ATT_D * 2;
-#ifndef TBIK_ATT_SPLIT
-#define TBIK_ATT_SPLIT 64     // other values: timing experiments only (the bits change, the oracle's tests fail)
-#endif
-constexpr int ATT_SPLIT = TBIK_ATT_SPLIT;   // key tiles per split (4096 keys): part of the result as well
 constexpr int ATT_THREAD_STATE = 4 + ATT_D / 32 * 16;            // floats of one thread's softmax state: m, l, two unused, o
 constexpr int ATT_STATE_FLOATS = ATT_THREAD_STATE * 256;         // one workgroup's
-
-typedef short att_v4i16 __attribute__((ext_vector_type(4)));
-typedef unsigned int att_u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int att_u32x2 __attribute__((ext_vector_type(2)));
 
 struct AttnParams {
     const uint16_t *Q, *K, *V;
@@ -79,7 +66,6 @@ struct AttnParams {
                                                       // n_splits > 1: [item][split] states for attention_merge_kernel
 };
 
-__device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 // Query blocks are numbered over the whole call without a table: sequence b owns the ids G(b) .. G(b) + blocks(b) - 1
 // with G(b) = cu_q[b] / R + b (R queries per block; G(b + 1) - G(b) >= ceil(Lq_b / R), so the ranges do not overlap,
@@ -193,15 +179,6 @@ __device__ __forceinline__ void attention_store_output(uint16_t *optr, float l, 
             w[1] = pack_16x2<F16>(v[2], v[3]);
             *reinterpret_cast<att_u32x2 *>(optr + db * 32 + 8 * q) = w;
         }
-}
-
-// A lane and its partner lane ^ 32 hold the two halves of one query's keys.  v_permlane32_swap exchanges the upper
-// half of its first operand with the lower half of its second: from (v, v) it makes (lower half's values, upper
-// half's values) in every lane, i.e. {mine, partner's} in some order -- enough for a maximum or a sum of the two.
-__device__ __forceinline__ void both_halves(float v, float &a, float &b) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    a = __uint_as_float(r[0]);
-    b = __uint_as_float(r[1]);
 }
 
 template <bool CAUSAL, bool F16>
@@ -936,7 +913,9 @@ static AttnPlan plan_attention(int batch, int64_t total_q, int max_seqlen_k, int
 size_t attention_workspace(int batch, int max_seqlen_q, int max_seqlen_k, int heads_q, int heads_kv) {
     if (batch <= 0 || max_seqlen_q <= 0 || heads_q <= 0 || heads_kv <= 0 || heads_q % heads_kv) return 0;
     // the variant switch may only move a call to the other kernel where no workspace is involved, so it does not matter here
-    return plan_attention(batch, (int64_t)batch * max_seqlen_q, max_seqlen_k, heads_q, heads_kv, 0, SIZE_MAX).state_bytes;
+    const size_t need = plan_attention(batch, (int64_t)batch * max_seqlen_q, max_seqlen_k, heads_q, heads_kv, 0, SIZE_MAX).state_bytes;
+    return attention_decode_supports(max_seqlen_q, heads_q, heads_kv)
+               ? std::max(need, attention_decode_workspace(batch, max_seqlen_q, max_seqlen_k, heads_q, heads_kv)) : need;
 }
 
 template <bool F16>
@@ -966,6 +945,11 @@ static hipError_t launch_of(const AttnArgs &a, AttnParams p, const AttnPlan &pl,
 
 hipError_t launch_attention(const AttnArgs &a, hipStream_t s) {
     if (a.batch <= 0 || a.max_seqlen_q <= 0 || a.total_q <= 0) return hipSuccess;
+    // Few queries per sequence: the other kernel wins or ties from 64 keys (12 us, the host's time of a call) to 10000, at
+    // 1 to 300 sequences (attention_decode.hip).  It loses up to 8 % in one corner, 33 .. 40 sequences of the same length
+    // on 8 key/value heads (a second, nearly empty round of workgroups); with lengths that differ it wins there too.
+    if (g_attention_variant.load() == 0 && attention_decode_supports(a.max_seqlen_q, a.heads_q, a.heads_kv))
+        return launch_attention_decode(a, s);
     // Blocks past batch x max_seqlen_q tokens are not launched (the workspace was sized from that bound): with
     // max_seqlen_q below the largest Lq the last queries of the call stay unwritten.
     const int64_t tokens = std::min<int64_t>(a.total_q, (int64_t)a.batch * a.max_seqlen_q);

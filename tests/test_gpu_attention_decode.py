@@ -1,0 +1,67 @@
+"""The kernel for few queries per sequence (max_seqlen_q x query heads per key/value head <= 32) gives the bits of the
+kernel for every call shape (0 differing bits), at the edges of its tiles, rounds of four tiles, splits, column groups and
+channel groups; a few rows are also held against the oracle with the bars of test_gpu_attention.py."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as gu
+from paper_2511_17826_amd import binding as tb
+from paper_2511_17826_amd import synthetic as syn
+from test_gpu_attention import check_against_oracle, i32
+
+pytestmark = pytest.mark.gpu
+
+
+def both(Hq, Hkv, lens_q, lens_k, causal=True, dtype=torch.bfloat16, seed=0, poison=float("nan")):
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(seed)
+    rnd = lambda n, h: torch.randn((n, h, 128), generator=g, device="cuda:0").to(dtype)
+    Q, K, V = rnd(sum(lens_q), Hq), rnd(max(sum(lens_k), 1), Hkv), rnd(max(sum(lens_k), 1), Hkv)
+    cq, ck = i32(np.cumsum([0] + list(lens_q))), i32(np.cumsum([0] + list(lens_k)))
+    call = tb.tbik_attention if dtype == torch.bfloat16 else tb.tbik_attention_f16
+    need = max(256, tb.attention_workspace_bytes(len(lens_q), max(lens_q), max(lens_k), Hq, Hkv))
+    out = []
+    for variant in (1, 0):
+        tb.tbik_set_attention_variant(variant)
+        ws = torch.full((need // 4,), poison, dtype=torch.float32, device="cuda:0")
+        O = torch.full_like(Q, 7.0)
+        call(Q, K, V, cq, ck, max(lens_q), 128 ** -0.5, causal, out=O, max_seqlen_k=max(lens_k), workspace=ws)
+        torch.cuda.synchronize()
+        out.append(O.view(torch.int16).cpu())
+    tb.tbik_set_attention_variant(0)
+    return out
+
+
+EDGES = [1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 191, 255, 256, 257, 300, 511, 513, 1000]
+
+
+@pytest.mark.parametrize("Hq,Hkv,q", [(4, 4, 1), (8, 4, 2), (8, 2, 1), (8, 2, 3), (8, 2, 4), (8, 2, 5), (8, 2, 8), (10, 2, 1), (10, 2, 3),
+                                      (32, 2, 1), (24, 1, 1), (32, 1, 1), (3, 1, 7)])
+@pytest.mark.parametrize("causal", [True, False])
+def test_few_queries_same_bits_at_tile_and_round_edges(Hq, Hkv, q, causal):
+    lens_q = [1 + (i * 7) % q for i in range(len(EDGES))]
+    lens_q[3] = q
+    a, b = both(Hq, Hkv, lens_q, [max(k, 1) for k in EDGES], causal, seed=q)
+    assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("batch,Hkv", [(1, 1), (3, 8), (9, 8), (17, 8), (40, 8), (70, 8)])
+def test_splits_in_parallel_walked_and_channel_groups_same_bits(dtype, batch, Hkv):
+    """1 to 3 splits of 4096 keys, sequences without keys or queries among them; few items (channel groups, one workgroup
+    per split and a fold) to many (splits walked)."""
+    lens = [4096, 4097, 4160, 8192, 8193, 4351, 100, 0, 9000, 4095]
+    lens_k = [lens[(3 * i) % len(lens)] for i in range(batch)]
+    lens_q = [1] * batch
+    if batch > 5:
+        lens_q[5] = 0
+    a, b = both(4 * Hkv, Hkv, lens_q, lens_k, dtype=dtype, seed=batch)
+    assert torch.equal(a, b)
+
+
+def test_short_workspace_walks_and_oracle_parity():
+    c = syn.attention_inputs(61, [1, 2, 1, 4], [4500, 70, 1000, 260], Hq=8, Hkv=2, D=128)
+    Q, K, V = gu.dev_bf16(c["Q"]), gu.dev_bf16(c["K"]), gu.dev_bf16(c["V"])
+    O = tb.tbik_attention(Q, K, V, i32(c["cu_q"]), i32(c["cu_k"]), 4, c["scale"], True)
+    check_against_oracle(gu.host_bf16_bits(O), c, True, min_equal=0.98)
