@@ -98,7 +98,6 @@ struct F32Params {
     int ns_per_shard;
     int64_t k_per_shard;
     int tiles_m, tiles_n;       // output tiles
-    int blocks_n, blocks;       // blocks of 8 x 4 tiles: per row of blocks, in all (large tile only)
     int shards;
 };
 
@@ -112,8 +111,10 @@ __device__ __forceinline__ void f32_wait_loads_and_barrier() {
 //   <1, 1, 4>   32 x 128 tile, for small batches: a quarter of the MFMA work per weight byte, so that streaming W
 //               (not multiplying rows that do not exist) sets the time.
 // Same instructions on the same k in the same order per output element, hence the same bits.
+// The small tile leaves room for a second workgroup on the compute unit (80 KiB of LDS, at most 112 registers), which fills
+// its pipeline fill and the gaps between its MFMAs: 240 tiles at K = 6144 split in two 121 -> 103 us.
 template <int LEVELS, int MT, int NT, int WN>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+__global__ __launch_bounds__(256, MT == 1 ? 2 : 1)
 void gemm_f32_tiled_kernel(const F32Params p) {
     constexpr int WM = 4 / WN;
     constexpr int BM = 32 * MT * WM;
@@ -133,17 +134,19 @@ void gemm_f32_tiled_kernel(const F32Params p) {
     int shard, tile_m, tile_n;
     if (BM == 128) {
         // Consecutive workgroups go round the 8 XCDs, and the 32 workgroups that an XCD (32 compute units, one workgroup
-        // each) runs at a time should share operand panels in its L2.  Tiles are grouped into blocks of 8 x 4 (12 panels
-        // for 32 tiles); block q runs on XCD q % 8 as that XCD's round q / 8.  Workgroups whose slot falls outside the
-        // matrix (ragged block, padding of the grid to whole rounds) leave at once.
-        const int id = blockIdx.x;
-        const int slot_in_block = (id >> 3) & 31;
-        const int q = ((id >> 8) << 3) + (id & 7);
-        shard = q / p.blocks;
-        const int blk = q % p.blocks;
-        tile_m = (blk / p.blocks_n) * 8 + (slot_in_block >> 2);
-        tile_n = (blk % p.blocks_n) * 4 + (slot_in_block & 3);
-        if (shard >= p.shards || tile_m >= p.tiles_m || tile_n >= p.tiles_n) return;      // uniform
+        // each) runs at a time should share operand panels in its L2.  Every XCD takes an eighth of the items, in an order
+        // that goes down eight tiles of a column before the next column: 32 in a row are 12 panels.  (Whole blocks of
+        // 8 x 4 tiles dealt to the XCDs left them unevenly loaded where the rows are not a multiple of eight tiles:
+        // 1200 x 2048 at K = 6144, split in four, four rounds on four XCDs and one on the others, 391 us.)
+        const int per_xcd = gridDim.x >> 3;
+        const int item = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+        const int tiles = p.tiles_m * p.tiles_n;
+        if (item >= tiles * p.shards) return;              // uniform
+        shard = item / tiles;
+        const int t = item % tiles, group = t / (8 * p.tiles_n), in_group = t % (8 * p.tiles_n);
+        const int height = min(8, p.tiles_m - 8 * group);
+        tile_m = 8 * group + in_group % height;
+        tile_n = in_group / height;
     } else {
         // Few rows: every workgroup streams its own panel of W; the grid is exactly tiles x shards.
         const int id = blockIdx.x;
@@ -396,12 +399,9 @@ static hipError_t launch_f32_shape(const GemmArgs &a, hipStream_t s) {
     p.k_per_shard = (int64_t)p.ns_per_shard * a.superleaf;
     p.tiles_n = (a.N + F32_BN - 1) / F32_BN;
     p.tiles_m = (a.M + BM - 1) / BM;
-    p.blocks_n = (p.tiles_n + 3) / 4;
-    p.blocks = p.blocks_n * ((p.tiles_m + 7) / 8);
     p.shards = a.P;
-    int64_t work;
-    if (BM == 128) work = (((int64_t)p.blocks * a.P + 7) / 8) * 256;     // rounds of 8 blocks of 32 tiles, one block per XCD
-    else work = (int64_t)p.tiles_m * p.tiles_n * a.P;
+    int64_t work = (int64_t)p.tiles_m * p.tiles_n * a.P;
+    if (BM == 128) work = (work + 7) / 8 * 8;              // an eighth per XCD
     if (work > 0x7fffffff) return hipErrorInvalidValue;
     int levels = 0;
     while ((1 << levels) < p.ns_per_shard) ++levels;
@@ -415,12 +415,11 @@ static hipError_t launch_f32_shape(const GemmArgs &a, hipStream_t s) {
     }
 }
 
-// variant: VARIANT_T128 forces the 128-row tile, VARIANT_T32 / VARIANT_T64 the 32-row tile; otherwise by the batch.
+// variant: VARIANT_T128 asks for the 128-row tile, VARIANT_T32 / VARIANT_T64 for the 32-row tile.
 hipError_t launch_gemm_f32_tiled(const GemmArgs &a, int variant, hipStream_t s) {
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
     if (!gemm_f32_tiled_supports(a)) return hipErrorInvalidValue;
-    const bool small = (variant == VARIANT_T32 || variant == VARIANT_T64) || (variant != VARIANT_T128 && a.M <= 64);
-    return small ? launch_f32_shape<1, 1, 4>(a, s) : launch_f32_shape<2, 2, 2>(a, s);
+    return variant != VARIANT_T128 ? launch_f32_shape<1, 1, 4>(a, s) : launch_f32_shape<2, 2, 2>(a, s);
 }
 
 }  // namespace tbik

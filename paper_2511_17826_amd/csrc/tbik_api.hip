@@ -1,5 +1,7 @@
 // C ABI of libtbik: argument validation, variant choice, launches.  No device memory is allocated here.
+#include <algorithm>
 #include <atomic>
+#include <cmath>
 
 #include "tbik_internal.hpp"
 
@@ -99,10 +101,41 @@ int internal_split(int M, int N, int K, int ns) {
     return split;
 }
 
+// fp32 operands: tile height and K split of a shape (pure), by a model of the time.  The fp32 MFMA is slow (a K-step of 32
+// takes a 128-row tile 1.9 us and a 32-row tile 0.585 us, of which two tiles side by side on a compute unit lose nothing),
+// so what decides is how evenly the work items fill 256 compute units: 600 x 2048 at K = 6144 is 80 tiles of 128 rows,
+// which a split in four turns into 320 items = two rounds, 197 us; as 304 tiles of 32 rows split in four it is 1216 items,
+// 137 us.  A combine costs 3 us and its planes' round trip at 5 TB/s.  (128-row tiles: one per compute unit at a time, whole
+// rounds.  32-row tiles: two, and a ragged last round costs about half.)  Constants fitted to 26 shapes of K = 6144 and
+// 4096 x {1 .. 1500} rows, each timed at every split and both heights; the choice is within 6 % of the best of them.
+struct F32Plan {
+    int rows, split;
+    double us;
+};
+F32Plan f32_plan_at(int M, int N, int K, int split) {
+    const double steps = K / 32.0 / split, cols = (N + 127) / 128;
+    const double combine = split > 1 ? 3.0 + (double)split * M * N * 4.0 / 5e6 : 0.0;
+    const double rounds = std::ceil(std::ceil(M / 128.0) * cols * split / 256.0), load = std::ceil(M / 32.0) * cols * split / 256.0;
+    const double t128 = rounds * (steps * 1.9 + 4.0) + combine;
+    const double t32 = (load <= 1.0 ? 1.0 : 0.5 * (load + std::ceil(load))) * steps * 0.585 + 6.0 + combine;
+    return t32 < t128 ? F32Plan{32, split, t32} : F32Plan{128, split, t128};
+}
+F32Plan f32_plan(int M, int N, int K, int ns) {
+    F32Plan best{0, 0, 0.0};
+    for (int split = 1; split <= ns && split <= TBIK_MAX_SHARDS; split *= 2) {
+        if (ns / split > 16) continue;                  // the tiled kernel walks at most 16 superleaves per shard
+        if (best.rows && split > 16) break;
+        const F32Plan p = f32_plan_at(M, N, K, split);
+        if (!best.rows || p.us < best.us) best = p;
+    }
+    return best.rows ? best : F32Plan{128, internal_split(M, N, K, ns), 0.0};
+}
+
 int pick_variant(const GemmArgs &a) {
     const int forced = g_forced_variant.load();
     if (forced != VARIANT_AUTO) return (forced == VARIANT_REFERENCE || tiled_supports(a, forced)) ? forced : VARIANT_REFERENCE;
-    if (a.x_dtype == TBIK_F32) return gemm_f32_tiled_supports(a) ? VARIANT_AUTO : VARIANT_REFERENCE;    // the launcher picks the tile
+    if (a.x_dtype == TBIK_F32)
+        return !gemm_f32_tiled_supports(a) ? VARIANT_REFERENCE : f32_plan_at(a.M, a.N, a.K, a.P).rows == 32 ? VARIANT_T32 : VARIANT_T128;
     const int rows = tile_rows(a.M, a.N);
     if (rows == 128 && gemm_tiled_supports(a, VARIANT_T128)) return VARIANT_T128;
     if (rows >= 64 && gemm_tiled_supports(a, VARIANT_T64)) return VARIANT_T64;
@@ -110,6 +143,9 @@ int pick_variant(const GemmArgs &a) {
     if (gemm_tiled_supports(a, VARIANT_T128)) return VARIANT_T128;
     return VARIANT_REFERENCE;
 }
+
+// Bytes of the fp32 planes of a K split.
+inline size_t split_planes_bytes(int M, int N, int split) { return split > 1 ? (size_t)split * (size_t)M * (size_t)N * sizeof(float) : 0; }
 
 // 16-bit output type that goes with an operand format.
 inline bool legal_y_dtype(int y_dtype, int x_dtype) { return y_dtype == TBIK_F32 || y_dtype == x_dtype; }
@@ -121,9 +157,8 @@ extern "C" {
 size_t tbik_gemm_workspace_bytes(int M, int N, int K, int leaf, int k_first) {
     int sl, ns;
     if (check_tree(M, N, K, leaf, k_first, 1, &sl, &ns) != TBIK_OK) return 0;
-    // fp32 partials of the internal K split, if this shape uses one
-    const int split = internal_split(M, N, K, ns);
-    return split > 1 ? (size_t)split * (size_t)M * (size_t)N * sizeof(float) : 0;
+    // fp32 partials of the internal K split, if this shape uses one (16-bit or fp32 operands: the larger of the two)
+    return split_planes_bytes(M, N, std::max(internal_split(M, N, K, ns), f32_plan(M, N, K, ns).split));
 }
 
 }  // extern "C"
@@ -160,13 +195,17 @@ int gemm(int x_dtype, const void *X, int64_t ldx, const void *W, int64_t ldw, vo
     if (!Y) return TBIK_ERR_NULL;
     if (ldy < N) return TBIK_ERR_SHAPE;
     if (!aligned(Y, y_dtype == TBIK_F32 ? 4 : 2)) return TBIK_ERR_ALIGN;
-    const size_t need = tbik_gemm_workspace_bytes(M, N, K, leaf, k_first);
+    int split = internal_split(M, N, K, ns);
+    const size_t need = split_planes_bytes(M, N, split);
     if (need > 0 && (!workspace || workspace_bytes < need)) return TBIK_ERR_WORKSPACE;
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
+    if (x_dtype == TBIK_F32) {                          // its own split, unless the caller brought no room for it
+        const int own = f32_plan(M, N, K, ns).split;
+        if (own == 1 || (workspace && workspace_bytes >= split_planes_bytes(M, N, own))) split = own;
+    }
 
     hipStream_t s = (hipStream_t)hip_stream;
     GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)W, ldw, nullptr, Y, ldy, y_dtype, M, N, K, sl, ns, 1, x_dtype};
-    const int split = internal_split(M, N, K, ns);
     GemmArgs probe = a;
     probe.P = split;
     const int v = pick_variant(probe);
@@ -709,7 +748,7 @@ size_t tbik_gemm_swiglu_workspace_bytes(int M, int I, int K, int leaf, int k_fir
     switch (swiglu_route(TBIK_BF16, M, I, K, sl, ns, &split)) {
         case SWIGLU_FUSED: return 0;
         case SWIGLU_SPLIT: return (size_t)split * (size_t)M * (size_t)(2 * I) * sizeof(float);
-        default: return (((size_t)M * (size_t)(2 * I) * 2 + 255) & ~(size_t)255) + tbik_gemm_workspace_bytes(M, 2 * I, K, leaf, k_first);
+        default: return (((size_t)M * (size_t)(2 * I) * 2 + 255) & ~(size_t)255) + split_planes_bytes(M, 2 * I, internal_split(M, 2 * I, K, ns));
     }
 }
 
