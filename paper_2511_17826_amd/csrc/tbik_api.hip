@@ -101,6 +101,86 @@ int internal_split(int M, int N, int K, int ns) {
     return split;
 }
 
+// Tile height and K split of a shape for 16-bit and 8-bit operands (pure, given the room for planes), by a model of the time:
+//   rounds x max(stages x step[height] + fill, weight bytes of an item / intake) + (split ? combine + planes / rate : 0)
+// with rounds = work items / 256 compute units, rounded up.  What the two rules above miss is how evenly the items fill the
+// compute units and that a lower tile is cheaper than a padded one: 100 rows of 4096 x 4096 in 8-bit operands took 128-row
+// tiles split in eight, 18.9 us, and take 12.4 us as 32-row tiles split in two; 400 rows at K = 12288 in bf16 took 224 tiles
+// of 64 rows, 82 us, and take 61 us as 128-row tiles split in two.  Constants fitted to 88 (16-bit) and 3 x 30 (8- and 4-bit)
+// shapes, K = 4096, 12288 and 25600 x {1 .. 4096} rows, each timed at every height and split: the choice is within 0.4 % of
+// the best of them in the mean (the rules: 5 to 9 %) and 6 % at most.  They are not physical rates one by one.  The rules'
+// choice stays where the model promises less than 4 %.
+enum Operands { OPERANDS_16BIT, OPERANDS_FP8, OPERANDS_MXFP8, OPERANDS_MXFP4, OPERANDS_MXFP6 };
+struct TilePlan {
+    int rows, split;
+};
+struct TileModel {
+    int stage_k;                        // k of an LDS stage
+    double bytes_per_k;
+    double step[3], fill;               // us: a stage of a 32-, 64-, 128-row tile; pipeline fill and epilogue of an item
+    double intake;                      // bytes of W per us and compute unit, in thousands
+    double combine, rate;               // us; bytes of planes per us, in millions
+};
+constexpr TileModel kTileModels[] = {
+    {64, 2.0, {0.005, 0.21, 0.525}, 5.9, 38.5, 3.95, 12.0},
+    {128, 1.0, {0.01, 0.24, 0.33}, 3.1, 51.0, 2.7, 1.2},
+    {128, 1.0, {0.0, 0.185, 0.375}, 3.6, 42.0, 4.8, 2.5},
+    {256, 0.5, {0.31, 0.335, 0.574}, 4.1, 31.4, 2.64, 2.7},
+    {128, 0.75, {0.0, 0.0, 0.61}, 3.6, 36.0, 4.8, 2.5},            // one height; MXFP8's with its stage
+};
+
+// Bytes of the fp32 planes of a K split.
+inline size_t split_planes_bytes(int M, int N, int split) { return split > 1 ? (size_t)split * (size_t)M * (size_t)N * sizeof(float) : 0; }
+
+double tile_plan_us(const TileModel &m, int M, int N, int K, TilePlan p) {
+    const double items = (double)((M + p.rows - 1) / p.rows) * ((N + 127) / 128) * p.split;
+    const double stages = (double)K / m.stage_k / p.split, weights = 128.0 * K / p.split * m.bytes_per_k;
+    const double step = m.step[p.rows == 32 ? 0 : p.rows == 64 ? 1 : 2];
+    return std::ceil(items / 256.0) * std::max(stages * step + m.fill, weights / (m.intake * 1e3)) +
+           (p.split > 1 ? m.combine + (double)p.split * M * N * 4.0 / (m.rate * 1e6) : 0.0);
+}
+
+int forced_rows(int otherwise) {        // what tbik_set_gemm_variant forces
+    switch (g_forced_variant.load()) {
+        case VARIANT_T128: return 128;
+        case VARIANT_T64: return 64;
+        case VARIANT_T32: return 32;
+        default: return otherwise;
+    }
+}
+
+// MXFP6 operands have one tile shape (128 x 128), so their rule for the K cut is that of a 128-row tile whatever M.
+int mxfp6_split(int M, int N, int ns) {
+    const int64_t tiles = (((int64_t)M + 127) / 128) * (((int64_t)N + 127) / 128);
+    int split = 1;
+    while (ns / split > 16 && split < TBIK_MAX_SHARDS) split *= 2;     // the tiled kernel walks at most 16 superleaves per shard
+    if (tiles >= 128) return split;
+    while (split < ns && split < 16 && tiles * split < 256) split *= 2;
+    return split;
+}
+
+// only_split > 0: the split is the caller's (shard partials), only the height is chosen.  room: bytes for planes.
+TilePlan tile_plan(Operands kind, int M, int N, int K, int ns, int only_split, size_t room) {
+    const bool one_height = kind == OPERANDS_MXFP6;
+    const TilePlan rule{one_height ? 128 : forced_rows(tile_rows(M, N)),
+                        only_split > 0 ? only_split : one_height ? mxfp6_split(M, N, ns) : internal_split(M, N, K, ns)};
+    if (g_forced_variant.load() != VARIANT_AUTO || M <= 0 || N <= 0) return rule;
+    const TileModel &m = kTileModels[kind];
+    TilePlan best = rule;
+    double best_us = tile_plan_us(m, M, N, K, rule) / 1.04;
+    for (int rows = one_height ? 128 : 32; rows <= 128; rows *= 2) {
+        for (int split = only_split > 0 ? only_split : 1; split <= ns && split <= 16; split *= 2) {
+            if (ns / split <= 16 && (only_split > 0 || split_planes_bytes(M, N, split) <= room)) {     // a tile walks at most 16 superleaves
+                const double us = tile_plan_us(m, M, N, K, {rows, split});
+                if (us < best_us) { best = {rows, split}; best_us = us; }
+            }
+            if (only_split > 0) break;
+        }
+    }
+    return best;
+}
+TilePlan tile_rule(int M, int N, int K, int ns) { return {forced_rows(tile_rows(M, N)), internal_split(M, N, K, ns)}; }
+
 // fp32 operands: tile height and K split of a shape (pure), by a model of the time.  The fp32 MFMA is slow (a K-step of 32
 // takes a 128-row tile 1.9 us and a 32-row tile 0.585 us, of which two tiles side by side on a compute unit lose nothing),
 // so what decides is how evenly the work items fill 256 compute units: 600 x 2048 at K = 6144 is 80 tiles of 128 rows,
@@ -131,21 +211,17 @@ F32Plan f32_plan(int M, int N, int K, int ns) {
     return best.rows ? best : F32Plan{128, internal_split(M, N, K, ns), 0.0};
 }
 
-int pick_variant(const GemmArgs &a) {
+int pick_variant(const GemmArgs &a, int rows) {      // rows: tile height for 16-bit operands
     const int forced = g_forced_variant.load();
     if (forced != VARIANT_AUTO) return (forced == VARIANT_REFERENCE || tiled_supports(a, forced)) ? forced : VARIANT_REFERENCE;
     if (a.x_dtype == TBIK_F32)
         return !gemm_f32_tiled_supports(a) ? VARIANT_REFERENCE : f32_plan_at(a.M, a.N, a.K, a.P).rows == 32 ? VARIANT_T32 : VARIANT_T128;
-    const int rows = tile_rows(a.M, a.N);
     if (rows == 128 && gemm_tiled_supports(a, VARIANT_T128)) return VARIANT_T128;
     if (rows >= 64 && gemm_tiled_supports(a, VARIANT_T64)) return VARIANT_T64;
     if (gemm_tiled_supports(a, VARIANT_T32)) return VARIANT_T32;
     if (gemm_tiled_supports(a, VARIANT_T128)) return VARIANT_T128;
     return VARIANT_REFERENCE;
 }
-
-// Bytes of the fp32 planes of a K split.
-inline size_t split_planes_bytes(int M, int N, int split) { return split > 1 ? (size_t)split * (size_t)M * (size_t)N * sizeof(float) : 0; }
 
 // 16-bit output type that goes with an operand format.
 inline bool legal_y_dtype(int y_dtype, int x_dtype) { return y_dtype == TBIK_F32 || y_dtype == x_dtype; }
@@ -158,7 +234,8 @@ size_t tbik_gemm_workspace_bytes(int M, int N, int K, int leaf, int k_first) {
     int sl, ns;
     if (check_tree(M, N, K, leaf, k_first, 1, &sl, &ns) != TBIK_OK) return 0;
     // fp32 partials of the internal K split, if this shape uses one (16-bit or fp32 operands: the larger of the two)
-    return split_planes_bytes(M, N, std::max(internal_split(M, N, K, ns), f32_plan(M, N, K, ns).split));
+    return split_planes_bytes(M, N, std::max({internal_split(M, N, K, ns), tile_plan(OPERANDS_16BIT, M, N, K, ns, 0, SIZE_MAX).split,
+                                              f32_plan(M, N, K, ns).split}));
 }
 
 }  // extern "C"
@@ -177,7 +254,7 @@ int gemm_shard_partials(int x_dtype, const void *X, int64_t ldx, const void *W, 
     if (!aligned(partials, 16)) return TBIK_ERR_ALIGN;
     GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)W, ldw, partials, nullptr, 0, TBIK_F32, M, N, K, sl, ns, P, x_dtype};
     hipStream_t s = (hipStream_t)hip_stream;
-    const int v = pick_variant(a);
+    const int v = pick_variant(a, tile_plan(OPERANDS_16BIT, M, N, K, ns, P, 0).rows);
     hipError_t e = (v == VARIANT_REFERENCE) ? launch_reference(a, s) : launch_tiled(a, v, s);
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
@@ -195,20 +272,23 @@ int gemm(int x_dtype, const void *X, int64_t ldx, const void *W, int64_t ldw, vo
     if (!Y) return TBIK_ERR_NULL;
     if (ldy < N) return TBIK_ERR_SHAPE;
     if (!aligned(Y, y_dtype == TBIK_F32 ? 4 : 2)) return TBIK_ERR_ALIGN;
-    int split = internal_split(M, N, K, ns);
-    const size_t need = split_planes_bytes(M, N, split);
+    TilePlan plan = tile_rule(M, N, K, ns);
+    const size_t need = split_planes_bytes(M, N, plan.split);
     if (need > 0 && (!workspace || workspace_bytes < need)) return TBIK_ERR_WORKSPACE;
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     if (x_dtype == TBIK_F32) {                          // its own split, unless the caller brought no room for it
         const int own = f32_plan(M, N, K, ns).split;
-        if (own == 1 || (workspace && workspace_bytes >= split_planes_bytes(M, N, own))) split = own;
+        if (own == 1 || (workspace && workspace_bytes >= split_planes_bytes(M, N, own))) plan.split = own;
+    } else {
+        plan = tile_plan(OPERANDS_16BIT, M, N, K, ns, 0, workspace ? workspace_bytes : 0);
     }
+    const int split = plan.split;
 
     hipStream_t s = (hipStream_t)hip_stream;
     GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)W, ldw, nullptr, Y, ldy, y_dtype, M, N, K, sl, ns, 1, x_dtype};
     GemmArgs probe = a;
     probe.P = split;
-    const int v = pick_variant(probe);
+    const int v = pick_variant(probe, plan.rows);
     hipError_t e;
     if (split == 1 || v == VARIANT_REFERENCE) {
         e = (v == VARIANT_REFERENCE) ? launch_reference(a, s) : launch_tiled(a, v, s);
@@ -317,16 +397,6 @@ int tbik_tree_combine(const float *partials, int P, void *Y, int64_t ldy, tbik_d
 // ---- 8-bit floating-point operands ----
 static bool is_fp8(int d) { return d == TBIK_FP8_E4M3 || d == TBIK_FP8_E5M2; }
 
-// Rows of the 8-bit kernel's workgroup tile: the rule of the 16-bit kernels, or what tbik_set_gemm_variant forces.
-static int fp8_tile_rows(int M, int N) {
-    switch (g_forced_variant.load()) {
-        case VARIANT_T128: return 128;
-        case VARIANT_T64: return 64;
-        case VARIANT_T32: return 32;
-        default: return tile_rows(M, N);
-    }
-}
-
 static int fp8_checks(int x_dtype, const void *X, int64_t ldx, const void *Wt, int64_t ldwt, int M, int N, int K,
                       int leaf, int k_first, int P, int *sl, int *ns) {
     int rc = check_tree(M, N, K, leaf, k_first, P, sl, ns);
@@ -343,8 +413,7 @@ static int fp8_checks(int x_dtype, const void *X, int64_t ldx, const void *Wt, i
 size_t tbik_gemm_fp8_workspace_bytes(int M, int N, int K, int leaf, int k_first) {
     int sl, ns;
     if (check_tree(M, N, K, leaf, k_first, 1, &sl, &ns) != TBIK_OK) return 0;
-    const int split = internal_split(M, N, K, ns);         // the tile shapes and the rule of the 16-bit kernels
-    return split > 1 ? (size_t)split * (size_t)M * (size_t)N * sizeof(float) : 0;
+    return split_planes_bytes(M, N, std::max(internal_split(M, N, K, ns), tile_plan(OPERANDS_FP8, M, N, K, ns, 0, SIZE_MAX).split));
 }
 
 int tbik_gemm_fp8(const void *X, int64_t ldx, const void *Wt, int64_t ldwt, void *Y, int64_t ldy,
@@ -358,13 +427,13 @@ int tbik_gemm_fp8(const void *X, int64_t ldx, const void *Wt, int64_t ldwt, void
     if (!Y) return TBIK_ERR_NULL;
     if (ldy < N) return TBIK_ERR_SHAPE;
     if (!aligned(Y, y_dtype == TBIK_F32 ? 4 : 2)) return TBIK_ERR_ALIGN;
-    const size_t need = tbik_gemm_fp8_workspace_bytes(M, N, K, leaf, k_first);
+    const size_t need = split_planes_bytes(M, N, internal_split(M, N, K, ns));       // more room may allow a better split
     if (need > 0 && (!workspace || workspace_bytes < need)) return TBIK_ERR_WORKSPACE;
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)hip_stream;
     GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)Wt, ldwt, nullptr, Y, ldy, (int)y_dtype, M, N, K, sl, ns, 1, (int)x_dtype, 0};
-    const int split = internal_split(M, N, K, ns);
-    const int rows = fp8_tile_rows(M, N);
+    const TilePlan plan = tile_plan(OPERANDS_FP8, M, N, K, ns, 0, workspace ? workspace_bytes : 0);
+    const int split = plan.split, rows = plan.rows;
     GemmArgs probe = a;
     probe.P = split;
     const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_fp8_tiled_supports(probe);
@@ -395,7 +464,7 @@ int tbik_gemm_shard_partials_fp8(const void *X, int64_t ldx, const void *Wt, int
     if (!aligned(partials, 16)) return TBIK_ERR_ALIGN;
     GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)Wt, ldwt, partials, nullptr, 0, TBIK_F32, M, N, K, sl, ns, P, (int)x_dtype, 0};
     const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_fp8_tiled_supports(a);
-    hipError_t e = tiled ? launch_gemm_fp8_tiled(a, fp8_tile_rows(M, N), (hipStream_t)hip_stream)
+    hipError_t e = tiled ? launch_gemm_fp8_tiled(a, tile_plan(OPERANDS_FP8, M, N, K, ns, P, 0).rows, (hipStream_t)hip_stream)
                          : launch_gemm_fp8_reference(a, (hipStream_t)hip_stream);
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
@@ -433,13 +502,12 @@ static int mxfp4_checks(const void *X, int64_t ldx, const void *Xs, int64_t ldxs
 // From 128 rows on the microscaling GEMMs re-tile their scales first (a launch of its own, which a small batch would
 // feel): the workspace is the fp32 planes of the K split, rounded up to 256 bytes, then the re-tiled scales.
 static bool mx_retiles(int M) { return M >= 128; }
-static size_t mx_planes_bytes(int M, int N, int K, int leaf, int k_first) {
-    return (tbik_gemm_fp8_workspace_bytes(M, N, K, leaf, k_first) + 255) & ~(size_t)255;      // the same tile shapes, the same K split
-}
+static size_t mx_planes_bytes(int M, int N, int split) { return (split_planes_bytes(M, N, split) + 255) & ~(size_t)255; }
+static size_t mxfp4_scales_room(int M, int N, int K) { return mx_retiles(M) && K % 256 == 0 ? mxfp4_retiled_scales_bytes(M, N, K) : 0; }
 size_t tbik_gemm_mxfp4_workspace_bytes(int M, int N, int K, int leaf, int k_first) {
     int sl, ns;
     if (check_tree(M, N, K, leaf, k_first, 1, &sl, &ns) != TBIK_OK) return 0;
-    return mx_planes_bytes(M, N, K, leaf, k_first) + (mx_retiles(M) && K % 256 == 0 ? mxfp4_retiled_scales_bytes(M, N, K) : 0);
+    return mx_planes_bytes(M, N, std::max(internal_split(M, N, K, ns), tile_plan(OPERANDS_MXFP4, M, N, K, ns, 0, SIZE_MAX).split)) + mxfp4_scales_room(M, N, K);
 }
 
 int tbik_gemm_mxfp4(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, const void *Wt, int64_t ldwt,
@@ -454,19 +522,21 @@ int tbik_gemm_mxfp4(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
     if (!Y) return TBIK_ERR_NULL;
     if (ldy < N) return TBIK_ERR_SHAPE;
     if (!aligned(Y, y_dtype == TBIK_F32 ? 4 : 2)) return TBIK_ERR_ALIGN;
-    const size_t need = tbik_gemm_mxfp4_workspace_bytes(M, N, K, leaf, k_first);
+    const size_t scales_room = mxfp4_scales_room(M, N, K);
+    const size_t need = mx_planes_bytes(M, N, internal_split(M, N, K, ns)) + scales_room;      // more room may allow a better split
     if (need > 0 && (!workspace || workspace_bytes < need)) return TBIK_ERR_WORKSPACE;
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)hip_stream;
     GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)Wt, ldwt, nullptr, Y, ldy, (int)y_dtype, M, N, K, sl, ns, 1, TBIK_MXFP4, 0};
     const Mxfp4Scales sc{(const uint8_t *)Xs, ldxs, (const uint8_t *)Ws, ldws};
-    const int split = internal_split(M, N, K, ns);
-    const int rows = fp8_tile_rows(M, N);
+    const size_t room = workspace_bytes >= scales_room + 255 ? workspace_bytes - scales_room - 255 : 0;      // (planes are rounded up to 256 bytes)
+    const TilePlan plan = tile_plan(OPERANDS_MXFP4, M, N, K, ns, 0, workspace ? room : 0);
+    const int split = plan.split, rows = plan.rows;
     GemmArgs probe = a;
     probe.P = split;
     const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_mxfp4_tiled_supports(probe, sc);
     hipError_t e;
-    void *retiled = (tiled && mx_retiles(M)) ? static_cast<char *>(workspace) + mx_planes_bytes(M, N, K, leaf, k_first) : nullptr;
+    void *retiled = (tiled && mx_retiles(M)) ? static_cast<char *>(workspace) + mx_planes_bytes(M, N, split) : nullptr;
     if (!tiled) {
         e = launch_gemm_mxfp4_reference(a, sc, s);
     } else if (split == 1) {
@@ -494,11 +564,9 @@ int tbik_gemm_shard_partials_mxfp4(const void *X, int64_t ldx, const void *Xs, i
     GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)Wt, ldwt, partials, nullptr, 0, TBIK_F32, M, N, K, sl, ns, P, TBIK_MXFP4, 0};
     const Mxfp4Scales sc{(const uint8_t *)Xs, ldxs, (const uint8_t *)Ws, ldws};
     const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_mxfp4_tiled_supports(a, sc);
-    // a workspace as tbik_gemm_mxfp4 takes it has room for the re-tiled scales behind the planes of the K cut
-    void *retiled = (tiled && mx_retiles(M) && workspace && aligned(workspace, 256) &&
-                     workspace_bytes >= tbik_gemm_mxfp4_workspace_bytes(M, N, K, leaf, k_first))
-                        ? static_cast<char *>(workspace) + mx_planes_bytes(M, N, K, leaf, k_first) : nullptr;
-    hipError_t e = tiled ? launch_gemm_mxfp4_tiled(a, sc, fp8_tile_rows(M, N), retiled, (hipStream_t)hip_stream)
+    // a workspace as tbik_gemm_mxfp4 takes it has room for the re-tiled scales
+    void *retiled = (tiled && mx_retiles(M) && workspace && aligned(workspace, 256) && workspace_bytes >= mxfp4_scales_room(M, N, K)) ? workspace : nullptr;
+    hipError_t e = tiled ? launch_gemm_mxfp4_tiled(a, sc, tile_plan(OPERANDS_MXFP4, M, N, K, ns, P, 0).rows, retiled, (hipStream_t)hip_stream)
                          : launch_gemm_mxfp4_reference(a, sc, (hipStream_t)hip_stream);
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
@@ -532,10 +600,11 @@ static int mxfp8_checks(int x_dtype, const void *X, int64_t ldx, const void *Xs,
     return TBIK_OK;
 }
 
+static size_t mxfp8_scales_room(int M, int N, int K) { return mx_retiles(M) && K % 128 == 0 ? mxfp8_retiled_scales_bytes(M, N, K) : 0; }
 size_t tbik_gemm_mxfp8_workspace_bytes(int M, int N, int K, int leaf, int k_first) {
     int sl, ns;
     if (check_tree(M, N, K, leaf, k_first, 1, &sl, &ns) != TBIK_OK) return 0;
-    return mx_planes_bytes(M, N, K, leaf, k_first) + (mx_retiles(M) && K % 128 == 0 ? mxfp8_retiled_scales_bytes(M, N, K) : 0);
+    return mx_planes_bytes(M, N, std::max(internal_split(M, N, K, ns), tile_plan(OPERANDS_MXFP8, M, N, K, ns, 0, SIZE_MAX).split)) + mxfp8_scales_room(M, N, K);
 }
 
 int tbik_gemm_mxfp8(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, const void *Wt, int64_t ldwt,
@@ -550,19 +619,21 @@ int tbik_gemm_mxfp8(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
     if (!Y) return TBIK_ERR_NULL;
     if (ldy < N) return TBIK_ERR_SHAPE;
     if (!aligned(Y, y_dtype == TBIK_F32 ? 4 : 2)) return TBIK_ERR_ALIGN;
-    const size_t need = tbik_gemm_mxfp8_workspace_bytes(M, N, K, leaf, k_first);
+    const size_t scales_room = mxfp8_scales_room(M, N, K);
+    const size_t need = mx_planes_bytes(M, N, internal_split(M, N, K, ns)) + scales_room;      // more room may allow a better split
     if (need > 0 && (!workspace || workspace_bytes < need)) return TBIK_ERR_WORKSPACE;
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)hip_stream;
     GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)Wt, ldwt, nullptr, Y, ldy, (int)y_dtype, M, N, K, sl, ns, 1, (int)x_dtype, 0};
     const Mxfp4Scales sc{(const uint8_t *)Xs, ldxs, (const uint8_t *)Ws, ldws};
-    const int split = internal_split(M, N, K, ns);
-    const int rows = fp8_tile_rows(M, N);
+    const size_t room = workspace_bytes >= scales_room + 255 ? workspace_bytes - scales_room - 255 : 0;      // (planes are rounded up to 256 bytes)
+    const TilePlan plan = tile_plan(OPERANDS_MXFP8, M, N, K, ns, 0, workspace ? room : 0);
+    const int split = plan.split, rows = plan.rows;
     GemmArgs probe = a;
     probe.P = split;
     const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_mxfp8_tiled_supports(probe, sc);
     hipError_t e;
-    void *retiled = (tiled && mx_retiles(M)) ? static_cast<char *>(workspace) + mx_planes_bytes(M, N, K, leaf, k_first) : nullptr;
+    void *retiled = (tiled && mx_retiles(M)) ? static_cast<char *>(workspace) + mx_planes_bytes(M, N, split) : nullptr;
     if (!tiled) {
         e = launch_gemm_mxfp8_reference(a, sc, s);
     } else if (split == 1) {
@@ -590,11 +661,9 @@ int tbik_gemm_shard_partials_mxfp8(const void *X, int64_t ldx, const void *Xs, i
     GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)Wt, ldwt, partials, nullptr, 0, TBIK_F32, M, N, K, sl, ns, P, (int)x_dtype, 0};
     const Mxfp4Scales sc{(const uint8_t *)Xs, ldxs, (const uint8_t *)Ws, ldws};
     const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_mxfp8_tiled_supports(a, sc);
-    // a workspace as tbik_gemm_mxfp8 takes it has room for the re-tiled scales behind the planes of the K cut
-    void *retiled = (tiled && mx_retiles(M) && workspace && aligned(workspace, 256) &&
-                     workspace_bytes >= tbik_gemm_mxfp8_workspace_bytes(M, N, K, leaf, k_first))
-                        ? static_cast<char *>(workspace) + mx_planes_bytes(M, N, K, leaf, k_first) : nullptr;
-    hipError_t e = tiled ? launch_gemm_mxfp8_tiled(a, sc, fp8_tile_rows(M, N), retiled, (hipStream_t)hip_stream)
+    // a workspace as tbik_gemm_mxfp8 takes it has room for the re-tiled scales
+    void *retiled = (tiled && mx_retiles(M) && workspace && aligned(workspace, 256) && workspace_bytes >= mxfp8_scales_room(M, N, K)) ? workspace : nullptr;
+    hipError_t e = tiled ? launch_gemm_mxfp8_tiled(a, sc, tile_plan(OPERANDS_MXFP8, M, N, K, ns, P, 0).rows, retiled, (hipStream_t)hip_stream)
                          : launch_gemm_mxfp8_reference(a, sc, (hipStream_t)hip_stream);
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
@@ -617,16 +686,7 @@ int tbik_gemm_reference_mxfp8(const void *X, int64_t ldx, const void *Xs, int64_
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
 
-// ---- MXFP6 operands: one tile shape (128 x 128), so the K cut is that of a 128-row tile whatever M ----
-static int mxfp6_split(int M, int N, int ns) {
-    const int64_t tiles = (((int64_t)M + 127) / 128) * (((int64_t)N + 127) / 128);
-    int split = 1;
-    while (ns / split > 16 && split < TBIK_MAX_SHARDS) split *= 2;     // the tiled kernel walks at most 16 superleaves per shard
-    if (tiles >= 128) return split;
-    while (split < ns && split < 16 && tiles * split < 256) split *= 2;
-    return split;
-}
-
+// ---- MXFP6 operands ----
 static int mxfp6_checks(int x_dtype, const void *X, int64_t ldx, const void *Xs, int64_t ldxs, const void *Wt, int64_t ldwt,
                         const void *Ws, int64_t ldws, int M, int N, int K, int leaf, int k_first, int P, int *sl, int *ns) {
     int rc = check_tree(M, N, K, leaf, k_first, P, sl, ns);
@@ -640,12 +700,11 @@ static int mxfp6_checks(int x_dtype, const void *X, int64_t ldx, const void *Xs,
     return TBIK_OK;
 }
 
+static size_t mxfp6_scales_room(int M, int N, int K) { return mx_retiles(M) && K % 128 == 0 ? mxfp6_retiled_scales_bytes(M, N, K) : 0; }
 size_t tbik_gemm_mxfp6_workspace_bytes(int M, int N, int K, int leaf, int k_first) {
     int sl, ns;
     if (check_tree(M, N, K, leaf, k_first, 1, &sl, &ns) != TBIK_OK) return 0;
-    const int split = mxfp6_split(M, N, ns);
-    const size_t planes = split > 1 ? (((size_t)split * (size_t)M * (size_t)N * sizeof(float) + 255) & ~(size_t)255) : 0;
-    return planes + (mx_retiles(M) && K % 128 == 0 ? mxfp6_retiled_scales_bytes(M, N, K) : 0);
+    return mx_planes_bytes(M, N, std::max(mxfp6_split(M, N, ns), tile_plan(OPERANDS_MXFP6, M, N, K, ns, 0, SIZE_MAX).split)) + mxfp6_scales_room(M, N, K);
 }
 
 int tbik_gemm_mxfp6(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, const void *Wt, int64_t ldwt,
@@ -660,18 +719,19 @@ int tbik_gemm_mxfp6(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
     if (!Y) return TBIK_ERR_NULL;
     if (ldy < N) return TBIK_ERR_SHAPE;
     if (!aligned(Y, y_dtype == TBIK_F32 ? 4 : 2)) return TBIK_ERR_ALIGN;
-    const size_t need = tbik_gemm_mxfp6_workspace_bytes(M, N, K, leaf, k_first);
+    const size_t scales_room = mxfp6_scales_room(M, N, K);
+    const size_t need = mx_planes_bytes(M, N, mxfp6_split(M, N, ns)) + scales_room;      // more room may allow a better split
     if (need > 0 && (!workspace || workspace_bytes < need)) return TBIK_ERR_WORKSPACE;
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)hip_stream;
     GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)Wt, ldwt, nullptr, Y, ldy, (int)y_dtype, M, N, K, sl, ns, 1, (int)x_dtype, 0};
     const Mxfp4Scales sc{(const uint8_t *)Xs, ldxs, (const uint8_t *)Ws, ldws};
-    const int split = mxfp6_split(M, N, ns);
+    const size_t room = workspace_bytes >= scales_room + 255 ? workspace_bytes - scales_room - 255 : 0;      // (planes are rounded up to 256 bytes)
+    const int split = tile_plan(OPERANDS_MXFP6, M, N, K, ns, 0, workspace ? room : 0).split;
     GemmArgs probe = a;
     probe.P = split;
     const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_mxfp6_tiled_supports(probe, sc);
-    const size_t planes = split > 1 ? (((size_t)split * (size_t)M * (size_t)N * sizeof(float) + 255) & ~(size_t)255) : 0;
-    void *retiled = (tiled && mx_retiles(M)) ? static_cast<char *>(workspace) + planes : nullptr;
+    void *retiled = (tiled && mx_retiles(M)) ? static_cast<char *>(workspace) + mx_planes_bytes(M, N, split) : nullptr;
     hipError_t e;
     if (!tiled) {
         e = launch_gemm_mxfp6_reference(a, sc, s);
@@ -700,12 +760,8 @@ int tbik_gemm_shard_partials_mxfp6(const void *X, int64_t ldx, const void *Xs, i
     GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)Wt, ldwt, partials, nullptr, 0, TBIK_F32, M, N, K, sl, ns, P, (int)x_dtype, 0};
     const Mxfp4Scales sc{(const uint8_t *)Xs, ldxs, (const uint8_t *)Ws, ldws};
     const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_mxfp6_tiled_supports(a, sc);
-    // a workspace as tbik_gemm_mxfp6 takes it has room for the re-tiled scales behind the planes of the K cut
-    const int own_split = mxfp6_split(M, N, ns);
-    const size_t planes = own_split > 1 ? (((size_t)own_split * (size_t)M * (size_t)N * sizeof(float) + 255) & ~(size_t)255) : 0;
-    void *retiled = (tiled && mx_retiles(M) && workspace && aligned(workspace, 256) &&
-                     workspace_bytes >= tbik_gemm_mxfp6_workspace_bytes(M, N, K, leaf, k_first))
-                        ? static_cast<char *>(workspace) + planes : nullptr;
+    // a workspace as tbik_gemm_mxfp6 takes it has room for the re-tiled scales
+    void *retiled = (tiled && mx_retiles(M) && workspace && aligned(workspace, 256) && workspace_bytes >= mxfp6_scales_room(M, N, K)) ? workspace : nullptr;
     hipError_t e = tiled ? launch_gemm_mxfp6_tiled(a, sc, retiled, (hipStream_t)hip_stream)
                          : launch_gemm_mxfp6_reference(a, sc, (hipStream_t)hip_stream);
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
@@ -736,7 +792,7 @@ static int swiglu_route(int dtype, int M, int I, int K, int sl, int ns, int *spl
     const int N = 2 * I;
     GemmArgs probe{nullptr, K, nullptr, N, nullptr, nullptr, I, dtype, M, N, K, sl, ns, 1, dtype, 0};
     probe.P = *split = internal_split(M, N, K, ns);
-    if (*split > 1) return pick_variant(probe) != VARIANT_REFERENCE ? SWIGLU_SPLIT : SWIGLU_STAGED;
+    if (*split > 1) return pick_variant(probe, tile_rows(M, N)) != VARIANT_REFERENCE ? SWIGLU_SPLIT : SWIGLU_STAGED;
     probe.swiglu = 1;
     return (tile_rows(M, N) == 128 && g_forced_variant.load() == VARIANT_AUTO && gemm_tiled_supports(probe, VARIANT_T128))
                ? SWIGLU_FUSED : SWIGLU_STAGED;
@@ -796,7 +852,7 @@ int tbik_gemm_swiglu(const void *X, int64_t ldx, const void *W_gu, int64_t ldw, 
         a.partials = reinterpret_cast<float *>(workspace);
         a.Y = nullptr;
         a.P = split;
-        e = launch_tiled(a, pick_variant(a), s);
+        e = launch_tiled(a, pick_variant(a, tile_rows(M, N)), s);
         if (e == hipSuccess) e = launch_tree_combine_swiglu(a.partials, split, (uint16_t *)act, lda, (int)dtype, M, I, s);
     } else {
         uint16_t *staged = reinterpret_cast<uint16_t *>(workspace);

@@ -1,0 +1,60 @@
+"""Whatever tile height and K split the time model chooses for 16-, 8-, 6- and 4-bit operands, a call gives the bits of the
+reference kernel (0 differing bits), at batch sizes around the edges of the tile heights and of rounds of 256 work items;
+also with a workspace that holds only the planes of the older rule's split, or nothing but what the call insists on."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as gu
+from paper_2511_17826_amd import binding as tb
+from paper_2511_17826_amd import synthetic as syn
+
+pytestmark = pytest.mark.gpu
+
+K, N, LEAF = 2048, 1536, 256
+
+
+@pytest.mark.parametrize("M", [1, 31, 33, 64, 65, 97, 129, 200, 300, 700])
+def test_16_bit(M):
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(M)
+    for dt, call, ref, partials in ((torch.bfloat16, tb.tbik_gemm, tb.tbik_gemm_reference, tb.tbik_gemm_shard_partials),
+                                    (torch.float16, tb.tbik_gemm_f16, tb.tbik_gemm_reference_f16, tb.tbik_gemm_shard_partials_f16)):
+        X = torch.randn((M, K), generator=g, device="cuda:0").to(dt)
+        W = (torch.randn((K, N), generator=g, device="cuda:0") * 0.02).to(dt)
+        want = ref(X, W, LEAF, 1, out_dtype=torch.float32)[1].view(torch.int32)
+        assert torch.equal(call(X, W, LEAF, 1, out_dtype=torch.float32).view(torch.int32), want)
+        full, done = tb.gemm_workspace_bytes(M, N, K, LEAF, 1), 0
+        for planes in (8, 4, 2, 1):
+            if planes * M * N * 4 > full:
+                continue
+            ws = torch.full((planes * M * N,), float("nan"), dtype=torch.float32, device="cuda:0")
+            try:
+                out = call(X, W, LEAF, 1, out_dtype=torch.float32, workspace=ws)
+            except tb.TbikError:
+                continue
+            done += 1
+            assert torch.equal(out.view(torch.int32), want), planes
+        for P in (1, 2, 8):
+            assert torch.equal(tb.tbik_tree_combine(partials(X, W, LEAF, 1, P), out_dtype=torch.float32).view(torch.int32), want), P
+
+
+@pytest.mark.parametrize("kind", ["fp8", "mxfp8", "mxfp6", "mxfp4"])
+@pytest.mark.parametrize("M", [1, 33, 65, 100, 129, 300, 700])
+def test_low_bit(kind, M):
+    if kind == "fp8":
+        X, W = syn.gemm_random_fp8(M, M, K, N)
+        ops = (X, W.T)                                            # the calls take the transposed weight
+        dev = [torch.from_numpy(np.ascontiguousarray(t)).to("cuda:0") for t in ops]
+        call, ref, parts, need = tb.tbik_gemm_fp8, tb.tbik_gemm_reference_fp8, tb.tbik_gemm_shard_partials_fp8, tb.gemm_fp8_workspace_bytes
+    else:
+        ops = getattr(syn, "gemm_random_" + kind)(M, M, K, N, scale_spread=2)
+        dev = [torch.from_numpy(np.ascontiguousarray(t)).to("cuda:0") for t in ops]
+        call, ref, parts, need = (getattr(tb, n % kind) for n in ("tbik_gemm_%s", "tbik_gemm_reference_%s", "tbik_gemm_shard_partials_%s",
+                                                                  "gemm_%s_workspace_bytes"))
+    want = ref(*dev, LEAF, 1)[0].view(torch.int32)
+    assert torch.equal(call(*dev, LEAF, 1, out_dtype=torch.float32).view(torch.int32), want)
+    ws = torch.full((max(256, need(M, N, K, LEAF, 1)) // 4,), float("nan"), dtype=torch.float32, device="cuda:0")
+    assert torch.equal(call(*dev, LEAF, 1, out_dtype=torch.float32, workspace=ws).view(torch.int32), want)
+    for P in (2, 8):
+        assert torch.equal(tb.tbik_tree_combine(parts(*dev, LEAF, 1, P), out_dtype=torch.float32).view(torch.int32), want), P
