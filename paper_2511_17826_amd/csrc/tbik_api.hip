@@ -120,13 +120,14 @@ struct TileModel {
     double step[3], fill;               // us: a stage of a 32-, 64-, 128-row tile; pipeline fill and epilogue of an item
     double intake;                      // bytes of W per us and compute unit, in thousands
     double combine, rate;               // us; bytes of planes per us, in millions
+    double retile;                      // us: the scales' re-tiling from 128 rows on
 };
 constexpr TileModel kTileModels[] = {
-    {64, 2.0, {0.005, 0.21, 0.525}, 5.9, 38.5, 3.95, 12.0},
-    {128, 1.0, {0.01, 0.24, 0.33}, 3.1, 51.0, 2.7, 1.2},
-    {128, 1.0, {0.0, 0.185, 0.375}, 3.6, 42.0, 4.8, 2.5},
-    {256, 0.5, {0.31, 0.335, 0.574}, 4.1, 31.4, 2.64, 2.7},
-    {128, 0.75, {0.0, 0.0, 0.61}, 3.6, 36.0, 4.8, 2.5},            // one height; MXFP8's with its stage
+    {64, 2.0, {0.005, 0.21, 0.525}, 5.9, 38.5, 3.95, 12.0, 0.0},
+    {128, 1.0, {0.01, 0.24, 0.33}, 3.1, 51.0, 2.7, 1.2, 0.0},
+    {128, 1.0, {0.0, 0.185, 0.375}, 3.6, 42.0, 4.8, 2.5, 4.0},
+    {256, 0.5, {0.31, 0.335, 0.574}, 4.1, 31.4, 2.64, 2.7, 4.0},
+    {128, 0.75, {0.0, 0.0, 0.61}, 3.6, 36.0, 4.8, 2.5, 4.0},       // one height; MXFP8's with its stage
 };
 
 // Bytes of the fp32 planes of a K split.
@@ -136,7 +137,7 @@ double tile_plan_us(const TileModel &m, int M, int N, int K, TilePlan p) {
     const double items = (double)((M + p.rows - 1) / p.rows) * ((N + 127) / 128) * p.split;
     const double stages = (double)K / m.stage_k / p.split, weights = 128.0 * K / p.split * m.bytes_per_k;
     const double step = m.step[p.rows == 32 ? 0 : p.rows == 64 ? 1 : 2];
-    return std::ceil(items / 256.0) * std::max(stages * step + m.fill, weights / (m.intake * 1e3)) +
+    return m.retile * (M >= 128) + std::ceil(items / 256.0) * std::max(stages * step + m.fill, weights / (m.intake * 1e3)) +
            (p.split > 1 ? m.combine + (double)p.split * M * N * 4.0 / (m.rate * 1e6) : 0.0);
 }
 
@@ -167,7 +168,7 @@ TilePlan tile_plan(Operands kind, int M, int N, int K, int ns, int only_split, s
     if (g_forced_variant.load() != VARIANT_AUTO || M <= 0 || N <= 0) return rule;
     const TileModel &m = kTileModels[kind];
     TilePlan best = rule;
-    double best_us = tile_plan_us(m, M, N, K, rule) / 1.04;
+    double best_us = only_split > 0 || split_planes_bytes(M, N, rule.split) <= room ? tile_plan_us(m, M, N, K, rule) / 1.04 : 1e30;
     for (int rows = one_height ? 128 : 32; rows <= 128; rows *= 2) {
         for (int split = only_split > 0 ? only_split : 1; split <= ns && split <= 16; split *= 2) {
             if (ns / split <= 16 && (only_split > 0 || split_planes_bytes(M, N, split) <= room)) {     // a tile walks at most 16 superleaves
@@ -179,7 +180,37 @@ TilePlan tile_plan(Operands kind, int M, int N, int K, int ns, int only_split, s
     }
     return best;
 }
-TilePlan tile_rule(int M, int N, int K, int ns) { return {forced_rows(tile_rows(M, N)), internal_split(M, N, K, ns)}; }
+// Rows of a batch that are better computed by a call of their own (0: none): a launch whose last round of tiles is nearly
+// empty is cut behind its last full round, and the remaining rows get the height and split of a small batch.  1100 rows
+// of 4096 x 4096 in bf16 are 288 tiles of 128 rows, two rounds, 72 us; as 1024 rows and 76 rows 54 us.  (The rows of
+// a result do not depend on each other, so neither do their bits.)
+constexpr double kPieceUs = 2.0;        // what a launch behind another costs
+int last_rows(Operands kind, int M, int N, int K, int ns, size_t room) {
+    const int cols = (N + 127) / 128, per_round = 256 / cols;                    // row tiles of 128 in a round
+    if (g_forced_variant.load() != VARIANT_AUTO || per_round < 1 || ns > 16 || M <= per_round * 128) return 0;
+    const int rest = M % (per_round * 128), full = M - rest;
+    if (rest == 0) return 0;
+    const TileModel &m = kTileModels[kind];
+    const double whole = tile_plan_us(m, M, N, K, tile_plan(kind, M, N, K, ns, 0, room));
+    const double pieces = tile_plan_us(m, full, N, K, tile_plan(kind, full, N, K, ns, 0, room)) +
+                          tile_plan_us(m, rest, N, K, tile_plan(kind, rest, N, K, ns, 0, room)) + kPieceUs;
+    return pieces < 0.95 * whole ? rest : 0;
+}
+// Bytes of planes a call can make use of, the older rule's included.
+size_t plan_planes_bytes(Operands kind, int M, int N, int K, int ns) {
+    size_t bytes = std::max(split_planes_bytes(M, N, kind == OPERANDS_MXFP6 ? mxfp6_split(M, N, ns) : internal_split(M, N, K, ns)),
+                            split_planes_bytes(M, N, tile_plan(kind, M, N, K, ns, 0, SIZE_MAX).split));
+    if (const int rest = last_rows(kind, M, N, K, ns, SIZE_MAX))
+        bytes = std::max(bytes, split_planes_bytes(rest, N, tile_plan(kind, rest, N, K, ns, 0, SIZE_MAX).split));
+    return bytes;
+}
+// Calls piece(first row, rows) for the one or two pieces of a batch.
+template <class Piece>
+hipError_t in_pieces(Operands kind, int M, int N, int K, int ns, size_t room, Piece piece) {
+    const int rest = last_rows(kind, M, N, K, ns, room);
+    hipError_t e = piece(0, M - rest);
+    return (e == hipSuccess && rest > 0) ? piece(M - rest, rest) : e;
+}
 
 // fp32 operands: tile height and K split of a shape (pure), by a model of the time.  The fp32 MFMA is slow (a K-step of 32
 // takes a 128-row tile 1.9 us and a 32-row tile 0.585 us, of which two tiles side by side on a compute unit lose nothing),
@@ -234,8 +265,7 @@ size_t tbik_gemm_workspace_bytes(int M, int N, int K, int leaf, int k_first) {
     int sl, ns;
     if (check_tree(M, N, K, leaf, k_first, 1, &sl, &ns) != TBIK_OK) return 0;
     // fp32 partials of the internal K split, if this shape uses one (16-bit or fp32 operands: the larger of the two)
-    return split_planes_bytes(M, N, std::max({internal_split(M, N, K, ns), tile_plan(OPERANDS_16BIT, M, N, K, ns, 0, SIZE_MAX).split,
-                                              f32_plan(M, N, K, ns).split}));
+    return std::max(plan_planes_bytes(OPERANDS_16BIT, M, N, K, ns), split_planes_bytes(M, N, f32_plan(M, N, K, ns).split));
 }
 
 }  // extern "C"
@@ -272,32 +302,32 @@ int gemm(int x_dtype, const void *X, int64_t ldx, const void *W, int64_t ldw, vo
     if (!Y) return TBIK_ERR_NULL;
     if (ldy < N) return TBIK_ERR_SHAPE;
     if (!aligned(Y, y_dtype == TBIK_F32 ? 4 : 2)) return TBIK_ERR_ALIGN;
-    TilePlan plan = tile_rule(M, N, K, ns);
-    const size_t need = split_planes_bytes(M, N, plan.split);
+    const size_t need = split_planes_bytes(M, N, internal_split(M, N, K, ns));       // more room may allow a better split
     if (need > 0 && (!workspace || workspace_bytes < need)) return TBIK_ERR_WORKSPACE;
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
-    if (x_dtype == TBIK_F32) {                          // its own split, unless the caller brought no room for it
-        const int own = f32_plan(M, N, K, ns).split;
-        if (own == 1 || (workspace && workspace_bytes >= split_planes_bytes(M, N, own))) plan.split = own;
-    } else {
-        plan = tile_plan(OPERANDS_16BIT, M, N, K, ns, 0, workspace ? workspace_bytes : 0);
-    }
-    const int split = plan.split;
-
+    const size_t room = workspace ? workspace_bytes : 0;
     hipStream_t s = (hipStream_t)hip_stream;
-    GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)W, ldw, nullptr, Y, ldy, y_dtype, M, N, K, sl, ns, 1, x_dtype};
-    GemmArgs probe = a;
-    probe.P = split;
-    const int v = pick_variant(probe, plan.rows);
-    hipError_t e;
-    if (split == 1 || v == VARIANT_REFERENCE) {
-        e = (v == VARIANT_REFERENCE) ? launch_reference(a, s) : launch_tiled(a, v, s);
-    } else {
+    auto rows_with = [&](int m0, int m, TilePlan plan) {
+        void *y = static_cast<char *>(Y) + (int64_t)m0 * ldy * (y_dtype == TBIK_F32 ? 4 : 2);
+        const char *x = static_cast<const char *>(X) + (int64_t)m0 * ldx * (x_dtype == TBIK_F32 ? 4 : 2);
+        GemmArgs a{(const uint16_t *)x, ldx, (const uint16_t *)W, ldw, nullptr, y, ldy, y_dtype, m, N, K, sl, ns, 1, x_dtype};
+        GemmArgs probe = a;
+        probe.P = plan.split;
+        const int v = pick_variant(probe, plan.rows);
+        if (v == VARIANT_REFERENCE) return launch_reference(a, s);
+        if (plan.split == 1) return launch_tiled(a, v, s);
         a.partials = reinterpret_cast<float *>(workspace);
         a.Y = nullptr;
-        a.P = split;
-        e = launch_tiled(a, v, s);
-        if (e == hipSuccess) e = launch_tree_combine(a.partials, split, Y, ldy, y_dtype, M, N, s);
+        a.P = plan.split;
+        hipError_t e = launch_tiled(a, v, s);
+        return e == hipSuccess ? launch_tree_combine(a.partials, plan.split, y, ldy, y_dtype, m, N, s) : e;
+    };
+    hipError_t e;
+    if (x_dtype == TBIK_F32) {                          // its own split, unless the caller brought no room for it
+        const int own = f32_plan(M, N, K, ns).split;
+        e = rows_with(0, M, {0, own == 1 || split_planes_bytes(M, N, own) <= room ? own : internal_split(M, N, K, ns)});
+    } else {
+        e = in_pieces(OPERANDS_16BIT, M, N, K, ns, room, [&](int m0, int m) { return rows_with(m0, m, tile_plan(OPERANDS_16BIT, m, N, K, ns, 0, room)); });
     }
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
@@ -413,7 +443,7 @@ static int fp8_checks(int x_dtype, const void *X, int64_t ldx, const void *Wt, i
 size_t tbik_gemm_fp8_workspace_bytes(int M, int N, int K, int leaf, int k_first) {
     int sl, ns;
     if (check_tree(M, N, K, leaf, k_first, 1, &sl, &ns) != TBIK_OK) return 0;
-    return split_planes_bytes(M, N, std::max(internal_split(M, N, K, ns), tile_plan(OPERANDS_FP8, M, N, K, ns, 0, SIZE_MAX).split));
+    return plan_planes_bytes(OPERANDS_FP8, M, N, K, ns);
 }
 
 int tbik_gemm_fp8(const void *X, int64_t ldx, const void *Wt, int64_t ldwt, void *Y, int64_t ldy,
@@ -431,24 +461,22 @@ int tbik_gemm_fp8(const void *X, int64_t ldx, const void *Wt, int64_t ldwt, void
     if (need > 0 && (!workspace || workspace_bytes < need)) return TBIK_ERR_WORKSPACE;
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)hip_stream;
-    GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)Wt, ldwt, nullptr, Y, ldy, (int)y_dtype, M, N, K, sl, ns, 1, (int)x_dtype, 0};
-    const TilePlan plan = tile_plan(OPERANDS_FP8, M, N, K, ns, 0, workspace ? workspace_bytes : 0);
-    const int split = plan.split, rows = plan.rows;
-    GemmArgs probe = a;
-    probe.P = split;
-    const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_fp8_tiled_supports(probe);
-    hipError_t e;
-    if (!tiled) {
-        e = launch_gemm_fp8_reference(a, s);
-    } else if (split == 1) {
-        e = launch_gemm_fp8_tiled(a, rows, s);
-    } else {
+    const size_t room = workspace ? workspace_bytes : 0;
+    hipError_t e = in_pieces(OPERANDS_FP8, M, N, K, ns, room, [&](int m0, int m) {
+        const TilePlan plan = tile_plan(OPERANDS_FP8, m, N, K, ns, 0, room);
+        void *y = static_cast<char *>(Y) + (int64_t)m0 * ldy * (y_dtype == TBIK_F32 ? 4 : 2);
+        GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
+                   (int)y_dtype, m, N, K, sl, ns, 1, (int)x_dtype, 0};
+        GemmArgs probe = a;
+        probe.P = plan.split;
+        if (g_forced_variant.load() == VARIANT_REFERENCE || !gemm_fp8_tiled_supports(probe)) return launch_gemm_fp8_reference(a, s);
+        if (plan.split == 1) return launch_gemm_fp8_tiled(a, plan.rows, s);
         a.partials = reinterpret_cast<float *>(workspace);
         a.Y = nullptr;
-        a.P = split;
-        e = launch_gemm_fp8_tiled(a, rows, s);
-        if (e == hipSuccess) e = launch_tree_combine(a.partials, split, Y, ldy, (int)y_dtype, M, N, s);
-    }
+        a.P = plan.split;
+        hipError_t pe = launch_gemm_fp8_tiled(a, plan.rows, s);
+        return pe == hipSuccess ? launch_tree_combine(a.partials, plan.split, y, ldy, (int)y_dtype, m, N, s) : pe;
+    });
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
 
@@ -502,12 +530,12 @@ static int mxfp4_checks(const void *X, int64_t ldx, const void *Xs, int64_t ldxs
 // From 128 rows on the microscaling GEMMs re-tile their scales first (a launch of its own, which a small batch would
 // feel): the workspace is the fp32 planes of the K split, rounded up to 256 bytes, then the re-tiled scales.
 static bool mx_retiles(int M) { return M >= 128; }
-static size_t mx_planes_bytes(int M, int N, int split) { return (split_planes_bytes(M, N, split) + 255) & ~(size_t)255; }
+static size_t round_256(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
 static size_t mxfp4_scales_room(int M, int N, int K) { return mx_retiles(M) && K % 256 == 0 ? mxfp4_retiled_scales_bytes(M, N, K) : 0; }
 size_t tbik_gemm_mxfp4_workspace_bytes(int M, int N, int K, int leaf, int k_first) {
     int sl, ns;
     if (check_tree(M, N, K, leaf, k_first, 1, &sl, &ns) != TBIK_OK) return 0;
-    return mx_planes_bytes(M, N, std::max(internal_split(M, N, K, ns), tile_plan(OPERANDS_MXFP4, M, N, K, ns, 0, SIZE_MAX).split)) + mxfp4_scales_room(M, N, K);
+    return round_256(plan_planes_bytes(OPERANDS_MXFP4, M, N, K, ns)) + mxfp4_scales_room(M, N, K);
 }
 
 int tbik_gemm_mxfp4(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, const void *Wt, int64_t ldwt,
@@ -523,31 +551,29 @@ int tbik_gemm_mxfp4(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
     if (ldy < N) return TBIK_ERR_SHAPE;
     if (!aligned(Y, y_dtype == TBIK_F32 ? 4 : 2)) return TBIK_ERR_ALIGN;
     const size_t scales_room = mxfp4_scales_room(M, N, K);
-    const size_t need = mx_planes_bytes(M, N, internal_split(M, N, K, ns)) + scales_room;      // more room may allow a better split
+    const size_t need = round_256(split_planes_bytes(M, N, internal_split(M, N, K, ns))) + scales_room;      // more room may allow a better split
     if (need > 0 && (!workspace || workspace_bytes < need)) return TBIK_ERR_WORKSPACE;
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)hip_stream;
-    GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)Wt, ldwt, nullptr, Y, ldy, (int)y_dtype, M, N, K, sl, ns, 1, TBIK_MXFP4, 0};
-    const Mxfp4Scales sc{(const uint8_t *)Xs, ldxs, (const uint8_t *)Ws, ldws};
-    const size_t room = workspace_bytes >= scales_room + 255 ? workspace_bytes - scales_room - 255 : 0;      // (planes are rounded up to 256 bytes)
-    const TilePlan plan = tile_plan(OPERANDS_MXFP4, M, N, K, ns, 0, workspace ? room : 0);
-    const int split = plan.split, rows = plan.rows;
-    GemmArgs probe = a;
-    probe.P = split;
-    const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_mxfp4_tiled_supports(probe, sc);
-    hipError_t e;
-    void *retiled = (tiled && mx_retiles(M)) ? static_cast<char *>(workspace) + mx_planes_bytes(M, N, split) : nullptr;
-    if (!tiled) {
-        e = launch_gemm_mxfp4_reference(a, sc, s);
-    } else if (split == 1) {
-        e = launch_gemm_mxfp4_tiled(a, sc, rows, retiled, s);
-    } else {
+    const size_t room = workspace && workspace_bytes > scales_room ? (workspace_bytes - scales_room) & ~(size_t)255 : 0;      // planes are rounded up to 256 bytes
+    hipError_t e = in_pieces(OPERANDS_MXFP4, M, N, K, ns, room, [&](int m0, int m) {
+        const TilePlan plan = tile_plan(OPERANDS_MXFP4, m, N, K, ns, 0, room);
+        void *y = static_cast<char *>(Y) + (int64_t)m0 * ldy * (y_dtype == TBIK_F32 ? 4 : 2);
+        GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
+                   (int)y_dtype, m, N, K, sl, ns, 1, TBIK_MXFP4, 0};
+        const Mxfp4Scales sc{static_cast<const uint8_t *>(Xs) + (int64_t)m0 * ldxs, ldxs, (const uint8_t *)Ws, ldws};
+        GemmArgs probe = a;
+        probe.P = plan.split;
+        if (g_forced_variant.load() == VARIANT_REFERENCE || !gemm_mxfp4_tiled_supports(probe, sc)) return launch_gemm_mxfp4_reference(a, sc, s);
+        // (the second piece's re-tiled scales may take the first one's place: the stream has passed the first by then)
+        void *retiled = mx_retiles(m) ? static_cast<char *>(workspace) + round_256(split_planes_bytes(m, N, plan.split)) : nullptr;
+        if (plan.split == 1) return launch_gemm_mxfp4_tiled(a, sc, plan.rows, retiled, s);
         a.partials = reinterpret_cast<float *>(workspace);
         a.Y = nullptr;
-        a.P = split;
-        e = launch_gemm_mxfp4_tiled(a, sc, rows, retiled, s);
-        if (e == hipSuccess) e = launch_tree_combine(a.partials, split, Y, ldy, (int)y_dtype, M, N, s);
-    }
+        a.P = plan.split;
+        hipError_t pe = launch_gemm_mxfp4_tiled(a, sc, plan.rows, retiled, s);
+        return pe == hipSuccess ? launch_tree_combine(a.partials, plan.split, y, ldy, (int)y_dtype, m, N, s) : pe;
+    });
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
 
@@ -604,7 +630,7 @@ static size_t mxfp8_scales_room(int M, int N, int K) { return mx_retiles(M) && K
 size_t tbik_gemm_mxfp8_workspace_bytes(int M, int N, int K, int leaf, int k_first) {
     int sl, ns;
     if (check_tree(M, N, K, leaf, k_first, 1, &sl, &ns) != TBIK_OK) return 0;
-    return mx_planes_bytes(M, N, std::max(internal_split(M, N, K, ns), tile_plan(OPERANDS_MXFP8, M, N, K, ns, 0, SIZE_MAX).split)) + mxfp8_scales_room(M, N, K);
+    return round_256(plan_planes_bytes(OPERANDS_MXFP8, M, N, K, ns)) + mxfp8_scales_room(M, N, K);
 }
 
 int tbik_gemm_mxfp8(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, const void *Wt, int64_t ldwt,
@@ -620,31 +646,29 @@ int tbik_gemm_mxfp8(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
     if (ldy < N) return TBIK_ERR_SHAPE;
     if (!aligned(Y, y_dtype == TBIK_F32 ? 4 : 2)) return TBIK_ERR_ALIGN;
     const size_t scales_room = mxfp8_scales_room(M, N, K);
-    const size_t need = mx_planes_bytes(M, N, internal_split(M, N, K, ns)) + scales_room;      // more room may allow a better split
+    const size_t need = round_256(split_planes_bytes(M, N, internal_split(M, N, K, ns))) + scales_room;      // more room may allow a better split
     if (need > 0 && (!workspace || workspace_bytes < need)) return TBIK_ERR_WORKSPACE;
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)hip_stream;
-    GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)Wt, ldwt, nullptr, Y, ldy, (int)y_dtype, M, N, K, sl, ns, 1, (int)x_dtype, 0};
-    const Mxfp4Scales sc{(const uint8_t *)Xs, ldxs, (const uint8_t *)Ws, ldws};
-    const size_t room = workspace_bytes >= scales_room + 255 ? workspace_bytes - scales_room - 255 : 0;      // (planes are rounded up to 256 bytes)
-    const TilePlan plan = tile_plan(OPERANDS_MXFP8, M, N, K, ns, 0, workspace ? room : 0);
-    const int split = plan.split, rows = plan.rows;
-    GemmArgs probe = a;
-    probe.P = split;
-    const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_mxfp8_tiled_supports(probe, sc);
-    hipError_t e;
-    void *retiled = (tiled && mx_retiles(M)) ? static_cast<char *>(workspace) + mx_planes_bytes(M, N, split) : nullptr;
-    if (!tiled) {
-        e = launch_gemm_mxfp8_reference(a, sc, s);
-    } else if (split == 1) {
-        e = launch_gemm_mxfp8_tiled(a, sc, rows, retiled, s);
-    } else {
+    const size_t room = workspace && workspace_bytes > scales_room ? (workspace_bytes - scales_room) & ~(size_t)255 : 0;      // planes are rounded up to 256 bytes
+    hipError_t e = in_pieces(OPERANDS_MXFP8, M, N, K, ns, room, [&](int m0, int m) {
+        const TilePlan plan = tile_plan(OPERANDS_MXFP8, m, N, K, ns, 0, room);
+        void *y = static_cast<char *>(Y) + (int64_t)m0 * ldy * (y_dtype == TBIK_F32 ? 4 : 2);
+        GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
+                   (int)y_dtype, m, N, K, sl, ns, 1, (int)x_dtype, 0};
+        const Mxfp4Scales sc{static_cast<const uint8_t *>(Xs) + (int64_t)m0 * ldxs, ldxs, (const uint8_t *)Ws, ldws};
+        GemmArgs probe = a;
+        probe.P = plan.split;
+        if (g_forced_variant.load() == VARIANT_REFERENCE || !gemm_mxfp8_tiled_supports(probe, sc)) return launch_gemm_mxfp8_reference(a, sc, s);
+        // (the second piece's re-tiled scales may take the first one's place: the stream has passed the first by then)
+        void *retiled = mx_retiles(m) ? static_cast<char *>(workspace) + round_256(split_planes_bytes(m, N, plan.split)) : nullptr;
+        if (plan.split == 1) return launch_gemm_mxfp8_tiled(a, sc, plan.rows, retiled, s);
         a.partials = reinterpret_cast<float *>(workspace);
         a.Y = nullptr;
-        a.P = split;
-        e = launch_gemm_mxfp8_tiled(a, sc, rows, retiled, s);
-        if (e == hipSuccess) e = launch_tree_combine(a.partials, split, Y, ldy, (int)y_dtype, M, N, s);
-    }
+        a.P = plan.split;
+        hipError_t pe = launch_gemm_mxfp8_tiled(a, sc, plan.rows, retiled, s);
+        return pe == hipSuccess ? launch_tree_combine(a.partials, plan.split, y, ldy, (int)y_dtype, m, N, s) : pe;
+    });
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
 
@@ -704,7 +728,7 @@ static size_t mxfp6_scales_room(int M, int N, int K) { return mx_retiles(M) && K
 size_t tbik_gemm_mxfp6_workspace_bytes(int M, int N, int K, int leaf, int k_first) {
     int sl, ns;
     if (check_tree(M, N, K, leaf, k_first, 1, &sl, &ns) != TBIK_OK) return 0;
-    return mx_planes_bytes(M, N, std::max(mxfp6_split(M, N, ns), tile_plan(OPERANDS_MXFP6, M, N, K, ns, 0, SIZE_MAX).split)) + mxfp6_scales_room(M, N, K);
+    return round_256(plan_planes_bytes(OPERANDS_MXFP6, M, N, K, ns)) + mxfp6_scales_room(M, N, K);
 }
 
 int tbik_gemm_mxfp6(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, const void *Wt, int64_t ldwt,
@@ -720,30 +744,29 @@ int tbik_gemm_mxfp6(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
     if (ldy < N) return TBIK_ERR_SHAPE;
     if (!aligned(Y, y_dtype == TBIK_F32 ? 4 : 2)) return TBIK_ERR_ALIGN;
     const size_t scales_room = mxfp6_scales_room(M, N, K);
-    const size_t need = mx_planes_bytes(M, N, mxfp6_split(M, N, ns)) + scales_room;      // more room may allow a better split
+    const size_t need = round_256(split_planes_bytes(M, N, mxfp6_split(M, N, ns))) + scales_room;      // more room may allow a better split
     if (need > 0 && (!workspace || workspace_bytes < need)) return TBIK_ERR_WORKSPACE;
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)hip_stream;
-    GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)Wt, ldwt, nullptr, Y, ldy, (int)y_dtype, M, N, K, sl, ns, 1, (int)x_dtype, 0};
-    const Mxfp4Scales sc{(const uint8_t *)Xs, ldxs, (const uint8_t *)Ws, ldws};
-    const size_t room = workspace_bytes >= scales_room + 255 ? workspace_bytes - scales_room - 255 : 0;      // (planes are rounded up to 256 bytes)
-    const int split = tile_plan(OPERANDS_MXFP6, M, N, K, ns, 0, workspace ? room : 0).split;
-    GemmArgs probe = a;
-    probe.P = split;
-    const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_mxfp6_tiled_supports(probe, sc);
-    void *retiled = (tiled && mx_retiles(M)) ? static_cast<char *>(workspace) + mx_planes_bytes(M, N, split) : nullptr;
-    hipError_t e;
-    if (!tiled) {
-        e = launch_gemm_mxfp6_reference(a, sc, s);
-    } else if (split == 1) {
-        e = launch_gemm_mxfp6_tiled(a, sc, retiled, s);
-    } else {
+    const size_t room = workspace && workspace_bytes > scales_room ? (workspace_bytes - scales_room) & ~(size_t)255 : 0;      // planes are rounded up to 256 bytes
+    hipError_t e = in_pieces(OPERANDS_MXFP6, M, N, K, ns, room, [&](int m0, int m) {
+        const TilePlan plan = tile_plan(OPERANDS_MXFP6, m, N, K, ns, 0, room);
+        void *y = static_cast<char *>(Y) + (int64_t)m0 * ldy * (y_dtype == TBIK_F32 ? 4 : 2);
+        GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
+                   (int)y_dtype, m, N, K, sl, ns, 1, (int)x_dtype, 0};
+        const Mxfp4Scales sc{static_cast<const uint8_t *>(Xs) + (int64_t)m0 * ldxs, ldxs, (const uint8_t *)Ws, ldws};
+        GemmArgs probe = a;
+        probe.P = plan.split;
+        if (g_forced_variant.load() == VARIANT_REFERENCE || !gemm_mxfp6_tiled_supports(probe, sc)) return launch_gemm_mxfp6_reference(a, sc, s);
+        // (the second piece's re-tiled scales may take the first one's place: the stream has passed the first by then)
+        void *retiled = mx_retiles(m) ? static_cast<char *>(workspace) + round_256(split_planes_bytes(m, N, plan.split)) : nullptr;
+        if (plan.split == 1) return launch_gemm_mxfp6_tiled(a, sc, retiled, s);
         a.partials = reinterpret_cast<float *>(workspace);
         a.Y = nullptr;
-        a.P = split;
-        e = launch_gemm_mxfp6_tiled(a, sc, retiled, s);
-        if (e == hipSuccess) e = launch_tree_combine(a.partials, split, Y, ldy, (int)y_dtype, M, N, s);
-    }
+        a.P = plan.split;
+        hipError_t pe = launch_gemm_mxfp6_tiled(a, sc, retiled, s);
+        return pe == hipSuccess ? launch_tree_combine(a.partials, plan.split, y, ldy, (int)y_dtype, m, N, s) : pe;
+    });
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
 

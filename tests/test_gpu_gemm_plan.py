@@ -58,3 +58,26 @@ def test_low_bit(kind, M):
     assert torch.equal(call(*dev, LEAF, 1, out_dtype=torch.float32, workspace=ws).view(torch.int32), want)
     for P in (2, 8):
         assert torch.equal(tb.tbik_tree_combine(parts(*dev, LEAF, 1, P), out_dtype=torch.float32).view(torch.int32), want), P
+
+
+@pytest.mark.parametrize("M", [4097, 4100, 4224, 4300])
+def test_last_rows_as_a_call_of_their_own(M):
+    """A batch a little above full rounds of 128-row tiles is computed in two pieces: rows equal those of other batch sizes."""
+    Kp, Np = 2048, 1024                                           # 8 column tiles: 32 row tiles fill a round
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(M)
+    X = torch.randn((M, Kp), generator=g, device="cuda:0").to(torch.bfloat16)
+    W = (torch.randn((Kp, Np), generator=g, device="cuda:0") * 0.02).to(torch.bfloat16)
+    want = tb.tbik_gemm(X[-700:], W, LEAF, 1)
+    head = tb.tbik_gemm(X[:700], W, LEAF, 1)
+    got = tb.tbik_gemm(X, W, LEAF, 1)
+    assert torch.equal(got[-700:].view(torch.int16), want.view(torch.int16)) and torch.equal(got[:700].view(torch.int16), head.view(torch.int16))
+    whole = tb.tbik_gemm_reference(X, W, LEAF, 1, out_dtype=torch.bfloat16)[1]
+    assert torch.equal(got.view(torch.int16), whole.view(torch.int16))
+    for kind in ("mxfp8", "mxfp4", "mxfp6"):
+        ops = [torch.from_numpy(np.ascontiguousarray(t)).to("cuda:0") for t in getattr(syn, "gemm_random_" + kind)(M, 300, Kp, Np)]
+        rep = -(-M // 300)
+        dev = [ops[0].repeat(rep, 1)[:M].contiguous(), ops[1].repeat(rep, 1)[:M].contiguous(), ops[2], ops[3]]
+        y = getattr(tb, "tbik_gemm_" + kind)(*dev, LEAF, 1)
+        one = getattr(tb, "tbik_gemm_" + kind)(*ops, LEAF, 1)
+        assert torch.equal(y.view(torch.int16), one.repeat(rep, 1)[:M].view(torch.int16)), kind
