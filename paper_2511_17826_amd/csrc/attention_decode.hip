@@ -328,6 +328,7 @@ void attention_decode_kernel(const DecodeParams p) {
     float m_acc = -INFINITY, l_acc = 0.0f;
     float m = -INFINITY, l = 0.0f, alpha[DEC_ROUND];
 
+    const att_u32x4 NEGATIVE_ZEROS = {0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};      // +0 x -0 = -0, and x + -0 is x for either zero as well
     // Tiles q and q + 1 of round r: V through LDS, then o = o alpha + V^T P^T tile after tile.
     auto two_tiles = [&](auto q_tag, int r) __attribute__((always_inline)) {
         constexpr int Q0 = decltype(q_tag)::value;
@@ -335,6 +336,12 @@ void attention_decode_kernel(const DecodeParams p) {
         for (int q = Q0; q < Q0 + 2; ++q) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) *reinterpret_cast<att_u32x4 *>(v_wr + (q & 1) * DEC_V_TILE + i * 1024) = vr[q][i];
+            // A tile past the end (the last round may have some) leaves o as it is: its weights are 0, its values must be finite.
+            // (A branch with nothing but stores: choosing in registers cost 1.5 of attention_decode's 28 us.)
+            if (t_begin + r * DEC_ROUND + q >= t_end) {           // uniform
+#pragma unroll
+                for (int i = 0; i < 4; ++i) *reinterpret_cast<att_u32x4 *>(v_wr + (q & 1) * DEC_V_TILE + i * 1024) = NEGATIVE_ZEROS;
+            }
             load_v(vr[q], t_begin + (r + 1) * DEC_ROUND + q);
         }
 #pragma unroll

@@ -13,12 +13,15 @@ from test_gpu_attention import check_against_oracle, i32
 pytestmark = pytest.mark.gpu
 
 
-def both(Hq, Hkv, lens_q, lens_k, causal=True, dtype=torch.bfloat16, seed=0, poison=float("nan")):
+def both(Hq, Hkv, lens_q, lens_k, causal=True, dtype=torch.bfloat16, seed=0, poison=float("nan"), edit=None):
     g = torch.Generator(device="cuda:0")
     g.manual_seed(seed)
     rnd = lambda n, h: torch.randn((n, h, 128), generator=g, device="cuda:0").to(dtype)
     Q, K, V = rnd(sum(lens_q), Hq), rnd(max(sum(lens_k), 1), Hkv), rnd(max(sum(lens_k), 1), Hkv)
     cq, ck = i32(np.cumsum([0] + list(lens_q))), i32(np.cumsum([0] + list(lens_k)))
+    if edit:
+        ends = np.cumsum(lens_k)
+        edit(K, V, ends - np.array(lens_k), ends)
     call = tb.tbik_attention if dtype == torch.bfloat16 else tb.tbik_attention_f16
     need = max(256, tb.attention_workspace_bytes(len(lens_q), max(lens_q), max(lens_k), Hq, Hkv))
     out = []
@@ -65,3 +68,31 @@ def test_short_workspace_walks_and_oracle_parity():
     Q, K, V = gu.dev_bf16(c["Q"]), gu.dev_bf16(c["K"]), gu.dev_bf16(c["V"])
     O = tb.tbik_attention(Q, K, V, i32(c["cu_q"]), i32(c["cu_k"]), 4, c["scale"], True)
     check_against_oracle(gu.host_bf16_bits(O), c, True, min_equal=0.98)
+
+
+def same_values(a, b, dtype):
+    """Same bits wherever a value is not NaN, NaN in the same places (the payload of a NaN is no part of the result)."""
+    a, b = a.view(dtype), b.view(dtype)
+    nan = torch.isnan(a)
+    return torch.equal(nan, torch.isnan(b)) and torch.equal(a.view(torch.int16)[~nan], b.view(torch.int16)[~nan])
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("value", [float("inf"), -float("inf"), float("nan")])
+@pytest.mark.parametrize("where", ["last", "first", "last of K"])
+def test_values_that_are_not_finite(dtype, value, where):
+    """Tiles past the end of a sequence contribute nothing whatever its last key and value are: key counts that end on a tile
+    edge inside a round of four tiles (64, 128, 192), on a round (256), inside a tile (65), behind a split (4160)."""
+    lens = [64, 128, 192, 256, 65, 320, 4160]
+
+    def poison(K, V, starts, ends):
+        for i, (s, e) in enumerate(zip(starts, ends)):
+            if where == "last of K":
+                K[e - 1, i % 2, 5] = value
+            else:
+                V[e - 1 if where == "last" else s, i % 2, 3::7] = value
+    for lens_q in ([1] * len(lens), [3] * len(lens)):
+        a, b = both(8, 2, lens_q, lens, dtype=dtype, seed=3, edit=poison)
+        assert same_values(a, b, dtype)
+        if where == "last" and value == float("inf") and lens_q[0] == 1:          # inf and not 0 x inf where no tile is ragged
+            assert torch.isinf(a.view(dtype)[:4]).any(dim=2).any(dim=1).all() and not torch.isnan(a.view(dtype)[:4]).any()
