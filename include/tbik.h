@@ -259,7 +259,8 @@ int tbik_row_reduce_static(const void *x, tbik_dtype x_dtype, void *out, tbik_ro
  *   cu_seqlens_q, cu_seqlens_k   DEVICE, int32 [batch + 1], non-decreasing prefix sums of the sequences' query and key
  *          counts; values are clamped to [0, total_q] / [0, total_k] inside the kernel
  *   max_seqlen_q   at least the largest Lq: batch x max_seqlen_q bounds the tokens the launch and the workspace are sized
- *          for (with a smaller value the last queries of the call may be left unwritten); never the bits;
+ *          for (in a call of more tokens than that the last queries may be left unwritten); never the bits.  A sequence
+ *          with more queries than max_seqlen_q in a call of fewer tokens is computed whole, if more slowly;
  *   max_seqlen_k   at least the largest Lk (keys of a sequence past it are left out); decides the workspace and how the
  *          call is cut into workgroups, never the bits; values above total_k are taken as total_k
  *          total_q, total_k: tokens in Q/O and in K/V

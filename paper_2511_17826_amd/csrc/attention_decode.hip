@@ -119,50 +119,40 @@ __device__ __forceinline__ void store_channels(uint16_t *optr, float l, const f3
     }
 }
 
+// A workgroup's part of the work: key/value head, rows 16 cg .. + 15 of it, and the split (n_splits > 1) of sequence seq.
+struct DecodeItem {
+    int hk, cg, seq, split, n_splits;
+    int q0, Lq, k0, Lk;                                           // the sequence's queries and keys in the packed tensors
+    int first_block, my_blocks;                                   // channel blocks of the values
+};
+
+// Queries q_base .. q_base + rows - 1 of an item.
 template <bool CAUSAL, bool F16>
-__global__ __launch_bounds__(DEC_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3)))
-void attention_decode_kernel(const DecodeParams p) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+__device__ __forceinline__ void decode_queries(const DecodeParams &p, const DecodeItem &it, int q_base, int tid, unsigned char *smem) {
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g4 = lane >> 4;
-
-    // Workgroups of one item -- the same keys, different channels of the values -- follow each other on one XCD.
-    int id = (int)(blockIdx.x >> 3) / p.chan_groups * 8 + (blockIdx.x & 7);
-    if (id >= p.items) return;
-    const int my_blocks = ATT_D / 32 / p.chan_groups, first_block = (int)(blockIdx.x >> 3) % p.chan_groups * my_blocks;
-    const int hk = id % p.heads_kv;
-    id /= p.heads_kv;
-    const int cg = id % p.col_groups;
-    id /= p.col_groups;
-    const int split = id % p.n_splits, seq = id / p.n_splits;
-
-    // Sequence bounds, clamped so that no value of the offset arrays can lead outside the tensors.
-    const int q0 = clampi(p.cu_q[seq], 0, p.total_q), q1 = clampi(p.cu_q[seq + 1], q0, p.total_q);
-    const int k0 = clampi(p.cu_k[seq], 0, p.total_k), k1 = clampi(p.cu_k[seq + 1], k0, p.total_k);
-    const int Lq = q1 - q0, Lk = k1 - k0;
-    if (Lq <= 0) return;                                          // uniform
+    const int q0 = it.q0, k0 = it.k0, Lq = it.Lq, Lk = it.Lk, hk = it.hk;
     const int shift = Lk - Lq;                                    // the queries are the last Lq positions
-    const int q_last = min(Lq, p.rows) - 1;
+    const int q_last = min(Lq, q_base + p.rows) - 1;
     const int lim_block = CAUSAL ? min(Lk - 1, q_last + shift) : Lk - 1;
     const int n_tiles = lim_block >= 0 ? min(p.max_tiles, lim_block / ATT_KV + 1) : 0;   // keys past max_seqlen_k are left out
 
-    // This lane's row: column col is query col % rows of head col / rows of the group; columns past those repeat one.
-    const int col = cg * DEC_COLS + l16;
-    const int head = hk * p.group + min(col / p.rows, p.group - 1), qrow = col % p.rows;
+    // This lane's row: column col is query q_base + col % rows of head col / rows of the group; columns past those repeat one.
+    const int col = it.cg * DEC_COLS + l16;
+    const int head = hk * p.group + min(col / p.rows, p.group - 1), qrow = q_base + col % p.rows;
     const bool stored = col < p.group * p.rows && qrow < Lq;
     const int qpos = min(qrow, Lq - 1);
     const int lim = CAUSAL ? min(Lk - 1, qpos + shift) : Lk - 1;  // last visible key; < 0: none
-    const int full = CAUSAL ? min(Lk - 1, shift) : Lk - 1;        // last key that every row sees
+    const int full = CAUSAL ? min(Lk - 1, q_base + shift) : Lk - 1;        // last key that every row sees
 
-    const int t_begin = p.n_splits > 1 ? split * ATT_SPLIT : 0;
-    const int t_end = p.n_splits > 1 ? min(n_tiles, t_begin + ATT_SPLIT) : n_tiles;
-    f32x4 *const state = p.states + (((size_t)(seq * p.col_groups + cg) * p.heads_kv + hk) * p.n_splits + split) * DEC_STATE_CHUNKS + lane;
-    const int db = wave < DEC_SCORE_WAVES ? 0 : first_block + wave - DEC_SCORE_WAVES;      // a product wavefront's channel block
-    if (wave >= DEC_SCORE_WAVES + my_blocks) return;
+    const int t_begin = it.n_splits > 1 ? it.split * ATT_SPLIT : 0;
+    const int t_end = it.n_splits > 1 ? min(n_tiles, t_begin + ATT_SPLIT) : n_tiles;
+    f32x4 *const state = p.states + (((size_t)(it.seq * p.col_groups + it.cg) * p.heads_kv + hk) * p.n_splits + it.split) * DEC_STATE_CHUNKS + lane;
+    const int db = wave < DEC_SCORE_WAVES ? 0 : it.first_block + wave - DEC_SCORE_WAVES;   // a product wavefront's channel block
     if (t_begin >= t_end) {                                       // uniform: no row sees a key (of this split)
         if (wave < DEC_SCORE_WAVES) return;
-        if (p.n_splits > 1) {
+        if (it.n_splits > 1) {
             if (db == 0) state[0] = f32x4{-INFINITY, 0.0f, 0.0f, 0.0f};         // an empty state: only m and l are looked at
         } else if (stored) {
             const f32x4 zero[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
@@ -399,7 +389,7 @@ void attention_decode_kernel(const DecodeParams p) {
     workgroup_barrier();
     finish_round(rounds - 1);
 
-    if (p.n_splits > 1) {                                         // the state as it is; attention_decode_merge_kernel folds and divides
+    if (it.n_splits > 1) {                                        // the state as it is; attention_decode_merge_kernel folds and divides
         if (db == 0) state[0] = f32x4{m, l, 0.0f, 0.0f};
         state[(1 + 2 * db) * 64] = o[0];
         state[(2 + 2 * db) * 64] = o[1];
@@ -407,6 +397,46 @@ void attention_decode_kernel(const DecodeParams p) {
     }
     fold_states(m_acc, l_acc, o_acc, m, l, o);                    // one split only: the accumulated state is empty
     if (stored) store_channels<F16>(p.O + (int64_t)(q0 + qrow) * p.o_stride + (int64_t)head * ATT_D + db * 32 + 4 * g4, l_acc, o_acc);
+}
+
+template <bool CAUSAL, bool F16>
+__global__ __launch_bounds__(DEC_THREADS) __attribute__((amdgpu_waves_per_eu(3, 3)))
+void attention_decode_kernel(const DecodeParams p) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+
+    // Workgroups of one item -- the same keys, different channels of the values -- follow each other on one XCD.
+    int id = (int)(blockIdx.x >> 3) / p.chan_groups * 8 + (blockIdx.x & 7);
+    if (id >= p.items) return;
+    DecodeItem it;
+    it.my_blocks = ATT_D / 32 / p.chan_groups;
+    it.first_block = (int)(blockIdx.x >> 3) % p.chan_groups * it.my_blocks;
+    if (wave >= DEC_SCORE_WAVES + it.my_blocks) return;
+    it.hk = id % p.heads_kv;
+    id /= p.heads_kv;
+    it.cg = id % p.col_groups;
+    id /= p.col_groups;
+    it.n_splits = p.n_splits;
+    it.split = id % p.n_splits;
+    it.seq = id / p.n_splits;
+
+    // Sequence bounds, clamped so that no value of the offset arrays can lead outside the tensors.
+    it.q0 = clampi(p.cu_q[it.seq], 0, p.total_q);
+    it.Lq = clampi(p.cu_q[it.seq + 1], it.q0, p.total_q) - it.q0;
+    it.k0 = clampi(p.cu_k[it.seq], 0, p.total_k);
+    it.Lk = clampi(p.cu_k[it.seq + 1], it.k0, p.total_k) - it.k0;
+    if (it.Lq <= 0) return;                                       // uniform
+    decode_queries<CAUSAL, F16>(p, it, 0, threadIdx.x, smem);
+    // A sequence with more queries than max_seqlen_q said (the host does not know): one workgroup walks the splits for the
+    // rest of them.  (A second copy of the code: one copy in a loop spills 41 registers.)
+    if (it.split != 0) return;
+    it.n_splits = 1;
+    for (int q_base = p.rows; q_base < it.Lq; q_base += p.rows) {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid), "+s"(it.Lk), "+s"(it.k0), "+s"(it.hk));     // nothing is computed before the loop and kept in registers
+        workgroup_barrier();                                      // the LDS of the queries before these has been read
+        decode_queries<CAUSAL, F16>(p, it, q_base, tid, smem);
+    }
 }
 
 // Folds the states of a (sequence, column group, key/value head)'s splits in ascending order and writes the output;

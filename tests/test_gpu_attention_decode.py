@@ -13,7 +13,7 @@ from test_gpu_attention import check_against_oracle, i32
 pytestmark = pytest.mark.gpu
 
 
-def both(Hq, Hkv, lens_q, lens_k, causal=True, dtype=torch.bfloat16, seed=0, poison=float("nan"), edit=None):
+def both(Hq, Hkv, lens_q, lens_k, causal=True, dtype=torch.bfloat16, seed=0, poison=float("nan"), edit=None, said_q=None):
     g = torch.Generator(device="cuda:0")
     g.manual_seed(seed)
     rnd = lambda n, h: torch.randn((n, h, 128), generator=g, device="cuda:0").to(dtype)
@@ -29,7 +29,7 @@ def both(Hq, Hkv, lens_q, lens_k, causal=True, dtype=torch.bfloat16, seed=0, poi
         tb.tbik_set_attention_variant(variant)
         ws = torch.full((need // 4,), poison, dtype=torch.float32, device="cuda:0")
         O = torch.full_like(Q, 7.0)
-        call(Q, K, V, cq, ck, max(lens_q), 128 ** -0.5, causal, out=O, max_seqlen_k=max(lens_k), workspace=ws)
+        call(Q, K, V, cq, ck, said_q if said_q and variant == 0 else max(lens_q), 128 ** -0.5, causal, out=O, max_seqlen_k=max(lens_k), workspace=ws)
         torch.cuda.synchronize()
         out.append(O.view(torch.int16).cpu())
     tb.tbik_set_attention_variant(0)
@@ -96,3 +96,15 @@ def test_values_that_are_not_finite(dtype, value, where):
         assert same_values(a, b, dtype)
         if where == "last" and value == float("inf") and lens_q[0] == 1:          # inf and not 0 x inf where no tile is ragged
             assert torch.isinf(a.view(dtype)[:4]).any(dim=2).any(dim=1).all() and not torch.isnan(a.view(dtype)[:4]).any()
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("Hq,Hkv,said_q,lens_q", [(8, 2, 1, [3, 0, 1, 0, 0, 2]), (8, 2, 2, [3, 1]), (8, 2, 8, [17, 1, 0, 9]), (4, 4, 3, [8, 1, 0]),
+                                                  (32, 1, 1, [2, 0, 1]), (8, 2, 5, [0, 21, 1, 1, 2, 0])])
+def test_a_sequence_with_more_queries_than_max_seqlen_q(Hq, Hkv, said_q, lens_q, causal):
+    """batch x max_seqlen_q covers the call's tokens, so every query is computed, whichever sequence it belongs to; keys of one
+    tile, of several rounds and of two splits (whose states the first max_seqlen_q queries pass through the workspace)."""
+    assert said_q * len(lens_q) >= sum(lens_q) and max(lens_q) > said_q
+    for lens_k in ([4500] * len(lens_q), [70 + 200 * i for i in range(len(lens_q))], [5] * len(lens_q)):
+        a, b = both(Hq, Hkv, lens_q, lens_k, causal, seed=said_q, said_q=said_q)
+        assert torch.equal(a, b)
