@@ -186,6 +186,7 @@ TilePlan tile_plan(Operands kind, int M, int N, int K, int ns, int only_split, s
 // a result do not depend on each other, so neither do their bits.)
 constexpr double kPieceUs = 2.0;        // what a launch behind another costs
 int last_rows(Operands kind, int M, int N, int K, int ns, size_t room) {
+    if (M <= 0 || N <= 0) return 0;
     const int cols = (N + 127) / 128, per_round = 256 / cols;                    // row tiles of 128 in a round
     if (g_forced_variant.load() != VARIANT_AUTO || per_round < 1 || ns > 16 || M <= per_round * 128) return 0;
     const int rest = M % (per_round * 128), full = M - rest;

@@ -48,6 +48,15 @@ def test_workspace_sizes_are_pure_and_zero_for_illegal_shapes(L):
     assert L.tbik_row_reduce_workspace_bytes(4, 100, 7) == 0
 
 
+@pytest.mark.parametrize("fmt", ["", "_fp8", "_mxfp4", "_mxfp8", "_mxfp6", "_swiglu"])
+def test_workspace_sizes_of_empty_problems(L, fmt):
+    """No rows or no columns: a size and no division by zero (the callers size the workspace before the call looks at M and N)."""
+    size = getattr(L, "tbik_gemm%s_workspace_bytes" % fmt)
+    for k, leaf, g in ((4096, 256, 1), (25600, 256, 25)):
+        assert size(0, 256, k, leaf, g) == 0 and size(5, 0, k, leaf, g) == 0 and size(0, 0, k, leaf, g) == 0
+        assert size(5000, 0, k, leaf, g) <= 5120 * k // 32        # one byte per block of 32 of X at most: the microscaling formats' re-tiled scales
+
+
 GOOD = 0x1000  # a fake, aligned, non-null "device pointer": validation must fail before it is ever used
 
 
