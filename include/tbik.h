@@ -264,12 +264,14 @@ int tbik_row_reduce_static(const void *x, tbik_dtype x_dtype, void *out, tbik_ro
  *   max_seqlen_k   at least the largest Lk (keys of a sequence past it are left out); decides the workspace and how the
  *          call is cut into workgroups, never the bits; values above total_k are taken as total_k
  *          total_q, total_k: tokens in Q/O and in K/V
- *   workspace   at least tbik_attention_workspace_bytes(batch, max_seqlen_q, max_seqlen_k, heads_q, heads_kv) bytes,
- *          256-byte aligned; that is 0 (and the pointer may be NULL) when max_seqlen_k <= 4096, else 68 KiB per
- *          128 rows of (query, head) of batch x max_seqlen_q tokens and -- below 512 such blocks -- per split of
- *          max_seqlen_k, but never more than 4608 x 68 KiB = 306 MiB (for the usual head counts): a call with more
- *          blocks than that is launched in pieces that take turns at the area.  Contents on entry do not matter; calls
- *          that share a workspace must not overlap in time
+ *   workspace   tbik_attention_workspace_bytes(batch, max_seqlen_q, max_seqlen_k, heads_q, heads_kv) bytes, 256-byte
+ *          aligned; that is 0 (and the pointer may be NULL) when max_seqlen_k <= 4096.  Less is refused below 68 KiB per
+ *          128 rows of (query, head) of batch x max_seqlen_q tokens and -- below 512 such blocks, if all states then fit
+ *          4608 x 68 KiB -- per split of max_seqlen_k; calls of few queries per sequence (max_seqlen_q x query heads per
+ *          key/value head <= 32) can use more, up to the same bound, for the states of splits computed side by side, and
+ *          walk the splits in fewer workgroups with less.  Never more than 4608 x 68 KiB = 306 MiB (for the usual head
+ *          counts): a call with more blocks than that is launched in pieces that take turns at the area.  Contents on
+ *          entry do not matter; calls that share a workspace must not overlap in time
  *   head_dim 128 (other values: TBIK_ERR_UNSUPPORTED); heads_q a multiple of heads_kv; strides in elements, multiples
  *   of 8, at least heads * head_dim, below 2^24; pointers 16-byte aligned.  O must not overlap Q, K or V.
  * Errors: NULL, SHAPE, UNSUPPORTED, ALIGN, WORKSPACE, HIP.

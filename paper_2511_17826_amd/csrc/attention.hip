@@ -909,11 +909,16 @@ static AttnPlan plan_attention(int batch, int64_t total_q, int max_seqlen_k, int
     return pl;
 }
 
-// From the arguments a caller has before the call: batch x max_seqlen_q bounds total_q.
-size_t attention_workspace(int batch, int max_seqlen_q, int max_seqlen_k, int heads_q, int heads_kv) {
+// From the arguments a caller has before the call: batch x max_seqlen_q bounds total_q.  What attention_kernel needs is what
+// a call insists on; where the kernel for few queries can use more, the size that callers are told includes it.
+size_t attention_workspace_required(int batch, int max_seqlen_q, int max_seqlen_k, int heads_q, int heads_kv) {
     if (batch <= 0 || max_seqlen_q <= 0 || heads_q <= 0 || heads_kv <= 0 || heads_q % heads_kv) return 0;
     // the variant switch may only move a call to the other kernel where no workspace is involved, so it does not matter here
-    const size_t need = plan_attention(batch, (int64_t)batch * max_seqlen_q, max_seqlen_k, heads_q, heads_kv, 0, SIZE_MAX).state_bytes;
+    return plan_attention(batch, (int64_t)batch * max_seqlen_q, max_seqlen_k, heads_q, heads_kv, 0, SIZE_MAX).state_bytes;
+}
+size_t attention_workspace(int batch, int max_seqlen_q, int max_seqlen_k, int heads_q, int heads_kv) {
+    if (batch <= 0 || max_seqlen_q <= 0 || heads_q <= 0 || heads_kv <= 0 || heads_q % heads_kv) return 0;
+    const size_t need = attention_workspace_required(batch, max_seqlen_q, max_seqlen_k, heads_q, heads_kv);
     return attention_decode_supports(max_seqlen_q, heads_q, heads_kv)
                ? std::max(need, attention_decode_workspace(batch, max_seqlen_q, max_seqlen_k, heads_q, heads_kv)) : need;
 }

@@ -522,7 +522,9 @@ static hipError_t launch_decode_of(const AttnArgs &a, const DecodeParams &p, hip
 
 hipError_t launch_attention_decode(const AttnArgs &a, hipStream_t s) {
     DecodePlan pl = plan_decode(a.batch, a.max_seqlen_q, a.max_seqlen_k, a.heads_q, a.heads_kv);
-    if (pl.state_bytes > (a.workspace ? a.workspace_bytes : 0)) pl.n_splits = 1;      // walking needs no workspace: same bits
+    // A workspace of the size that attention_kernel asks for may not hold the states; walking needs none and has the same bits.
+    // (Where that kernel would have the splits side by side its 68 KiB per state and split are room enough for these 9 KiB.)
+    if (pl.state_bytes > (a.workspace ? a.workspace_bytes : 0)) pl.n_splits = 1;
     if ((int64_t)a.batch * a.heads_kv * pl.col_groups * pl.n_splits > 0x7ffffff0) return hipErrorInvalidValue;
     DecodeParams p;
     p.Q = a.Q; p.K = a.K; p.V = a.V; p.O = a.O;

@@ -938,7 +938,7 @@ static int attention(int dtype, const void *Q, const void *K, const void *V, voi
         !aligned(cu_seqlens_k, 4) || q_stride % 8 || k_stride % 8 || v_stride % 8 || o_stride % 8)
         return TBIK_ERR_ALIGN;
     if (max_seqlen_k > total_k) max_seqlen_k = total_k;          // no sequence has more keys than the call
-    const size_t need = attention_workspace(batch, max_seqlen_q, max_seqlen_k, heads_q, heads_kv);
+    const size_t need = attention_workspace_required(batch, max_seqlen_q, max_seqlen_k, heads_q, heads_kv);     // more room may allow splits side by side
     if (need > 0 && (!workspace || workspace_bytes < need)) return TBIK_ERR_WORKSPACE;
     if (need > 0 && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     AttnArgs a{(const uint16_t *)Q, (const uint16_t *)K, (const uint16_t *)V, (uint16_t *)O, dtype, cu_seqlens_q, cu_seqlens_k,

@@ -13,7 +13,7 @@ from test_gpu_attention import check_against_oracle, i32
 pytestmark = pytest.mark.gpu
 
 
-def both(Hq, Hkv, lens_q, lens_k, causal=True, dtype=torch.bfloat16, seed=0, poison=float("nan"), edit=None, said_q=None):
+def both(Hq, Hkv, lens_q, lens_k, causal=True, dtype=torch.bfloat16, seed=0, poison=float("nan"), edit=None, said_q=None, ws_bytes=0):
     g = torch.Generator(device="cuda:0")
     g.manual_seed(seed)
     rnd = lambda n, h: torch.randn((n, h, 128), generator=g, device="cuda:0").to(dtype)
@@ -23,7 +23,7 @@ def both(Hq, Hkv, lens_q, lens_k, causal=True, dtype=torch.bfloat16, seed=0, poi
         ends = np.cumsum(lens_k)
         edit(K, V, ends - np.array(lens_k), ends)
     call = tb.tbik_attention if dtype == torch.bfloat16 else tb.tbik_attention_f16
-    need = max(256, tb.attention_workspace_bytes(len(lens_q), max(lens_q), max(lens_k), Hq, Hkv))
+    need = ws_bytes or max(256, tb.attention_workspace_bytes(len(lens_q), max(lens_q), max(lens_k), Hq, Hkv))
     out = []
     for variant in (1, 0):
         tb.tbik_set_attention_variant(variant)
@@ -63,7 +63,21 @@ def test_splits_in_parallel_walked_and_channel_groups_same_bits(dtype, batch, Hk
     assert torch.equal(a, b)
 
 
-def test_short_workspace_walks_and_oracle_parity():
+@pytest.mark.parametrize("causal", [True, False])
+def test_short_workspace_walks(causal):
+    """A workspace of the size that the kernel for every call shape asks for (one state of 68 KiB per item where it walks the
+    splits) does not hold the states of 40 sequences x 8 heads x 15 splits: the splits are walked, same bits; less is refused."""
+    lens_k = [61440, 8193, 4096] + [70 + i for i in range(37)]
+    lens_q = [1] * 40
+    required = (40 * 1 // 32 + 40) * 8 * 4 * (4 + 64) * 256
+    assert required < tb.attention_workspace_bytes(40, 1, 61440, 32, 8) >= 40 * 8 * 15 * 9216
+    a, b = both(32, 8, lens_q, lens_k, causal, ws_bytes=required)
+    assert torch.equal(a, b)
+    with pytest.raises(tb.TbikError):
+        both(32, 8, lens_q, lens_k, causal, ws_bytes=required - 256)
+
+
+def test_oracle_parity():
     c = syn.attention_inputs(61, [1, 2, 1, 4], [4500, 70, 1000, 260], Hq=8, Hkv=2, D=128)
     Q, K, V = gu.dev_bf16(c["Q"]), gu.dev_bf16(c["K"]), gu.dev_bf16(c["V"])
     O = tb.tbik_attention(Q, K, V, i32(c["cu_q"]), i32(c["cu_k"]), 4, c["scale"], True)
