@@ -492,6 +492,12 @@ static DecodePlan plan_decode(int batch, int max_seqlen_q, int max_seqlen_k, int
     return {col_groups, splits, states};
 }
 
+// A launch holds fewer than 2^32 threads: from 5.6 million items on, 65535 sequences on 86 key/value heads, these workgroups
+// of 768 are too many where attention_kernel's of 256 are not.
+bool attention_decode_launches(int batch, int max_seqlen_q, int heads_q, int heads_kv) {
+    return ((int64_t)batch * heads_kv * plan_decode(batch, max_seqlen_q, 0, heads_q, heads_kv).col_groups + 7) / 8 * 8 * DEC_THREADS < ((int64_t)1 << 32);
+}
+
 bool attention_decode_supports(int max_seqlen_q, int heads_q, int heads_kv) {
     return (int64_t)max_seqlen_q * (heads_q / heads_kv) <= 2 * DEC_COLS;
 }
@@ -525,7 +531,6 @@ hipError_t launch_attention_decode(const AttnArgs &a, hipStream_t s) {
     // A workspace of the size that attention_kernel asks for may not hold the states; walking needs none and has the same bits.
     // (Where that kernel would have the splits side by side its 68 KiB per state and split are room enough for these 9 KiB.)
     if (pl.state_bytes > (a.workspace ? a.workspace_bytes : 0)) pl.n_splits = 1;
-    if ((int64_t)a.batch * a.heads_kv * pl.col_groups * pl.n_splits > 0x7ffffff0) return hipErrorInvalidValue;
     DecodeParams p;
     p.Q = a.Q; p.K = a.K; p.V = a.V; p.O = a.O;
     p.cu_q = a.cu_q; p.cu_k = a.cu_k;

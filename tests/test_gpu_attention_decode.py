@@ -122,3 +122,11 @@ def test_a_sequence_with_more_queries_than_max_seqlen_q(Hq, Hkv, said_q, lens_q,
     for lens_k in ([4500] * len(lens_q), [70 + 200 * i for i in range(len(lens_q))], [5] * len(lens_q)):
         a, b = both(Hq, Hkv, lens_q, lens_k, causal, seed=said_q, said_q=said_q)
         assert torch.equal(a, b)
+
+
+def test_more_workgroups_than_a_launch_of_this_kernel_holds():
+    """65535 sequences (three of them with a query) on 128 heads: 8.4 million items of 768 threads are past the limit of 2^32
+    threads, attention_kernel's are not."""
+    lens_q, lens_k = [0] * 65532 + [1, 1, 1], [0] * 65532 + [100, 64, 300]
+    a, b = both(128, 128, lens_q, lens_k)
+    assert torch.equal(a, b) and not (b == torch.tensor(7.0, dtype=torch.bfloat16).view(torch.int16)).all(dim=2).any()
