@@ -134,7 +134,7 @@ constexpr TileModel kTileModels[] = {
 inline size_t split_planes_bytes(int M, int N, int split) { return split > 1 ? (size_t)split * (size_t)M * (size_t)N * sizeof(float) : 0; }
 
 double tile_plan_us(const TileModel &m, int M, int N, int K, TilePlan p) {
-    const double items = (double)((M + p.rows - 1) / p.rows) * ((N + 127) / 128) * p.split;
+    const double items = (double)(((int64_t)M + p.rows - 1) / p.rows) * (((int64_t)N + 127) / 128) * p.split;
     const double stages = (double)K / m.stage_k / p.split, weights = 128.0 * K / p.split * m.bytes_per_k;
     const double step = m.step[p.rows == 32 ? 0 : p.rows == 64 ? 1 : 2];
     return m.retile * (M >= 128) + std::ceil(items / 256.0) * std::max(stages * step + m.fill, weights / (m.intake * 1e3)) +
@@ -187,7 +187,7 @@ TilePlan tile_plan(Operands kind, int M, int N, int K, int ns, int only_split, s
 constexpr double kPieceUs = 2.0;        // what a launch behind another costs
 int last_rows(Operands kind, int M, int N, int K, int ns, size_t room) {
     if (M <= 0 || N <= 0) return 0;
-    const int cols = (N + 127) / 128, per_round = 256 / cols;                    // row tiles of 128 in a round
+    const int cols = (int)(((int64_t)N + 127) / 128), per_round = 256 / cols;    // row tiles of 128 in a round
     if (g_forced_variant.load() != VARIANT_AUTO || per_round < 1 || ns > 16 || M <= per_round * 128) return 0;
     const int rest = M % (per_round * 128), full = M - rest;
     if (rest == 0) return 0;
@@ -225,7 +225,7 @@ struct F32Plan {
     double us;
 };
 F32Plan f32_plan_at(int M, int N, int K, int split) {
-    const double steps = K / 32.0 / split, cols = (N + 127) / 128;
+    const double steps = K / 32.0 / split, cols = (double)(((int64_t)N + 127) / 128);
     const double combine = split > 1 ? 3.0 + (double)split * M * N * 4.0 / 5e6 : 0.0;
     const double rounds = std::ceil(std::ceil(M / 128.0) * cols * split / 256.0), load = std::ceil(M / 32.0) * cols * split / 256.0;
     const double t128 = rounds * (steps * 1.9 + 4.0) + combine;

@@ -57,6 +57,16 @@ def test_workspace_sizes_of_empty_problems(L, fmt):
         assert size(5000, 0, k, leaf, g) <= 5120 * k // 32        # one byte per block of 32 of X at most: the microscaling formats' re-tiled scales
 
 
+@pytest.mark.parametrize("fmt", ["", "_fp8", "_mxfp4", "_mxfp8", "_mxfp6"])
+def test_workspace_sizes_at_the_largest_shapes(L, fmt):
+    """Tile counts do not overflow: the last 128 values of M or N get what a slightly smaller one gets."""
+    size = getattr(L, "tbik_gemm%s_workspace_bytes" % fmt)
+    top = 2 ** 31 - 1
+    for below in range(0, 128, 9):
+        assert 0 <= size(top - below, 128, 4096, 256, 1) - size(top - 1000, 128, 4096, 256, 1) <= 1000 * 128
+        assert size(1, top - below, 4096, 256, 1) == size(1, top - 1000, 4096, 256, 1)
+
+
 GOOD = 0x1000  # a fake, aligned, non-null "device pointer": validation must fail before it is ever used
 
 
