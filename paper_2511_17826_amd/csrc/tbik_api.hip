@@ -1,7 +1,6 @@
 // C ABI of libtbik: argument validation, variant choice, launches.  No device memory is allocated here.
 #include <algorithm>
 #include <atomic>
-#include <cmath>
 
 #include "tbik_internal.hpp"
 
@@ -82,10 +81,10 @@ int tile_rows(int M, int N) {
 // a pipeline fill per item; at K <= 12288 splitting for rounds measured slower (o_proj M = 768: 31 -> 46 us), so there
 // only the first two reasons apply.
 int internal_split(int M, int N, int K, int ns) {
-    const int64_t bm = tile_rows(M, N);
-    const int64_t tiles = ((M + bm - 1) / bm) * (((int64_t)N + 127) / 128);
+    const int bm = tile_rows(M, N);
+    const int64_t tiles = (bm == 32 ? ((int64_t)M + 31) >> 5 : bm == 64 ? ((int64_t)M + 63) >> 6 : ((int64_t)M + 127) >> 7) * (((int64_t)N + 127) / 128);
     int split = 1;
-    while (ns / split > 16 && split < TBIK_MAX_SHARDS) split *= 2;   // the tiled kernel walks at most 16 superleaves per shard
+    while (ns > 16 * split && split < TBIK_MAX_SHARDS) split *= 2;   // the tiled kernel walks at most 16 superleaves per shard
     if (K >= 16384) {
         int best = split;
         double best_cost = 0;
@@ -133,13 +132,25 @@ constexpr TileModel kTileModels[] = {
 // Bytes of the fp32 planes of a K split.
 inline size_t split_planes_bytes(int M, int N, int split) { return split > 1 ? (size_t)split * (size_t)M * (size_t)N * sizeof(float) : 0; }
 
-double tile_plan_us(const TileModel &m, int M, int N, int K, TilePlan p) {
-    const double items = (double)(((int64_t)M + p.rows - 1) / p.rows) * (((int64_t)N + 127) / 128) * p.split;
-    const double stages = (double)K / m.stage_k / p.split, weights = 128.0 * K / p.split * m.bytes_per_k;
-    const double step = m.step[p.rows == 32 ? 0 : p.rows == 64 ? 1 : 2];
-    return m.retile * (M >= 128) + std::ceil(items / 256.0) * std::max(stages * step + m.fill, weights / (m.intake * 1e3)) +
-           (p.split > 1 ? m.combine + (double)p.split * M * N * 4.0 / (m.rate * 1e6) : 0.0);
-}
+// The model's time of a shape's plans.  The plan is chosen on every call, so what does not depend on it is worked out once
+// (a split is a power of two: scaling by it is exact) and rounds are counted in integers.
+struct PlanTimes {
+    const TileModel &m;
+    int64_t M, cols;
+    double stages, weights_us, planes_us, retile_us;    // of one shard
+    PlanTimes(const TileModel &model, int rows_in_all, int N, int K)
+        : m(model), M(rows_in_all), cols(((int64_t)N + 127) / 128), stages((double)K / m.stage_k),
+          weights_us(128.0 * K * m.bytes_per_k / (m.intake * 1e3)), planes_us((double)M * N * 4.0 / (m.rate * 1e6)),
+          retile_us(M >= 128 ? m.retile : 0.0) {}
+    int64_t row_tiles(int rows) const { return rows == 32 ? (M + 31) >> 5 : rows == 64 ? (M + 63) >> 6 : (M + 127) >> 7; }
+    double us(int64_t tiles, double step, int split, double per_split) const {      // per_split: 1 / split
+        const double rounds = (double)((tiles * split + 255) >> 8);
+        const double item = std::max(stages * per_split * step + m.fill, weights_us * per_split);
+        return retile_us + rounds * item + (split > 1 ? m.combine + planes_us * split : 0.0);
+    }
+    double step(int rows) const { return m.step[rows == 32 ? 0 : rows == 64 ? 1 : 2]; }
+    double us(TilePlan p) const { return us(row_tiles(p.rows) * cols, step(p.rows), p.split, 1.0 / p.split); }
+};
 
 int forced_rows(int otherwise) {        // what tbik_set_gemm_variant forces
     switch (g_forced_variant.load()) {
@@ -154,63 +165,82 @@ int forced_rows(int otherwise) {        // what tbik_set_gemm_variant forces
 int mxfp6_split(int M, int N, int ns) {
     const int64_t tiles = (((int64_t)M + 127) / 128) * (((int64_t)N + 127) / 128);
     int split = 1;
-    while (ns / split > 16 && split < TBIK_MAX_SHARDS) split *= 2;     // the tiled kernel walks at most 16 superleaves per shard
+    while (ns > 16 * split && split < TBIK_MAX_SHARDS) split *= 2;     // the tiled kernel walks at most 16 superleaves per shard
     if (tiles >= 128) return split;
     while (split < ns && split < 16 && tiles * split < 256) split *= 2;
     return split;
 }
 
+struct TimedPlan {
+    TilePlan plan;
+    double us;
+};
 // only_split > 0: the split is the caller's (shard partials), only the height is chosen.  room: bytes for planes.
-TilePlan tile_plan(Operands kind, int M, int N, int K, int ns, int only_split, size_t room) {
+TimedPlan tile_plan(Operands kind, int M, int N, int K, int ns, int only_split, size_t room) {
     const bool one_height = kind == OPERANDS_MXFP6;
     const TilePlan rule{one_height ? 128 : forced_rows(tile_rows(M, N)),
                         only_split > 0 ? only_split : one_height ? mxfp6_split(M, N, ns) : internal_split(M, N, K, ns)};
-    if (g_forced_variant.load() != VARIANT_AUTO || M <= 0 || N <= 0) return rule;
-    const TileModel &m = kTileModels[kind];
-    TilePlan best = rule;
-    double best_us = only_split > 0 || split_planes_bytes(M, N, rule.split) <= room ? tile_plan_us(m, M, N, K, rule) / 1.04 : 1e30;
+    if (g_forced_variant.load() != VARIANT_AUTO || M <= 0 || N <= 0) return {rule, 0.0};
+    const PlanTimes times(kTileModels[kind], M, N, K);
+    const double rule_us = times.us(rule);
+    TimedPlan best{rule, rule_us};
+    double best_us = only_split > 0 || split_planes_bytes(M, N, rule.split) <= room ? rule_us / 1.04 : 1e30;
+    int first_split = only_split > 0 ? only_split : 1;
+    while (only_split <= 0 && ns > 16 * (int64_t)first_split) first_split *= 2;         // a tile walks at most 16 superleaves
+    const int last_split = only_split <= 0 ? std::min(ns, 16) : only_split <= 16 && ns / only_split <= 16 ? only_split : 0;
+    int64_t shorter = 0;
     for (int rows = one_height ? 128 : 32; rows <= 128; rows *= 2) {
-        for (int split = only_split > 0 ? only_split : 1; split <= ns && split <= 16; split *= 2) {
-            if (ns / split <= 16 && (only_split > 0 || split_planes_bytes(M, N, split) <= room)) {     // a tile walks at most 16 superleaves
-                const double us = tile_plan_us(m, M, N, K, {rows, split});
-                if (us < best_us) { best = {rows, split}; best_us = us; }
-            }
-            if (only_split > 0) break;
+        const int64_t row_tiles = times.row_tiles(rows);
+        if (row_tiles == shorter) break;                // a taller tile that does not save one costs more
+        shorter = row_tiles;
+        const double step = times.step(rows);
+        double per_split = 1.0 / first_split;
+        for (int split = first_split; split <= last_split; split *= 2, per_split *= 0.5) {
+            if (only_split <= 0 && split_planes_bytes(M, N, split) > room) break;
+            const double us = times.us(row_tiles * times.cols, step, split, per_split);
+            if (us < best_us) { best = {{rows, split}, us}; best_us = us; }
         }
     }
     return best;
 }
-// Rows of a batch that are better computed by a call of their own (0: none): a launch whose last round of tiles is nearly
-// empty is cut behind its last full round, and the remaining rows get the height and split of a small batch.  1100 rows
-// of 4096 x 4096 in bf16 are 288 tiles of 128 rows, two rounds, 72 us; as 1024 rows and 76 rows 54 us.  (The rows of
+// Rows of a batch that are better computed by a call of their own (last_rows, 0: none): a launch whose last round of tiles is
+// nearly empty is cut behind its last full round, and the remaining rows get the height and split of a small batch.  1100
+// rows of 4096 x 4096 in bf16 are 288 tiles of 128 rows, two rounds, 72 us; as 1024 rows and 76 rows 54 us.  (The rows of
 // a result do not depend on each other, so neither do their bits.)
 constexpr double kPieceUs = 2.0;        // what a launch behind another costs
-int last_rows(Operands kind, int M, int N, int K, int ns, size_t room) {
-    if (M <= 0 || N <= 0) return 0;
-    const int cols = (int)(((int64_t)N + 127) / 128), per_round = 256 / cols;    // row tiles of 128 in a round
-    if (g_forced_variant.load() != VARIANT_AUTO || per_round < 1 || ns > 16 || M <= per_round * 128) return 0;
+struct BatchPlan {
+    int last_rows;
+    TilePlan first, last;               // of the rows before the last ones, of the last ones
+    size_t planes;                      // bytes: the larger need of the last rows' plan and of the whole batch's as one piece
+};
+BatchPlan batch_plan(Operands kind, int M, int N, int K, int ns, size_t room) {
+    const TimedPlan whole = tile_plan(kind, M, N, K, ns, 0, room);
+    BatchPlan plan{0, whole.plan, whole.plan, split_planes_bytes(M, N, whole.plan.split)};
+    if (M <= 0 || N <= 0 || ns > 16 || g_forced_variant.load() != VARIANT_AUTO) return plan;
+    const int64_t cols = ((int64_t)N + 127) / 128;
+    const int per_round = cols > 256 ? 0 : 256 / (int)cols;                      // row tiles of 128 in a round
+    if (per_round < 1 || M <= per_round * 128) return plan;
     const int rest = M % (per_round * 128), full = M - rest;
-    if (rest == 0) return 0;
-    const TileModel &m = kTileModels[kind];
-    const double whole = tile_plan_us(m, M, N, K, tile_plan(kind, M, N, K, ns, 0, room));
-    const double pieces = tile_plan_us(m, full, N, K, tile_plan(kind, full, N, K, ns, 0, room)) +
-                          tile_plan_us(m, rest, N, K, tile_plan(kind, rest, N, K, ns, 0, room)) + kPieceUs;
-    return pieces < 0.95 * whole ? rest : 0;
+    if (rest == 0) return plan;
+    const TimedPlan first = tile_plan(kind, full, N, K, ns, 0, room), last = tile_plan(kind, rest, N, K, ns, 0, room);
+    if (first.us + last.us + kPieceUs >= 0.95 * whole.us) return plan;
+    plan.planes = std::max(plan.planes, split_planes_bytes(rest, N, last.plan.split));
+    plan.last_rows = rest;
+    plan.first = first.plan;
+    plan.last = last.plan;
+    return plan;
 }
 // Bytes of planes a call can make use of, the older rule's included.
 size_t plan_planes_bytes(Operands kind, int M, int N, int K, int ns) {
-    size_t bytes = std::max(split_planes_bytes(M, N, kind == OPERANDS_MXFP6 ? mxfp6_split(M, N, ns) : internal_split(M, N, K, ns)),
-                            split_planes_bytes(M, N, tile_plan(kind, M, N, K, ns, 0, SIZE_MAX).split));
-    if (const int rest = last_rows(kind, M, N, K, ns, SIZE_MAX))
-        bytes = std::max(bytes, split_planes_bytes(rest, N, tile_plan(kind, rest, N, K, ns, 0, SIZE_MAX).split));
-    return bytes;
+    return std::max(split_planes_bytes(M, N, kind == OPERANDS_MXFP6 ? mxfp6_split(M, N, ns) : internal_split(M, N, K, ns)),
+                    batch_plan(kind, M, N, K, ns, SIZE_MAX).planes);
 }
-// Calls piece(first row, rows) for the one or two pieces of a batch.
+// Calls piece(first row, rows, plan) for the one or two pieces of a batch.
 template <class Piece>
 hipError_t in_pieces(Operands kind, int M, int N, int K, int ns, size_t room, Piece piece) {
-    const int rest = last_rows(kind, M, N, K, ns, room);
-    hipError_t e = piece(0, M - rest);
-    return (e == hipSuccess && rest > 0) ? piece(M - rest, rest) : e;
+    const BatchPlan plan = batch_plan(kind, M, N, K, ns, room);
+    hipError_t e = piece(0, M - plan.last_rows, plan.first);
+    return (e == hipSuccess && plan.last_rows > 0) ? piece(M - plan.last_rows, plan.last_rows, plan.last) : e;
 }
 
 // fp32 operands: tile height and K split of a shape (pure), by a model of the time.  The fp32 MFMA is slow (a K-step of 32
@@ -225,17 +255,18 @@ struct F32Plan {
     double us;
 };
 F32Plan f32_plan_at(int M, int N, int K, int split) {
-    const double steps = K / 32.0 / split, cols = (double)(((int64_t)N + 127) / 128);
+    const int64_t cols = ((int64_t)N + 127) / 128, items128 = ((int64_t)M + 127) / 128 * cols * split, items32 = ((int64_t)M + 31) / 32 * cols * split;
+    const double steps = K / 32.0 / split;
     const double combine = split > 1 ? 3.0 + (double)split * M * N * 4.0 / 5e6 : 0.0;
-    const double rounds = std::ceil(std::ceil(M / 128.0) * cols * split / 256.0), load = std::ceil(M / 32.0) * cols * split / 256.0;
+    const double rounds = (double)((items128 + 255) >> 8), load = (double)items32 / 256.0;
     const double t128 = rounds * (steps * 1.9 + 4.0) + combine;
-    const double t32 = (load <= 1.0 ? 1.0 : 0.5 * (load + std::ceil(load))) * steps * 0.585 + 6.0 + combine;
+    const double t32 = (items32 <= 256 ? 1.0 : 0.5 * (load + (double)((items32 + 255) >> 8))) * steps * 0.585 + 6.0 + combine;
     return t32 < t128 ? F32Plan{32, split, t32} : F32Plan{128, split, t128};
 }
 F32Plan f32_plan(int M, int N, int K, int ns) {
     F32Plan best{0, 0, 0.0};
     for (int split = 1; split <= ns && split <= TBIK_MAX_SHARDS; split *= 2) {
-        if (ns / split > 16) continue;                  // the tiled kernel walks at most 16 superleaves per shard
+        if (ns > 16 * split) continue;                  // the tiled kernel walks at most 16 superleaves per shard
         if (best.rows && split > 16) break;
         const F32Plan p = f32_plan_at(M, N, K, split);
         if (!best.rows || p.us < best.us) best = p;
@@ -285,7 +316,7 @@ int gemm_shard_partials(int x_dtype, const void *X, int64_t ldx, const void *W, 
     if (!aligned(partials, 16)) return TBIK_ERR_ALIGN;
     GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)W, ldw, partials, nullptr, 0, TBIK_F32, M, N, K, sl, ns, P, x_dtype};
     hipStream_t s = (hipStream_t)hip_stream;
-    const int v = pick_variant(a, tile_plan(OPERANDS_16BIT, M, N, K, ns, P, 0).rows);
+    const int v = pick_variant(a, tile_plan(OPERANDS_16BIT, M, N, K, ns, P, 0).plan.rows);
     hipError_t e = (v == VARIANT_REFERENCE) ? launch_reference(a, s) : launch_tiled(a, v, s);
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
@@ -328,7 +359,7 @@ int gemm(int x_dtype, const void *X, int64_t ldx, const void *W, int64_t ldw, vo
         const int own = f32_plan(M, N, K, ns).split;
         e = rows_with(0, M, {0, own == 1 || split_planes_bytes(M, N, own) <= room ? own : internal_split(M, N, K, ns)});
     } else {
-        e = in_pieces(OPERANDS_16BIT, M, N, K, ns, room, [&](int m0, int m) { return rows_with(m0, m, tile_plan(OPERANDS_16BIT, m, N, K, ns, 0, room)); });
+        e = in_pieces(OPERANDS_16BIT, M, N, K, ns, room, rows_with);
     }
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
@@ -463,8 +494,7 @@ int tbik_gemm_fp8(const void *X, int64_t ldx, const void *Wt, int64_t ldwt, void
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)hip_stream;
     const size_t room = workspace ? workspace_bytes : 0;
-    hipError_t e = in_pieces(OPERANDS_FP8, M, N, K, ns, room, [&](int m0, int m) {
-        const TilePlan plan = tile_plan(OPERANDS_FP8, m, N, K, ns, 0, room);
+    hipError_t e = in_pieces(OPERANDS_FP8, M, N, K, ns, room, [&](int m0, int m, TilePlan plan) {
         void *y = static_cast<char *>(Y) + (int64_t)m0 * ldy * (y_dtype == TBIK_F32 ? 4 : 2);
         GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
                    (int)y_dtype, m, N, K, sl, ns, 1, (int)x_dtype, 0};
@@ -493,7 +523,7 @@ int tbik_gemm_shard_partials_fp8(const void *X, int64_t ldx, const void *Wt, int
     if (!aligned(partials, 16)) return TBIK_ERR_ALIGN;
     GemmArgs a{(const uint16_t *)X, ldx, (const uint16_t *)Wt, ldwt, partials, nullptr, 0, TBIK_F32, M, N, K, sl, ns, P, (int)x_dtype, 0};
     const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_fp8_tiled_supports(a);
-    hipError_t e = tiled ? launch_gemm_fp8_tiled(a, tile_plan(OPERANDS_FP8, M, N, K, ns, P, 0).rows, (hipStream_t)hip_stream)
+    hipError_t e = tiled ? launch_gemm_fp8_tiled(a, tile_plan(OPERANDS_FP8, M, N, K, ns, P, 0).plan.rows, (hipStream_t)hip_stream)
                          : launch_gemm_fp8_reference(a, (hipStream_t)hip_stream);
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
@@ -557,8 +587,7 @@ int tbik_gemm_mxfp4(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)hip_stream;
     const size_t room = workspace && workspace_bytes > scales_room ? (workspace_bytes - scales_room) & ~(size_t)255 : 0;      // planes are rounded up to 256 bytes
-    hipError_t e = in_pieces(OPERANDS_MXFP4, M, N, K, ns, room, [&](int m0, int m) {
-        const TilePlan plan = tile_plan(OPERANDS_MXFP4, m, N, K, ns, 0, room);
+    hipError_t e = in_pieces(OPERANDS_MXFP4, M, N, K, ns, room, [&](int m0, int m, TilePlan plan) {
         void *y = static_cast<char *>(Y) + (int64_t)m0 * ldy * (y_dtype == TBIK_F32 ? 4 : 2);
         GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
                    (int)y_dtype, m, N, K, sl, ns, 1, TBIK_MXFP4, 0};
@@ -593,7 +622,7 @@ int tbik_gemm_shard_partials_mxfp4(const void *X, int64_t ldx, const void *Xs, i
     const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_mxfp4_tiled_supports(a, sc);
     // a workspace as tbik_gemm_mxfp4 takes it has room for the re-tiled scales
     void *retiled = (tiled && mx_retiles(M) && workspace && aligned(workspace, 256) && workspace_bytes >= mxfp4_scales_room(M, N, K)) ? workspace : nullptr;
-    hipError_t e = tiled ? launch_gemm_mxfp4_tiled(a, sc, tile_plan(OPERANDS_MXFP4, M, N, K, ns, P, 0).rows, retiled, (hipStream_t)hip_stream)
+    hipError_t e = tiled ? launch_gemm_mxfp4_tiled(a, sc, tile_plan(OPERANDS_MXFP4, M, N, K, ns, P, 0).plan.rows, retiled, (hipStream_t)hip_stream)
                          : launch_gemm_mxfp4_reference(a, sc, (hipStream_t)hip_stream);
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
@@ -652,8 +681,7 @@ int tbik_gemm_mxfp8(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)hip_stream;
     const size_t room = workspace && workspace_bytes > scales_room ? (workspace_bytes - scales_room) & ~(size_t)255 : 0;      // planes are rounded up to 256 bytes
-    hipError_t e = in_pieces(OPERANDS_MXFP8, M, N, K, ns, room, [&](int m0, int m) {
-        const TilePlan plan = tile_plan(OPERANDS_MXFP8, m, N, K, ns, 0, room);
+    hipError_t e = in_pieces(OPERANDS_MXFP8, M, N, K, ns, room, [&](int m0, int m, TilePlan plan) {
         void *y = static_cast<char *>(Y) + (int64_t)m0 * ldy * (y_dtype == TBIK_F32 ? 4 : 2);
         GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
                    (int)y_dtype, m, N, K, sl, ns, 1, (int)x_dtype, 0};
@@ -688,7 +716,7 @@ int tbik_gemm_shard_partials_mxfp8(const void *X, int64_t ldx, const void *Xs, i
     const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_mxfp8_tiled_supports(a, sc);
     // a workspace as tbik_gemm_mxfp8 takes it has room for the re-tiled scales
     void *retiled = (tiled && mx_retiles(M) && workspace && aligned(workspace, 256) && workspace_bytes >= mxfp8_scales_room(M, N, K)) ? workspace : nullptr;
-    hipError_t e = tiled ? launch_gemm_mxfp8_tiled(a, sc, tile_plan(OPERANDS_MXFP8, M, N, K, ns, P, 0).rows, retiled, (hipStream_t)hip_stream)
+    hipError_t e = tiled ? launch_gemm_mxfp8_tiled(a, sc, tile_plan(OPERANDS_MXFP8, M, N, K, ns, P, 0).plan.rows, retiled, (hipStream_t)hip_stream)
                          : launch_gemm_mxfp8_reference(a, sc, (hipStream_t)hip_stream);
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
@@ -750,8 +778,7 @@ int tbik_gemm_mxfp6(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)hip_stream;
     const size_t room = workspace && workspace_bytes > scales_room ? (workspace_bytes - scales_room) & ~(size_t)255 : 0;      // planes are rounded up to 256 bytes
-    hipError_t e = in_pieces(OPERANDS_MXFP6, M, N, K, ns, room, [&](int m0, int m) {
-        const TilePlan plan = tile_plan(OPERANDS_MXFP6, m, N, K, ns, 0, room);
+    hipError_t e = in_pieces(OPERANDS_MXFP6, M, N, K, ns, room, [&](int m0, int m, TilePlan plan) {
         void *y = static_cast<char *>(Y) + (int64_t)m0 * ldy * (y_dtype == TBIK_F32 ? 4 : 2);
         GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
                    (int)y_dtype, m, N, K, sl, ns, 1, (int)x_dtype, 0};
