@@ -296,8 +296,12 @@ int tbik_attention_f16(const void *Q, const void *K, const void *V, void *O,
                        float scale, int causal, void *workspace, size_t workspace_bytes, void *hip_stream);
 
 /* Scratch sizes (pure host functions; 0 if the arguments are illegal or no scratch is needed).
- * tbik_gemm_workspace_bytes covers tbik_gemm and tbik_gemm_shard_partials for any legal P. */
+ * tbik_gemm_workspace_bytes covers tbik_gemm and tbik_gemm_shard_partials and their fp16 and fp32 forms for any legal P;
+ * it is the larger of the two below it, which a caller of one operand width alone can reserve instead: fp32's plans may
+ * take planes where 16-bit operands need none (600 x 4096 at K = 4096: 75 MiB and 0). */
 size_t tbik_gemm_workspace_bytes(int M, int N, int K, int leaf, int k_first);
+size_t tbik_gemm_16bit_workspace_bytes(int M, int N, int K, int leaf, int k_first);
+size_t tbik_gemm_f32_workspace_bytes(int M, int N, int K, int leaf, int k_first);
 size_t tbik_row_reduce_workspace_bytes(int M, int64_t V, tbik_rowop op);
 
 /* Reference kernel of tbik_gemm_shard_partials / tbik_gemm: one wavefront per 32x32 output tile,

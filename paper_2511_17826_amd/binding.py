@@ -79,6 +79,8 @@ SIGNATURES = {
                                           C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p]),
     "tbik_gemm_fp8_workspace_bytes": (C.c_size_t, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int]),
     "tbik_gemm_workspace_bytes": (C.c_size_t, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int]),
+    "tbik_gemm_16bit_workspace_bytes": (C.c_size_t, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int]),
+    "tbik_gemm_f32_workspace_bytes": (C.c_size_t, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int]),
     "tbik_row_reduce_workspace_bytes": (C.c_size_t, [C.c_int, C.c_int64, C.c_int]),
     "tbik_gemm_reference": (C.c_int, [C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p, C.c_int64,
                                       C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p]),
@@ -195,6 +197,14 @@ def gemm_workspace_bytes(M, N, K, leaf, k_first=1) -> int:
     return int(lib().tbik_gemm_workspace_bytes(M, N, K, leaf, k_first))
 
 
+def gemm_16bit_workspace_bytes(M, N, K, leaf, k_first=1) -> int:
+    return int(lib().tbik_gemm_16bit_workspace_bytes(M, N, K, leaf, k_first))
+
+
+def gemm_f32_workspace_bytes(M, N, K, leaf, k_first=1) -> int:
+    return int(lib().tbik_gemm_f32_workspace_bytes(M, N, K, leaf, k_first))
+
+
 def _gemm(entry: str, in_dtype, X, W, leaf, k_first, out_dtype, out, workspace):
     _rowmajor(X, "X"); _rowmajor(W, "W")
     assert X.dtype == in_dtype and W.dtype == in_dtype
@@ -205,7 +215,7 @@ def _gemm(entry: str, in_dtype, X, W, leaf, k_first, out_dtype, out, workspace):
         out = torch.empty((M, N), dtype=out_dtype, device=X.device)
     _rowmajor(out, "out")
     if workspace is None:
-        need = gemm_workspace_bytes(M, N, K, leaf, k_first)
+        need = gemm_16bit_workspace_bytes(M, N, K, leaf, k_first)
         if need:
             workspace = _workspace(need, X.device)
     st = getattr(lib(), entry)(X.data_ptr(), X.stride(0), W.data_ptr(), W.stride(0), out.data_ptr(), out.stride(0),
@@ -241,7 +251,7 @@ def tbik_gemm_f32(X: torch.Tensor, W: torch.Tensor, leaf: int, k_first: int = 1,
     _rowmajor(out, "out")
     assert out.dtype == torch.float32 and out.shape == (M, N)
     if workspace is None:
-        need = gemm_workspace_bytes(M, N, K, leaf, k_first)
+        need = gemm_f32_workspace_bytes(M, N, K, leaf, k_first)
         if need:
             workspace = _workspace(need, X.device)
     st = lib().tbik_gemm_f32(X.data_ptr(), X.stride(0), W.data_ptr(), W.stride(0), out.data_ptr(), out.stride(0),
@@ -260,7 +270,7 @@ def _gemm_shard_partials(entry: str, in_dtype, X, W, leaf, k_first, P, out, work
     if out is None:
         out = torch.empty((max(P, 1), M, N), dtype=torch.float32, device=X.device)
     assert out.is_contiguous() and out.dtype == torch.float32
-    need = gemm_workspace_bytes(M, N, K, leaf, k_first)
+    need = (gemm_f32_workspace_bytes if in_dtype == torch.float32 else gemm_16bit_workspace_bytes)(M, N, K, leaf, k_first)
     if workspace is None and need:
         workspace = _workspace(need, X.device)
     st = getattr(lib(), entry)(X.data_ptr(), X.stride(0), W.data_ptr(), W.stride(0), out.data_ptr(),

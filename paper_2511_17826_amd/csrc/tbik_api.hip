@@ -293,11 +293,21 @@ inline bool legal_y_dtype(int y_dtype, int x_dtype) { return y_dtype == TBIK_F32
 
 extern "C" {
 
-size_t tbik_gemm_workspace_bytes(int M, int N, int K, int leaf, int k_first) {
+// fp32 partials of the K split, if this shape uses one.
+size_t tbik_gemm_16bit_workspace_bytes(int M, int N, int K, int leaf, int k_first) {
     int sl, ns;
     if (check_tree(M, N, K, leaf, k_first, 1, &sl, &ns) != TBIK_OK) return 0;
-    // fp32 partials of the internal K split, if this shape uses one (16-bit or fp32 operands: the larger of the two)
-    return std::max(plan_planes_bytes(OPERANDS_16BIT, M, N, K, ns), split_planes_bytes(M, N, f32_plan(M, N, K, ns).split));
+    return plan_planes_bytes(OPERANDS_16BIT, M, N, K, ns);
+}
+
+size_t tbik_gemm_f32_workspace_bytes(int M, int N, int K, int leaf, int k_first) {
+    int sl, ns;
+    if (check_tree(M, N, K, leaf, k_first, 1, &sl, &ns) != TBIK_OK) return 0;
+    return std::max(split_planes_bytes(M, N, internal_split(M, N, K, ns)), split_planes_bytes(M, N, f32_plan(M, N, K, ns).split));
+}
+
+size_t tbik_gemm_workspace_bytes(int M, int N, int K, int leaf, int k_first) {
+    return std::max(tbik_gemm_16bit_workspace_bytes(M, N, K, leaf, k_first), tbik_gemm_f32_workspace_bytes(M, N, K, leaf, k_first));
 }
 
 }  // extern "C"

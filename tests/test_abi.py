@@ -48,7 +48,7 @@ def test_workspace_sizes_are_pure_and_zero_for_illegal_shapes(L):
     assert L.tbik_row_reduce_workspace_bytes(4, 100, 7) == 0
 
 
-@pytest.mark.parametrize("fmt", ["", "_fp8", "_mxfp4", "_mxfp8", "_mxfp6", "_swiglu"])
+@pytest.mark.parametrize("fmt", ["", "_16bit", "_f32", "_fp8", "_mxfp4", "_mxfp8", "_mxfp6", "_swiglu"])
 def test_workspace_sizes_of_empty_problems(L, fmt):
     """No rows or no columns: a size and no division by zero (the callers size the workspace before the call looks at M and N)."""
     size = getattr(L, "tbik_gemm%s_workspace_bytes" % fmt)
@@ -57,7 +57,18 @@ def test_workspace_sizes_of_empty_problems(L, fmt):
         assert size(5000, 0, k, leaf, g) <= 5120 * k // 32        # one byte per block of 32 of X at most: the microscaling formats' re-tiled scales
 
 
-@pytest.mark.parametrize("fmt", ["", "_fp8", "_mxfp4", "_mxfp8", "_mxfp6"])
+def test_workspace_sizes_of_one_operand_width(L):
+    """16-bit operands do not reserve what only fp32's plans use; the size for both is the larger one."""
+    planes = lambda n, M, N: n * M * N * 4
+    assert L.tbik_gemm_16bit_workspace_bytes(600, 4096, 4096, 256, 1) == 0 < L.tbik_gemm_f32_workspace_bytes(600, 4096, 4096, 256, 1)
+    assert L.tbik_gemm_16bit_workspace_bytes(1100, 4096, 12288, 256, 3) <= planes(4, 1100, 4096)
+    for M in (0, 1, 77, 321, 600, 1100, 1500, 4096):
+        for k, n, leaf, g in ((4096, 4096, 256, 1), (12288, 4096, 256, 3), (25600, 5120, 128, 25), (6144, 2048, 128, 3)):
+            both = L.tbik_gemm_16bit_workspace_bytes(M, n, k, leaf, g), L.tbik_gemm_f32_workspace_bytes(M, n, k, leaf, g)
+            assert L.tbik_gemm_workspace_bytes(M, n, k, leaf, g) == max(both)
+
+
+@pytest.mark.parametrize("fmt", ["", "_16bit", "_f32", "_fp8", "_mxfp4", "_mxfp8", "_mxfp6"])
 def test_workspace_sizes_at_the_largest_shapes(L, fmt):
     """Tile counts do not overflow: the last 128 values of M or N get what a slightly smaller one gets."""
     size = getattr(L, "tbik_gemm%s_workspace_bytes" % fmt)

@@ -81,3 +81,13 @@ def test_last_rows_as_a_call_of_their_own(M):
         y = getattr(tb, "tbik_gemm_" + kind)(*dev, LEAF, 1)
         one = getattr(tb, "tbik_gemm_" + kind)(*ops, LEAF, 1)
         assert torch.equal(y.view(torch.int16), one.repeat(rep, 1)[:M].view(torch.int16)), kind
+
+
+def test_a_16_bit_call_holds_no_planes_of_the_fp32_plans(monkeypatch):
+    """600 rows of 4096 x 4096: no planes in 16 bits, 75 MiB in fp32."""
+    asked = []
+    monkeypatch.setattr(tb, "_workspace", lambda nbytes, device, real=tb._workspace: asked.append(nbytes) or real(nbytes, device))
+    for dt, call, parts in ((torch.bfloat16, tb.tbik_gemm, tb.tbik_gemm_shard_partials), (torch.float16, tb.tbik_gemm_f16, tb.tbik_gemm_shard_partials_f16)):
+        X, W = torch.ones((600, 4096), dtype=dt, device="cuda:0"), torch.ones((4096, 4096), dtype=dt, device="cuda:0")
+        assert (call(X, W, 256, 1) == 4096).all() and (parts(X, W, 256, 1, 2) == 2048).all()
+    assert asked == []
