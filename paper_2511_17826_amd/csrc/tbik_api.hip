@@ -211,7 +211,7 @@ constexpr double kPieceUs = 2.0;        // what a launch behind another costs
 struct BatchPlan {
     int last_rows;
     TilePlan first, last;               // of the rows before the last ones, of the last ones
-    size_t planes;                      // bytes: the larger need of the last rows' plan and of the whole batch's as one piece
+    size_t planes;                      // bytes that the plans use
 };
 BatchPlan batch_plan(Operands kind, int M, int N, int K, int ns, size_t room) {
     const TimedPlan whole = tile_plan(kind, M, N, K, ns, 0, room);
@@ -224,7 +224,7 @@ BatchPlan batch_plan(Operands kind, int M, int N, int K, int ns, size_t room) {
     if (rest == 0) return plan;
     const TimedPlan first = tile_plan(kind, full, N, K, ns, 0, room), last = tile_plan(kind, rest, N, K, ns, 0, room);
     if (first.us + last.us + kPieceUs >= 0.95 * whole.us) return plan;
-    plan.planes = std::max(plan.planes, split_planes_bytes(rest, N, last.plan.split));
+    plan.planes = std::max(split_planes_bytes(full, N, first.plan.split), split_planes_bytes(rest, N, last.plan.split));
     plan.last_rows = rest;
     plan.first = first.plan;
     plan.last = last.plan;
