@@ -51,7 +51,8 @@ def test_few_queries_same_bits_at_tile_and_round_edges(Hq, Hkv, q, causal):
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("batch,Hkv", [(1, 1), (3, 8), (9, 8), (17, 8), (40, 8), (70, 8)])
-def test_splits_in_parallel_walked_and_channel_groups_same_bits(dtype, batch, Hkv):
+@pytest.mark.parametrize("causal", [True, False])
+def test_splits_in_parallel_walked_and_channel_groups_same_bits(dtype, batch, Hkv, causal):
     """1 to 3 splits of 4096 keys, sequences without keys or queries among them; few items (channel groups, one workgroup
     per split and a fold) to many (splits walked)."""
     lens = [4096, 4097, 4160, 8192, 8193, 4351, 100, 0, 9000, 4095]
@@ -59,7 +60,7 @@ def test_splits_in_parallel_walked_and_channel_groups_same_bits(dtype, batch, Hk
     lens_q = [1] * batch
     if batch > 5:
         lens_q[5] = 0
-    a, b = both(4 * Hkv, Hkv, lens_q, lens_k, dtype=dtype, seed=batch)
+    a, b = both(4 * Hkv, Hkv, lens_q, lens_k, causal, dtype=dtype, seed=batch)
     assert torch.equal(a, b)
 
 

@@ -30,21 +30,16 @@ def test_plan_bits(K, N, leaf, kf, M):
     tb.tbik_set_gemm_variant(0)
 
 
-def test_smaller_workspace_takes_a_smaller_split():
-    M, N, K, leaf = 600, 2048, 1536, 96
+@pytest.mark.parametrize("M,N,K,leaf,rule,plan", [(1200, 2048, 1536, 96, 1, 2), (321, 4096, 2048, 256, 1, 2), (129, 4096, 4096, 256, 4, 8)])
+def test_smaller_workspace_takes_a_smaller_split(M, N, K, leaf, rule, plan):
+    """The model's split takes more planes than the older rule's: a workspace of the rule's planes is enough, the bits are the same,
+    and less is refused."""
     X, W = torch.randn((M, K), device="cuda:0"), torch.randn((K, N), device="cuda:0")
     want = tb.tbik_gemm_reference_f32(X, W, leaf, 1)[1]
-    full = tb.gemm_workspace_bytes(M, N, K, leaf, 1)
-    sizes = []
-    for planes in (16, 8, 4, 2):
-        nbytes = planes * M * N * 4
-        if nbytes > full:
-            continue
-        ws = torch.full((nbytes // 4,), float("nan"), dtype=torch.float32, device="cuda:0")
-        try:
-            out = tb.tbik_gemm_f32(X, W, leaf, 1, workspace=ws)
-        except tb.TbikError:
-            continue
-        sizes.append(planes)
-        assert torch.equal(out.view(torch.int32), want.view(torch.int32)), planes
-    assert sizes
+    assert tb.gemm_f32_workspace_bytes(M, N, K, leaf, 1) == plan * M * N * 4
+    for planes in (0 if rule == 1 else rule, plan - 1, plan):
+        ws = torch.full((planes * M * N,), float("nan"), dtype=torch.float32, device="cuda:0")
+        assert torch.equal(tb.tbik_gemm_f32(X, W, leaf, 1, workspace=ws).view(torch.int32), want.view(torch.int32)), planes
+    if rule > 1:
+        with pytest.raises(tb.TbikError):
+            tb.tbik_gemm_f32(X, W, leaf, 1, workspace=torch.empty(rule * M * N - 64, dtype=torch.float32, device="cuda:0"))
