@@ -78,8 +78,8 @@ int tile_rows(int M, int N) {
 // long K, rounds -- 256 compute units take the work items in rounds, so 320 tiles cost two rounds of whole-K tiles
 // unsplit but five rounds of quarter-K items split in four (32B-class down_proj, K = 25600: M = 1024 454 -> 323 us,
 // M = 512 218 -> 189 us, M = 128 78 -> 64 us).  The price of a split is the partials' round trip, the second launch and
-// a pipeline fill per item; at K <= 12288 splitting for rounds measured slower (o_proj M = 768: 31 -> 46 us), so there
-// only the first two reasons apply.
+// a pipeline fill per item; at K <= 12288 splitting for rounds measured slower (o_proj M = 768: 31 -> 46 us), so this rule
+// applies only the first two reasons there (the time model below may still split).
 int internal_split(int M, int N, int K, int ns) {
     const int bm = tile_rows(M, N);
     const int64_t tiles = (bm == 32 ? ((int64_t)M + 31) >> 5 : bm == 64 ? ((int64_t)M + 63) >> 6 : ((int64_t)M + 127) >> 7) * (((int64_t)N + 127) / 128);
@@ -105,10 +105,16 @@ int internal_split(int M, int N, int K, int ns) {
 // with rounds = work items / 256 compute units, rounded up.  What the two rules above miss is how evenly the items fill the
 // compute units and that a lower tile is cheaper than a padded one: 100 rows of 4096 x 4096 in 8-bit operands took 128-row
 // tiles split in eight, 18.9 us, and take 12.4 us as 32-row tiles split in two; 400 rows at K = 12288 in bf16 took 224 tiles
-// of 64 rows, 82 us, and take 61 us as 128-row tiles split in two.  Constants fitted to 88 (16-bit) and 3 x 30 (8- and 4-bit)
-// shapes, K = 4096, 12288 and 25600 x {1 .. 4096} rows, each timed at every height and split: the choice is within 0.4 % of
-// the best of them in the mean (the rules: 5 to 9 %) and 6 % at most.  They are not physical rates one by one.  The rules'
-// choice stays where the model promises less than 4 %.
+// of 64 rows, 82 us, and take 61 us as 128-row tiles split in two.  The constants were fitted to times of K = 4096, 12288 and
+// 25600; they are not physical rates one by one (the same planes move at 12 TB/s in one row and at 1.2 in another), and the
+// time they give is off by -36 .. +36 % for 16-bit operands, -47 .. +25 % for the others: they rank plans, no more.  Checked
+// over 227 (16-bit) and 4 x 99 (low-bit) shapes of the tests' layers, K = 5120 and 14336 among them, 1 .. 4096 rows, each timed
+// at every height and split (profiles/tile_split_plans.csv): the chosen plan, cuts included, takes 0.938 (16-bit), 0.894
+// (8-bit), 0.924 (MXFP8), 0.899 (MXFP4) and 0.941 (MXFP6) of the rules' time in the geometric mean and up to 1.06, 1.04, 1.01,
+// 1.03 and 1.02 of it (two runs of one plan differ by up to 4 %), and 0.992 .. 0.998 of the best plan in one piece in the
+// mean, up to 1.18, 1.09, 1.06, 1.12 and 1.20.  The rules' choice stays where the model promises less than the margin: with
+// 4 % for 16-bit operands too it split 21 of the 227 that the rules computed faster by more than 2 % (768 rows at K = 12288
+// 96 against 90 us, 768 rows of 4096 x 6144 71 against 65, and 56 now, cut behind 640); with 8 % three are left.
 enum Operands { OPERANDS_16BIT, OPERANDS_FP8, OPERANDS_MXFP8, OPERANDS_MXFP4, OPERANDS_MXFP6 };
 struct TilePlan {
     int rows, split;
@@ -120,13 +126,14 @@ struct TileModel {
     double intake;                      // bytes of W per us and compute unit, in thousands
     double combine, rate;               // us; bytes of planes per us, in millions
     double retile;                      // us: the scales' re-tiling from 128 rows on
+    double margin;                      // the rules' choice stays where the model promises less than this
 };
 constexpr TileModel kTileModels[] = {
-    {64, 2.0, {0.005, 0.21, 0.525}, 5.9, 38.5, 3.95, 12.0, 0.0},
-    {128, 1.0, {0.01, 0.24, 0.33}, 3.1, 51.0, 2.7, 1.2, 0.0},
-    {128, 1.0, {0.0, 0.185, 0.375}, 3.6, 42.0, 4.8, 2.5, 4.0},
-    {256, 0.5, {0.31, 0.335, 0.574}, 4.1, 31.4, 2.64, 2.7, 4.0},
-    {128, 0.75, {0.0, 0.0, 0.61}, 3.6, 36.0, 4.8, 2.5, 4.0},       // one height; MXFP8's with its stage
+    {64, 2.0, {0.005, 0.21, 0.525}, 5.9, 38.5, 3.95, 12.0, 0.0, 1.08},
+    {128, 1.0, {0.01, 0.24, 0.33}, 3.1, 51.0, 2.7, 1.2, 0.0, 1.04},
+    {128, 1.0, {0.0, 0.185, 0.375}, 3.6, 42.0, 4.8, 2.5, 4.0, 1.04},
+    {256, 0.5, {0.31, 0.335, 0.574}, 4.1, 31.4, 2.64, 2.7, 4.0, 1.04},
+    {128, 0.75, {0.0, 0.0, 0.61}, 3.6, 36.0, 4.8, 2.5, 4.0, 1.04},       // one height; MXFP8's with its stage
 };
 
 // Bytes of the fp32 planes of a K split.
@@ -184,7 +191,7 @@ TimedPlan tile_plan(Operands kind, int M, int N, int K, int ns, int only_split, 
     const PlanTimes times(kTileModels[kind], M, N, K);
     const double rule_us = times.us(rule);
     TimedPlan best{rule, rule_us};
-    double best_us = only_split > 0 || split_planes_bytes(M, N, rule.split) <= room ? rule_us / 1.04 : 1e30;
+    double best_us = only_split > 0 || split_planes_bytes(M, N, rule.split) <= room ? rule_us / times.m.margin : 1e30;
     int first_split = only_split > 0 ? only_split : 1;
     while (only_split <= 0 && ns > 16 * (int64_t)first_split) first_split *= 2;         // a tile walks at most 16 superleaves
     const int last_split = only_split <= 0 ? std::min(ns, 16) : only_split <= 16 && ns / only_split <= 16 ? only_split : 0;
@@ -248,8 +255,9 @@ hipError_t in_pieces(Operands kind, int M, int N, int K, int ns, size_t room, Pi
 // so what decides is how evenly the work items fill 256 compute units: 600 x 2048 at K = 6144 is 80 tiles of 128 rows,
 // which a split in four turns into 320 items = two rounds, 197 us; as 304 tiles of 32 rows split in four it is 1216 items,
 // 137 us.  A combine costs 3 us and its planes' round trip at 5 TB/s.  (128-row tiles: one per compute unit at a time, whole
-// rounds.  32-row tiles: two, and a ragged last round costs about half.)  Constants fitted to 26 shapes of K = 6144 and
-// 4096 x {1 .. 1500} rows, each timed at every split and both heights; the choice is within 6 % of the best of them.
+// rounds.  32-row tiles: two, and a ragged last round costs about half.)  Constants fitted to 26 shapes of K = 6144 and 4096.
+// Over 84 shapes of 1 .. 1500 rows, each timed at every split and both heights (profiles/tile_split_plans.csv), the choice
+// takes 0.85 of the older rule's time in the geometric mean (up to 1.04) and 1.016 of the best plan's in the mean, up to 1.13.
 struct F32Plan {
     int rows, split;
     double us;
