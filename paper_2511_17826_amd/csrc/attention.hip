@@ -950,11 +950,8 @@ static hipError_t launch_of(const AttnArgs &a, AttnParams p, const AttnPlan &pl,
 
 hipError_t launch_attention(const AttnArgs &a, hipStream_t s) {
     if (a.batch <= 0 || a.max_seqlen_q <= 0 || a.total_q <= 0) return hipSuccess;
-    // Few queries per sequence: the other kernel wins or ties from 64 keys (12 us, the host's time of a call) to 10000, at
-    // 1 to 300 sequences (attention_decode.hip).  It loses up to 8 % in one corner, 33 .. 40 sequences of the same length
-    // on 8 key/value heads (a second, nearly empty round of workgroups); with lengths that differ it wins there too.
-    if (g_attention_variant.load() == 0 && attention_decode_supports(a.max_seqlen_q, a.heads_q, a.heads_kv) &&
-        attention_decode_launches(a.batch, a.max_seqlen_q, a.heads_q, a.heads_kv))
+    // Few queries per sequence: the other kernel, at 1 to 300 sequences of up to 10000 keys half the time in the mean.
+    if (g_attention_variant.load() == 0 && attention_decode_takes(a))
         return launch_attention_decode(a, s);
     // Blocks past batch x max_seqlen_q tokens are not launched (the workspace was sized from that bound): with
     // max_seqlen_q below the largest Lq the last queries of the call stay unwritten.

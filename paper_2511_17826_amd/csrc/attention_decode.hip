@@ -494,8 +494,34 @@ static DecodePlan plan_decode(int batch, int max_seqlen_q, int max_seqlen_k, int
 
 // A launch holds fewer than 2^32 threads: from 5.6 million items on, 65535 sequences on 86 key/value heads, these workgroups
 // of 768 are too many where attention_kernel's of 256 are not.
-bool attention_decode_launches(int batch, int max_seqlen_q, int heads_q, int heads_kv) {
+static bool launches(int batch, int max_seqlen_q, int heads_q, int heads_kv) {
     return ((int64_t)batch * heads_kv * plan_decode(batch, max_seqlen_q, 0, heads_q, heads_kv).col_groups + 7) / 8 * 8 * DEC_THREADS < ((int64_t)1 << 32);
+}
+
+// Where attention_kernel is the quicker one although a sequence has few queries: it has two workgroups on a compute unit
+// where this kernel has one, so it is a matter of rounds, and only for groups that it packs into one workgroup (powers of
+// two; the others it reads once per query head).  Times of the two, attention_kernel first, 8800 shapes of 1 .. 10000 keys:
+//   * More than 16 rows on a key/value head: its keys are read here by two workgroups.  64 heads over 8, 4 queries: 33
+//     sequences of 4096 keys 141 / 177 us, 32 of 64 keys 10.0 / 11.8 (16 of them 8 / 6), 128 of 1024 keys 114 / 151.
+//   * One key tile is over before the rounds overlap.  32 heads over 32: 9 sequences of 64 keys 9.9 / 11.5 us, 200 of them
+//     89 / 113; two query heads per key/value head lose from 3 rounds on, four from 7 (a tenth at most).  (4 heads over 4: 128
+//     sequences 13.6 / 11.4, the neighbours lose as well; left to this kernel.)
+//   * Sequences of nearly one length and a second round that is nearly empty.  16 heads over 16: 18 sequences of 2048 keys
+//     take 1.19 times the time here, 22 of them 1.08, 28 1.02; 32 heads over 8: 33 of 4096 keys 1.09 .. 1.12, 40 of them
+//     1.02 .. 1.06, 48 1.01.  With lengths spread over a factor of ten this kernel wins there, by 1.1 to 2.5.
+static bool attention_kernel_is_quicker(const AttnArgs &a) {
+    const int group = a.heads_q / a.heads_kv;
+    if (group & (group - 1)) return false;
+    const int64_t heads = (int64_t)a.batch * a.heads_kv;
+    if (a.max_seqlen_q * group > DEC_COLS) return heads > (a.max_seqlen_k <= 2 * ATT_KV ? 128 : 256);
+    if (a.max_seqlen_k <= ATT_KV) return a.heads_kv >= 8 && heads > 256 * (2 * group - 1);
+    if (a.max_seqlen_k < 1024 || a.max_seqlen_k > ATT_SPLIT * ATT_KV || heads <= 256 || 10 * (int64_t)a.total_k < 9 * (int64_t)a.batch * a.max_seqlen_k) return false;
+    return group <= 2 ? heads <= (a.max_seqlen_k >= 2048 ? 352 : 288) : group == 4 && a.max_seqlen_k >= 3000 && heads <= 320;
+}
+
+bool attention_decode_takes(const AttnArgs &a) {
+    return attention_decode_supports(a.max_seqlen_q, a.heads_q, a.heads_kv) && launches(a.batch, a.max_seqlen_q, a.heads_q, a.heads_kv) &&
+           !attention_kernel_is_quicker(a);
 }
 
 bool attention_decode_supports(int max_seqlen_q, int heads_q, int heads_kv) {

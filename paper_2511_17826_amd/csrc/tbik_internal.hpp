@@ -116,7 +116,7 @@ size_t attention_workspace(int batch, int max_seqlen_q, int max_seqlen_k, int he
 hipError_t launch_attention(const AttnArgs &a, hipStream_t s);
 // Calls whose sequences have few queries (max_seqlen_q x query heads per key/value head <= 32): a kernel of their own.
 bool attention_decode_supports(int max_seqlen_q, int heads_q, int heads_kv);
-bool attention_decode_launches(int batch, int max_seqlen_q, int heads_q, int heads_kv);
+bool attention_decode_takes(const AttnArgs &a);
 size_t attention_decode_workspace(int batch, int max_seqlen_q, int max_seqlen_k, int heads_q, int heads_kv);
 hipError_t launch_attention_decode(const AttnArgs &a, hipStream_t s);
 int set_attention_variant(int v);   // 0 = default, 1 = two workgroups per CU, 2 = two groups of wavefronts taking turns; returns the previous value, -1 if illegal
