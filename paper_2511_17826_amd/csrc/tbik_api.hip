@@ -105,16 +105,16 @@ int internal_split(int M, int N, int K, int ns) {
 // with rounds = work items / 256 compute units, rounded up.  What the two rules above miss is how evenly the items fill the
 // compute units and that a lower tile is cheaper than a padded one: 100 rows of 4096 x 4096 in 8-bit operands took 128-row
 // tiles split in eight, 18.9 us, and take 12.4 us as 32-row tiles split in two; 400 rows at K = 12288 in bf16 took 224 tiles
-// of 64 rows, 82 us, and take 61 us as 128-row tiles split in two.  The constants were fitted to times of K = 4096, 12288 and
-// 25600; they are not physical rates one by one (the same planes move at 12 TB/s in one row and at 1.2 in another), and the
-// time they give is off by -36 .. +36 % for 16-bit operands, -47 .. +25 % for the others: they rank plans, no more.  Checked
-// over 227 (16-bit) and 4 x 99 (low-bit) shapes of the tests' layers, K = 5120 and 14336 among them, 1 .. 4096 rows, each timed
-// at every height and split (profiles/tile_split_plans.csv): the chosen plan, cuts included, takes 0.938 (16-bit), 0.894
-// (8-bit), 0.924 (MXFP8), 0.899 (MXFP4) and 0.941 (MXFP6) of the rules' time in the geometric mean and up to 1.06, 1.04, 1.01,
-// 1.03 and 1.02 of it (two runs of one plan differ by up to 4 %), and 0.992 .. 0.998 of the best plan in one piece in the
-// mean, up to 1.18, 1.09, 1.06, 1.12 and 1.20.  The rules' choice stays where the model promises less than the margin: with
-// 4 % for 16-bit operands too it split 21 of the 227 that the rules computed faster by more than 2 % (768 rows at K = 12288
-// 96 against 90 us, 768 rows of 4096 x 6144 71 against 65, and 56 now, cut behind 640); with 8 % three are left.
+// of 64 rows, 82 us, and take 61 us as 128-row tiles split in two.  The constants were fitted to measured times; they are not
+// physical rates one by one (the same planes move at 12 TB/s in one row and at 1.2 in another), and the time they give is
+// off by -41 .. +33 % for 16-bit operands, -55 .. +18 % for the others: they rank plans, no more.  Checked over 227 (16-bit)
+// and 4 x 99 (low-bit) shapes of the tests' layers, 1 .. 4096 rows, each timed at every height and split, with weights from
+// HBM and with weights from the memory-side cache (profiles/tile_split_plans.csv).  The chosen plan, cuts included, takes of
+// the rules' time, from HBM / from the cache in the geometric mean: 0.940 / 0.943 (16-bit), 0.927 / 0.884 (8-bit), 0.964 / 0.922
+// (MXFP8), 0.924 / 0.890 (MXFP4), 0.949 / 0.936 (MXFP6), from HBM up to 1.08 (two runs of one plan differ by up to 5 %); of
+// the best plan's in one piece 0.996 .. 1.008 from HBM, up to 1.29.  The rules' choice stays where the model promises less than
+// the margin.  A tile of 64 rows that the model took too cheap was split where the rule is quicker by a tenth (768 rows of
+// 4096 x 6144 from HBM 79 against 71 us, 64 now, cut behind 640).
 enum Operands { OPERANDS_16BIT, OPERANDS_FP8, OPERANDS_MXFP8, OPERANDS_MXFP4, OPERANDS_MXFP6 };
 struct TilePlan {
     int rows, split;
@@ -129,11 +129,11 @@ struct TileModel {
     double margin;                      // the rules' choice stays where the model promises less than this
 };
 constexpr TileModel kTileModels[] = {
-    {64, 2.0, {0.005, 0.21, 0.525}, 5.9, 38.5, 3.95, 12.0, 0.0, 1.08},
+    {64, 2.0, {0.005, 0.25, 0.525}, 5.9, 38.5, 3.95, 12.0, 0.0, 1.04},
     {128, 1.0, {0.01, 0.24, 0.33}, 3.1, 51.0, 2.7, 1.2, 0.0, 1.04},
-    {128, 1.0, {0.0, 0.185, 0.375}, 3.6, 42.0, 4.8, 2.5, 4.0, 1.04},
-    {256, 0.5, {0.31, 0.335, 0.574}, 4.1, 31.4, 2.64, 2.7, 4.0, 1.04},
-    {128, 0.75, {0.0, 0.0, 0.61}, 3.6, 36.0, 4.8, 2.5, 4.0, 1.04},       // one height; MXFP8's with its stage
+    {128, 1.0, {0.0, 0.185, 0.356}, 3.6, 42.0, 4.8, 2.5, 4.0, 1.08},
+    {256, 0.5, {0.325, 0.335, 0.574}, 4.1, 31.4, 2.64, 2.7, 4.0, 1.04},
+    {128, 0.75, {0.0, 0.0, 0.61}, 3.6, 36.0, 3.84, 2.5, 4.0, 1.0},       // one height; MXFP8's with its stage
 };
 
 // Bytes of the fp32 planes of a K split.

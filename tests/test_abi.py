@@ -64,8 +64,7 @@ def test_workspace_sizes_of_one_operand_width(L):
     # 1024 rows in one piece and the rest of them split: planes of the rest alone
     assert L.tbik_gemm_16bit_workspace_bytes(1100, 4096, 12288, 256, 3) == planes(8, 76, 4096)
     assert L.tbik_gemm_16bit_workspace_bytes(1152, 4096, 4096, 256, 1) == planes(4, 128, 4096)
-    # batches that whole tiles compute no more slowly than split ones, and one that is cut behind 640 rows instead of split
-    assert L.tbik_gemm_16bit_workspace_bytes(768, 4096, 12288, 256, 3) == 0 == L.tbik_gemm_16bit_workspace_bytes(321, 5120, 5120, 128, 5)
+    # a cut behind 640 rows instead of the whole as 64-row tiles split in two
     assert L.tbik_gemm_16bit_workspace_bytes(768, 6144, 4096, 256, 1) == planes(2, 128, 6144)
     for M in (0, 1, 77, 321, 600, 1100, 1500, 4096):
         for k, n, leaf, g in ((4096, 4096, 256, 1), (12288, 4096, 256, 3), (25600, 5120, 128, 25), (6144, 2048, 128, 3)):
