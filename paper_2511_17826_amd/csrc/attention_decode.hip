@@ -46,7 +46,9 @@ constexpr int DEC_LDS_P = DEC_LDS_V + DEC_PROD_WAVES * 2 * DEC_V_TILE;
 constexpr int DEC_LDS_PMAX = DEC_LDS_P + 2 * DEC_P_ROUND;
 constexpr int DEC_LDS_HSUM = DEC_LDS_PMAX + 2 * DEC_SCORE_WAVES * DEC_COLS * 4;
 constexpr int DEC_LDS_PSUM = DEC_LDS_HSUM + 2 * DEC_ROUND * 32 * 4;
-constexpr int DEC_LDS = DEC_LDS_PSUM + 2 * DEC_ROUND * DEC_COLS * 4;
+static_assert(DEC_V_TILE == DEC_ROUND * 1024, "the first four wavefronts fill a tile");
+constexpr int DEC_LDS_ZERO = DEC_LDS_PSUM + 2 * DEC_ROUND * DEC_COLS * 4;    // a tile of values that are -0
+constexpr int DEC_LDS = DEC_LDS_ZERO + DEC_V_TILE;
 static_assert(DEC_LDS <= 160 * 1024, "LDS of a compute unit");
 // A split's state: chunk c of lane t at [c * 64 + t] of 16 bytes; chunk 0 is (m, l, -, -), chunk 1 + 2 db + bl holds the
 // lane's four channels of o in the bl-th 16 of channel block db.
@@ -195,6 +197,9 @@ __device__ __forceinline__ void decode_queries(const DecodeParams &p, const Deco
         const unsigned char *const k_rd = k_lds + l16 * 256;
         unsigned char *const p_wr = smem + DEC_LDS_P + (qt * 2 + kb) * 1024 + lane * 16;
 
+        if (wave < DEC_ROUND)                                     // (+0 x -0 = -0, and x + -0 is x for either zero; past barrier A of round 0)
+            *reinterpret_cast<att_u32x4 *>(smem + DEC_LDS_ZERO + wave * 1024 + lane * 16) = att_u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
+
         float m = -INFINITY;
         auto round = [&](att_u32x4 (&kr)[8], int r) __attribute__((always_inline)) {
             const int t = t_begin + r * DEC_ROUND + qt, b = r & 1;
@@ -304,9 +309,9 @@ __device__ __forceinline__ void decode_queries(const DecodeParams &p, const Deco
     // transposing read's 16 lanes take 4 keys x 16 channels, and the two groups that read keys 0 .. 3 and 4 .. 7 then hit
     // different banks.
     const int g = g4 & 1;
-    unsigned char *const v_lds = smem + DEC_LDS_V + (wave - DEC_SCORE_WAVES) * 2 * DEC_V_TILE;
-    unsigned char *const v_wr = v_lds + sub * 64 + ((pos ^ (2 * g)) << 4);           // (sub >> 2) & 1 == g4 & 1
-    const unsigned char *const v_rd = v_lds + (16 * (g4 >> 1) + 4 * g + (l16 >> 2)) * 64 + (l16 & 3) * 8;
+    unsigned char *const v_wr = smem + DEC_LDS_V + (wave - DEC_SCORE_WAVES) * 2 * DEC_V_TILE + sub * 64 + ((pos ^ (2 * g)) << 4);           // (sub >> 2) & 1 == g4 & 1
+    const unsigned char *const v_rd = smem + (16 * (g4 >> 1) + 4 * g + (l16 >> 2)) * 64 + (l16 & 3) * 8;       // + the tile's place
+    const int v_at = DEC_LDS_V + (wave - DEC_SCORE_WAVES) * 2 * DEC_V_TILE;
     const unsigned char *const p_rd = smem + DEC_LDS_P + lane * 16;
 
     att_u32x4 vr[DEC_ROUND][4];
@@ -318,7 +323,6 @@ __device__ __forceinline__ void decode_queries(const DecodeParams &p, const Deco
     float m_acc = -INFINITY, l_acc = 0.0f;
     float m = -INFINITY, l = 0.0f, alpha[DEC_ROUND];
 
-    const att_u32x4 NEGATIVE_ZEROS = {0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};      // +0 x -0 = -0, and x + -0 is x for either zero as well
     // Tiles q and q + 1 of round r: V through LDS, then o = o alpha + V^T P^T tile after tile.
     auto two_tiles = [&](auto q_tag, int r) __attribute__((always_inline)) {
         constexpr int Q0 = decltype(q_tag)::value;
@@ -326,16 +330,13 @@ __device__ __forceinline__ void decode_queries(const DecodeParams &p, const Deco
         for (int q = Q0; q < Q0 + 2; ++q) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) *reinterpret_cast<att_u32x4 *>(v_wr + (q & 1) * DEC_V_TILE + i * 1024) = vr[q][i];
-            // A tile past the end (the last round may have some) leaves o as it is: its weights are 0, its values must be finite.
-            // (A branch with nothing but stores: choosing in registers cost 1.5 of attention_decode's 28 us.)
-            if (t_begin + r * DEC_ROUND + q >= t_end) {           // uniform
-#pragma unroll
-                for (int i = 0; i < 4; ++i) *reinterpret_cast<att_u32x4 *>(v_wr + (q & 1) * DEC_V_TILE + i * 1024) = NEGATIVE_ZEROS;
-            }
             load_v(vr[q], t_begin + (r + 1) * DEC_ROUND + q);
         }
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
+            // A tile past the end (the last round may have some) leaves o as it is: its weights are 0, its values must be finite.
+            // (Values replaced in registers, or behind a branch in LDS, cost 5 and 3 % where most rounds are the last.)
+            const unsigned char *const rd = v_rd + (t_begin + r * DEC_ROUND + Q0 + u < t_end ? v_at + u * DEC_V_TILE : DEC_LDS_ZERO);   // uniform
             bf16x8 pb[2];
             union { att_v4i16 h2[2]; bf16x8 v; } vf[2][2];
 #pragma unroll
@@ -346,7 +347,7 @@ __device__ __forceinline__ void decode_queries(const DecodeParams &p, const Deco
 #pragma unroll
                     for (int hh = 0; hh < 2; ++hh)
                         vf[kb][bl].h2[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                            (__attribute__((address_space(3))) att_v4i16 *)(v_rd + u * DEC_V_TILE + (32 * kb + 8 * hh) * 64 + ((bl ^ g) << 5)));
+                            (__attribute__((address_space(3))) att_v4i16 *)(rd + (32 * kb + 8 * hh) * 64 + ((bl ^ g) << 5)));
             }
 #pragma unroll
             for (int bl = 0; bl < 2; ++bl)
