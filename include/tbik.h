@@ -51,7 +51,7 @@ typedef enum {
     TBIK_ERR_SHARDS = 3,      /* P < 1, P not a power of two, P > n_s, or P > TBIK_MAX_SHARDS           */
     TBIK_ERR_DTYPE = 4,       /* unknown tbik_dtype / tbik_rowop, or a combination that is not offered */
     TBIK_ERR_ALIGN = 5,       /* a pointer or leading dimension violates the stated alignment          */
-    TBIK_ERR_WORKSPACE = 6,   /* workspace missing or smaller than the matching *_workspace_bytes()    */
+    TBIK_ERR_WORKSPACE = 6,   /* workspace missing or too small; never if it has *_workspace_bytes()    */
     TBIK_ERR_UNSUPPORTED = 7, /* legal request that this build does not implement                      */
     TBIK_ERR_HIP = 8          /* a HIP runtime call failed; see tbik_last_hip_error()                  */
 } tbik_status;
@@ -78,8 +78,10 @@ typedef enum { TBIK_SUM = 0, TBIK_MAX = 1, TBIK_LOGSOFTMAX = 2 } tbik_rowop;
  *   X   device, bf16, [M, ldx], ldx >= K     W   device, bf16, [K, ldw], ldw >= N
  *   Y   device, y_dtype, [M, ldy], ldy >= N
  *   Alignment: X, W 16 bytes, ldx and ldw multiples of 8; Y 4 bytes (TBIK_F32) / 2 bytes (TBIK_BF16).
- *   workspace  device scratch of at least tbik_gemm_workspace_bytes(M,N,K,leaf,k_first) bytes,
- *              256-byte aligned; may be NULL when that size is 0.  Contents are undefined afterwards.
+ *   workspace  device scratch of tbik_gemm_workspace_bytes(M,N,K,leaf,k_first) bytes (or of
+ *              tbik_gemm_16bit_workspace_bytes(...) for 16-bit operands), 256-byte aligned; may be NULL
+ *              when that size is 0.  That is room for the quickest way to cut the work; a call may also take
+ *              less and cut it in a way that fits (same bits), or refuse.  Contents are undefined afterwards.
  * Errors: NULL, SHAPE, DTYPE, ALIGN, WORKSPACE, HIP.
  */
 int tbik_gemm(const void *X, int64_t ldx, const void *W, int64_t ldw, void *Y, int64_t ldy,
