@@ -131,3 +131,15 @@ def test_more_workgroups_than_a_launch_of_this_kernel_holds():
     lens_q, lens_k = [0] * 65532 + [1, 1, 1], [0] * 65532 + [100, 64, 300]
     a, b = both(128, 128, lens_q, lens_k)
     assert torch.equal(a, b) and not (b == torch.tensor(7.0, dtype=torch.bfloat16).view(torch.int16)).all(dim=2).any()
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("Hq,Hkv,q,batches,keys", [(64, 8, 4, (16, 17), 100), (64, 8, 4, (32, 33), 300), (32, 32, 1, (8, 9), 64), (16, 8, 1, (96, 97), 40),
+                                                   (16, 16, 1, (16, 17, 18, 19), 1030), (16, 16, 2, (22, 23), 2100), (32, 8, 1, (32, 33, 40, 41), 3001)])
+def test_both_sides_of_the_lines_between_the_two_kernels(Hq, Hkv, q, batches, keys, causal):
+    """Sizes next to each line of the rule that gives a call of few queries to one kernel or the other: same bits on both sides, and
+    for sequences of one length as for ragged ones, which the rule tells apart."""
+    for B in batches:
+        for lens_k in ([keys] * B, [keys - (i * 37) % (keys - 8) for i in range(B)]):
+            a, b = both(Hq, Hkv, [q] * B, lens_k, causal, seed=B)
+            assert torch.equal(a, b), (B, lens_k[-1])
