@@ -30,13 +30,13 @@ int check_tree(int M, int N, int K, int leaf, int k_first, int P, int *superleaf
         while (q % 2 == 0) q /= 2;
         k_first = (int)q;
     }
-    const int64_t sl = (int64_t)leaf * k_first;
-    if (sl > K || K % sl != 0 || sl % 16 != 0) return TBIK_ERR_SHAPE;
-    const int64_t n = K / sl;
-    if (!is_pow2(n)) return TBIK_ERR_SHAPE;
+    const int64_t sl64 = (int64_t)leaf * k_first;
+    if (sl64 > K || sl64 % 16 != 0) return TBIK_ERR_SHAPE;
+    const int sl = (int)sl64, n = K / sl;
+    if (n * sl != K || !is_pow2(n)) return TBIK_ERR_SHAPE;
     if (P < 1 || !is_pow2(P) || P > n || P > TBIK_MAX_SHARDS) return TBIK_ERR_SHARDS;
-    *superleaf = (int)sl;
-    *ns = (int)n;
+    *superleaf = sl;
+    *ns = n;
     return TBIK_OK;
 }
 
@@ -181,16 +181,17 @@ int mxfp6_split(int M, int N, int ns) {
 struct TimedPlan {
     TilePlan plan;
     double us;
+    int rule_split;                     // the older rule's
 };
 // only_split > 0: the split is the caller's (shard partials), only the height is chosen.  room: bytes for planes.
 TimedPlan tile_plan(Operands kind, int M, int N, int K, int ns, int only_split, size_t room) {
     const bool one_height = kind == OPERANDS_MXFP6;
     const TilePlan rule{one_height ? 128 : forced_rows(tile_rows(M, N)),
                         only_split > 0 ? only_split : one_height ? mxfp6_split(M, N, ns) : internal_split(M, N, K, ns)};
-    if (g_forced_variant.load() != VARIANT_AUTO || M <= 0 || N <= 0) return {rule, 0.0};
+    if (g_forced_variant.load() != VARIANT_AUTO || M <= 0 || N <= 0) return {rule, 0.0, rule.split};
     const PlanTimes times(kTileModels[kind], M, N, K);
     const double rule_us = times.us(rule);
-    TimedPlan best{rule, rule_us};
+    TimedPlan best{rule, rule_us, rule.split};
     double best_us = only_split > 0 || split_planes_bytes(M, N, rule.split) <= room ? rule_us / times.m.margin : 1e30;
     int first_split = only_split > 0 ? only_split : 1;
     while (only_split <= 0 && ns > 16 * (int64_t)first_split) first_split *= 2;         // a tile walks at most 16 superleaves
@@ -205,7 +206,8 @@ TimedPlan tile_plan(Operands kind, int M, int N, int K, int ns, int only_split, 
         for (int split = first_split; split <= last_split; split *= 2, per_split *= 0.5) {
             if (only_split <= 0 && split_planes_bytes(M, N, split) > room) break;
             const double us = times.us(row_tiles * times.cols, step, split, per_split);
-            if (us < best_us) { best = {{rows, split}, us}; best_us = us; }
+            if (us < best_us) { best.plan = {rows, split}; best.us = best_us = us; }
+            if ((row_tiles * times.cols * split & 255) == 0) break;       // full rounds: a further split only adds to each
         }
     }
     return best;
@@ -218,11 +220,11 @@ constexpr double kPieceUs = 2.0;        // what a launch behind another costs
 struct BatchPlan {
     int last_rows;
     TilePlan first, last;               // of the rows before the last ones, of the last ones
-    size_t planes;                      // bytes that the plans use
+    size_t planes, rule_planes;         // bytes that the plans use, that the older rule's split would
 };
 BatchPlan batch_plan(Operands kind, int M, int N, int K, int ns, size_t room) {
     const TimedPlan whole = tile_plan(kind, M, N, K, ns, 0, room);
-    BatchPlan plan{0, whole.plan, whole.plan, split_planes_bytes(M, N, whole.plan.split)};
+    BatchPlan plan{0, whole.plan, whole.plan, split_planes_bytes(M, N, whole.plan.split), split_planes_bytes(M, N, whole.rule_split)};
     if (M <= 0 || N <= 0 || ns > 16 || g_forced_variant.load() != VARIANT_AUTO) return plan;
     const int64_t cols = ((int64_t)N + 127) / 128;
     const int per_round = cols > 256 ? 0 : 256 / (int)cols;                      // row tiles of 128 in a round
@@ -237,15 +239,33 @@ BatchPlan batch_plan(Operands kind, int M, int N, int K, int ns, size_t room) {
     plan.last = last.plan;
     return plan;
 }
+// The plan of a shape with room for all its planes.  A call asks twice, for the size and for the plan, and a program's layers ask
+// for the same few shapes over and over, so a thread remembers what it worked out last (a pure function of the key).  Searching
+// each time takes 30 ns in a loop and far more between two launches, where its code and tables are cold: one token 13.0 us, 11.7 so.
+const BatchPlan &roomy_plan(Operands kind, int M, int N, int K, int ns) {
+    struct Entry {
+        int kind, M, N, K, ns;          // ns == 0: empty
+        BatchPlan plan;
+    };
+    constexpr unsigned kEntries = 64;
+    static thread_local Entry entries[kEntries];
+    Entry &e = entries[((unsigned)M * 7u + ((unsigned)N >> 7) * 13u + ((unsigned)K >> 8) * 29u + (unsigned)ns + (unsigned)kind * 17u) % kEntries];
+    if (e.M != M || e.N != N || e.K != K || e.ns != ns || e.kind != (int)kind || g_forced_variant.load() != VARIANT_AUTO) {
+        e = {(int)kind, M, N, K, ns, batch_plan(kind, M, N, K, ns, SIZE_MAX)};
+        if (g_forced_variant.load() != VARIANT_AUTO) e.ns = 0;     // not remembered
+    }
+    return e.plan;
+}
 // Bytes of planes a call can make use of, the older rule's included.
 size_t plan_planes_bytes(Operands kind, int M, int N, int K, int ns) {
-    return std::max(split_planes_bytes(M, N, kind == OPERANDS_MXFP6 ? mxfp6_split(M, N, ns) : internal_split(M, N, K, ns)),
-                    batch_plan(kind, M, N, K, ns, SIZE_MAX).planes);
+    const BatchPlan &plan = roomy_plan(kind, M, N, K, ns);
+    return std::max(plan.planes, plan.rule_planes);
 }
 // Calls piece(first row, rows, plan) for the one or two pieces of a batch.
 template <class Piece>
 hipError_t in_pieces(Operands kind, int M, int N, int K, int ns, size_t room, Piece piece) {
-    const BatchPlan plan = batch_plan(kind, M, N, K, ns, room);
+    BatchPlan plan = roomy_plan(kind, M, N, K, ns);
+    if (plan.planes > room) plan = batch_plan(kind, M, N, K, ns, room);
     hipError_t e = piece(0, M - plan.last_rows, plan.first);
     return (e == hipSuccess && plan.last_rows > 0) ? piece(M - plan.last_rows, plan.last_rows, plan.last) : e;
 }

@@ -248,3 +248,26 @@ def test_fp32_gemm_entry_points_validate_like_the_others(L):
     rf = L.tbik_gemm_reference_f32
     assert rf(GOOD, 512, GOOD, 256, GOOD, GOOD, 256, 4, 256, 512, 64, 1, 2, None) == 3         # Y only with P == 1
     assert rf(GOOD, 512, GOOD, 256, None, None, 256, 4, 256, 512, 64, 1, 1, None) == 1
+
+
+def test_workspace_sizes_do_not_depend_on_what_was_asked_before(L):
+    """Plans are remembered by thread and shape: more shapes than are remembered, in two orders, in other threads and with a forced
+    kernel in between."""
+    import random
+    import threading
+    shapes = [(fmt, M, N, K, 256, g) for fmt in ("_16bit", "_fp8", "_mxfp4", "_mxfp8", "_mxfp6") for M in (1, 33, 77, 321, 700, 1100, 1152)
+              for N, K, g in ((4096, 4096, 1), (4096, 12288, 3), (6144, 4096, 1))]
+    ask = lambda s: getattr(L, "tbik_gemm%s_workspace_bytes" % s[0])(*s[1:])
+    first = {s: ask(s) for s in shapes}
+    again = shapes * 3
+    random.Random(1).shuffle(again)
+    assert all(ask(s) == first[s] for s in again)
+    bad = []
+    threads = [threading.Thread(target=lambda: bad.extend(s for s in again if ask(s) != first[s])) for _ in range(4)]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
+    assert not bad
+    L.tbik_set_gemm_variant(2)
+    [ask(s) for s in shapes]
+    L.tbik_set_gemm_variant(0)
+    assert all(ask(s) == first[s] for s in again)
