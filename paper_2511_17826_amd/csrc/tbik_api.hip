@@ -322,6 +322,9 @@ int pick_variant(const GemmArgs &a, int rows) {      // rows: tile height for 16
     return VARIANT_REFERENCE;
 }
 
+// A small batch of a low-bit format goes to the kernel that needs one launch, unless a variant is forced.
+bool takes_slices(const GemmArgs &a, const Mxfp4Scales *sc) { return g_forced_variant.load() == VARIANT_AUTO && gemm_slice_takes(a, sc); }
+
 // 16-bit output type that goes with an operand format.
 inline bool legal_y_dtype(int y_dtype, int x_dtype) { return y_dtype == TBIK_F32 || y_dtype == x_dtype; }
 
@@ -544,6 +547,7 @@ int tbik_gemm_fp8(const void *X, int64_t ldx, const void *Wt, int64_t ldwt, void
         void *y = static_cast<char *>(Y) + (int64_t)m0 * ldy * (y_dtype == TBIK_F32 ? 4 : 2);
         GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
                    (int)y_dtype, m, N, K, sl, ns, 1, (int)x_dtype, 0};
+        if (takes_slices(a, nullptr)) return launch_gemm_slice(a, nullptr, s);
         GemmArgs probe = a;
         probe.P = plan.split;
         if (g_forced_variant.load() == VARIANT_REFERENCE || !gemm_fp8_tiled_supports(probe)) return launch_gemm_fp8_reference(a, s);
@@ -638,6 +642,7 @@ int tbik_gemm_mxfp4(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
         GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
                    (int)y_dtype, m, N, K, sl, ns, 1, TBIK_MXFP4, 0};
         const Mxfp4Scales sc{static_cast<const uint8_t *>(Xs) + (int64_t)m0 * ldxs, ldxs, (const uint8_t *)Ws, ldws};
+        if (takes_slices(a, &sc)) return launch_gemm_slice(a, &sc, s);
         GemmArgs probe = a;
         probe.P = plan.split;
         if (g_forced_variant.load() == VARIANT_REFERENCE || !gemm_mxfp4_tiled_supports(probe, sc)) return launch_gemm_mxfp4_reference(a, sc, s);
@@ -732,6 +737,7 @@ int tbik_gemm_mxfp8(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
         GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
                    (int)y_dtype, m, N, K, sl, ns, 1, (int)x_dtype, 0};
         const Mxfp4Scales sc{static_cast<const uint8_t *>(Xs) + (int64_t)m0 * ldxs, ldxs, (const uint8_t *)Ws, ldws};
+        if (takes_slices(a, &sc)) return launch_gemm_slice(a, &sc, s);
         GemmArgs probe = a;
         probe.P = plan.split;
         if (g_forced_variant.load() == VARIANT_REFERENCE || !gemm_mxfp8_tiled_supports(probe, sc)) return launch_gemm_mxfp8_reference(a, sc, s);
@@ -829,6 +835,7 @@ int tbik_gemm_mxfp6(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
         GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
                    (int)y_dtype, m, N, K, sl, ns, 1, (int)x_dtype, 0};
         const Mxfp4Scales sc{static_cast<const uint8_t *>(Xs) + (int64_t)m0 * ldxs, ldxs, (const uint8_t *)Ws, ldws};
+        if (takes_slices(a, &sc)) return launch_gemm_slice(a, &sc, s);
         GemmArgs probe = a;
         probe.P = plan.split;
         if (g_forced_variant.load() == VARIANT_REFERENCE || !gemm_mxfp6_tiled_supports(probe, sc)) return launch_gemm_mxfp6_reference(a, sc, s);

@@ -85,6 +85,11 @@ hipError_t launch_gemm_mxfp6_tiled(const GemmArgs &a, const Mxfp4Scales &sc, voi
 bool gemm_mxfp6_tiled_supports(const GemmArgs &a, const Mxfp4Scales &sc);
 size_t mxfp6_retiled_scales_bytes(int M, int N, int K);
 
+// The low-bit formats' batches of up to 32 rows in one launch without a workspace (sc: the scales of a microscaling format, or
+// nullptr); P == 1, the rounded output as the tiled kernels give it.
+bool gemm_slice_takes(const GemmArgs &a, const Mxfp4Scales *sc);
+hipError_t launch_gemm_slice(const GemmArgs &a, const Mxfp4Scales *sc, hipStream_t s);
+
 // Y = T(partials[0..P)) elementwise + one rounding.
 hipError_t launch_tree_combine(const float *partials, int P, void *Y, int64_t ldy, int y_dtype, int M, int N,
                                hipStream_t s);
