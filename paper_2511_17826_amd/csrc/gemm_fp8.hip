@@ -25,6 +25,7 @@
 #include "tbik_device.hpp"
 #include "mx_scales.hpp"
 #include "tbik_internal.hpp"
+#include "tile_store.hpp"
 #include "tree_walk.hpp"
 
 namespace tbik {
@@ -481,6 +482,21 @@ void gemm_fp8_tiled_kernel(const Fp8Params p) {
                 }
             }
             stores_in_flight = to_bf16 ? STORES_BF16 : STORES_F32;
+        } else if (n0 + BN <= p.N && p.vector_stores) {      // ragged last row tile: the same through the patch, rows clamped
+            const int last_slot = cur == 0 ? RING8 - 1 : cur - 1;
+            float *patch = reinterpret_cast<float *>(smem + last_slot * STAGE8 + wave * REGION8);
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            const bool to_bf16 = (part == nullptr) && p.y_bf16;
+            const int wm_u = wave_u / WN, wn_u = wave_u % WN;
+            const int row0 = m0 + wm_u * MT * 32, last = p.M - 1 - row0;      // the wavefront's rows, the last one that exists
+            if (to_bf16) {
+                store_ragged_16bit<false>(acc, patch, reinterpret_cast<uint16_t *>(p.Y) + (int64_t)row0 * p.ldy + n0 + wn_u * WCOLS, p.ldy, last, lane);
+            } else {
+                const int64_t ld = part ? p.N : p.ldy;
+                float *dst = (part ? part : reinterpret_cast<float *>(p.Y)) + (int64_t)row0 * ld + n0 + wn_u * WCOLS;
+                store_ragged_f32(acc, patch, dst, ld, last, lane, p.stream_stores);
+            }
+            stores_in_flight = last < (MT - 1) * 32 ? -1 : to_bf16 ? STORES_BF16 : STORES_F32;
         } else {
 #pragma unroll
             for (int a = 0; a < MT; ++a) {

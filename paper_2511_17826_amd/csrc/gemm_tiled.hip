@@ -21,6 +21,7 @@
 
 #include "tbik_device.hpp"
 #include "tbik_internal.hpp"
+#include "tile_store.hpp"
 #include "tree_walk.hpp"
 
 namespace tbik {
@@ -422,7 +423,38 @@ void gemm_tiled_kernel(const TiledParams p) {
                 }
             }
             stores_in_flight = (NT == 2 && p.swiglu) ? STORES_ACT : to_bf16 ? STORES_BF16 : STORES_F32;
-        } else if (NT == 2 && p.swiglu) {                    // ragged last row tile
+        } else if (n0 + BN <= p.N && p.vector_stores) {      // ragged last row tile: the same through the patch, rows clamped
+            const int last_slot = cur == 0 ? RING - 1 : cur - 1;
+            float *patch = reinterpret_cast<float *>(smem + last_slot * STAGE_BYTES + wave * REGION_BYTES);
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            const bool to_bf16 = (part == nullptr) && p.y_bf16;
+            const int wm_u = wave_u / WN, wn_u = wave_u % WN;
+            const int row0 = m0 + wm_u * MT * 32, last = p.M - 1 - row0;      // the wavefront's rows, the last one that exists
+            if (NT == 2 && p.swiglu) {
+#pragma unroll
+                for (int a = 0; a < MT; ++a) {
+                    if (last < 32 * a) continue;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        patch[(8 * (r >> 2) + 4 * lg + (r & 3)) * 32 + li] =
+                            silu_mul(through_16_bits<F16>(acc.t[a][0][r]), through_16_bits<F16>(acc.t[a][NT - 1][r]));
+                    uint16_t *base = reinterpret_cast<uint16_t *>(p.Y) + (int64_t)(row0 + a * 32) * p.ldy + n0 / 2 + wn_u * 32;
+#pragma unroll
+                    for (int it = 0; it < 2; ++it) {
+                        const int row = min((lane >> 2) + it * 16, last - 32 * a);
+                        *reinterpret_cast<tile_u32x4 *>(reinterpret_cast<char *>(base) + (unsigned)(row * (int)p.ldy + (lane & 3) * 8) * 2u) =
+                            pack_8<F16>(patch + row * 32 + (lane & 3) * 8);
+                    }
+                }
+            } else if (to_bf16) {
+                store_ragged_16bit<F16>(acc, patch, reinterpret_cast<uint16_t *>(p.Y) + (int64_t)row0 * p.ldy + n0 + wn_u * WCOLS, p.ldy, last, lane);
+            } else {
+                const int64_t ld = part ? p.N : p.ldy;
+                float *dst = (part ? part : reinterpret_cast<float *>(p.Y)) + (int64_t)row0 * ld + n0 + wn_u * WCOLS;
+                store_ragged_f32(acc, patch, dst, ld, last, lane, p.stream_stores);
+            }
+            stores_in_flight = last < (MT - 1) * 32 ? -1 : (NT == 2 && p.swiglu) ? STORES_ACT : to_bf16 ? STORES_BF16 : STORES_F32;
+        } else if (NT == 2 && p.swiglu) {                    // rows that cannot be stored 16 bytes at a time
             const int col = n0 / 2 + wn * 32 + li;
 #pragma unroll
             for (int a = 0; a < MT; ++a) {
