@@ -144,7 +144,7 @@ struct Fp8Params {
     const uint8_t *Wt;
     const uint8_t *Xs, *Ws;     // MX: E8M0 scales [M, ldxs], [N, ldws], one per 32 k -- or, scales_packed, the re-tiled copies
     int64_t ldxs, ldws;
-    int scales_packed;          // the scales were re-tiled by mx_scales_retile_kernel to the tile height of this launch
+    int scales_packed;          // the scales were re-tiled by mx_scales_retile_kernel (blocks of 128 rows)
     int stages_total;           // K / 128
     float *partials;
     void *Y;
@@ -220,8 +220,8 @@ void gemm_fp8_tiled_kernel(const Fp8Params p) {
             const bool of_x = wave_is_x;               // uniform
             if (p.scales_packed) {                     // a stage's scale bytes of a row block are consecutive: two cache lines per load
                 const int64_t stage0 = kbase / BK8;
-                const char *xs = reinterpret_cast<const char *>(p.Xs) + ((int64_t)(m0 / BM) * p.stages_total + stage0) * (BM * 4);
-                const char *ws = reinterpret_cast<const char *>(p.Ws) + ((int64_t)(n0 / BN) * p.stages_total + stage0) * (BN * 4);
+                const char *xs = reinterpret_cast<const char *>(p.Xs) + ((int64_t)(m0 / 128) * p.stages_total + stage0) * 512 + m0 % 128 * 4;
+                const char *ws = reinterpret_cast<const char *>(p.Ws) + ((int64_t)(n0 / BN) * p.stages_total + stage0) * 512;
                 s_ptr = uniform_pointer(of_x ? xs : ws);
                 soff = (unsigned)(4 * (of_x ? rs % BM : rs));
             } else {                                   // straight from the caller's [rows, K / 32] arrays: a cache line per lane
@@ -237,7 +237,7 @@ void gemm_fp8_tiled_kernel(const Fp8Params p) {
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     const unsigned m0_in_stage = smem_lds + wave_u * REGION8 + A_LOADS8 * 1024;
     const unsigned m0_scales = smem_lds + SCALES_AT + wave_u * 256;         // X rows 0 .. 127, then Wt rows 0 .. 127, four bytes each
-    const int s_step = !(MX && p.scales_packed) ? BK8 / 32 : (wave_u < 2 ? BM * 4 : BN * 4);      // scale bytes per stage
+    const int s_step = !(MX && p.scales_packed) ? BK8 / 32 : 512;      // scale bytes per stage
     auto issue_part = [&](int slot, auto part_c) __attribute__((always_inline)) {
         constexpr int PART = decltype(part_c)::value;
         if (PART == 0 && __builtin_expect(issue_stage == stages_per_item, 0)) {
@@ -653,18 +653,15 @@ bool gemm_mxfp8_tiled_supports(const GemmArgs &a, const Mxfp4Scales &sc) {
 
 size_t mxfp8_retiled_scales_bytes(int M, int N, int K) { return mx_retiled_scales_bytes<1>(M, N, K / BK8); }
 
-// packed_ws: nullptr, or mxfp8_retiled_scales_bytes(M, N, K) bytes (4-byte aligned) into which the scales are re-tiled
-// first (one short launch), after which every scale load of the GEMM touches two cache lines instead of 64.
-hipError_t launch_gemm_mxfp8_tiled(const GemmArgs &a, const Mxfp4Scales &sc, int rows, void *packed_ws, hipStream_t s) {
+hipError_t launch_mxfp8_retile(const Mxfp4Scales &raw, int M, int N, int K, void *out, Mxfp4Scales *packed, hipStream_t s) {
+    return launch_mx_scales_retile<1>(raw, M, N, K / BK8, out, packed, s);
+}
+
+// Re-tiled scales make every scale load touch two cache lines instead of 64.
+hipError_t launch_gemm_mxfp8_tiled(const GemmArgs &a, const Mxfp4Scales &sc, int rows, hipStream_t s) {
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
     if (!gemm_mxfp8_tiled_supports(a, sc) || (rows != 32 && rows != 64 && rows != 128)) return hipErrorInvalidValue;
-    Mxfp4Scales use = sc;
-    if (packed_ws) {
-        hipError_t e = launch_mx_scales_retile<1>(sc.Xs, sc.ldxs, a.M, rows, sc.Ws, sc.ldws, a.N, a.K / BK8, packed_ws, &use.Xs, &use.Ws, s);
-        if (e != hipSuccess) return e;
-        use.packed = 1;
-    }
-    return a.x_dtype == TBIK_FP8_E5M2 ? launch_rows_mx<1>(a, use, rows, s) : launch_rows_mx<0>(a, use, rows, s);
+    return a.x_dtype == TBIK_FP8_E5M2 ? launch_rows_mx<1>(a, sc, rows, s) : launch_rows_mx<0>(a, sc, rows, s);
 }
 
 hipError_t launch_gemm_mxfp8_reference(const GemmArgs &a, const Mxfp4Scales &sc, hipStream_t s) {

@@ -125,7 +125,7 @@ struct Mx4Params {
     int tiles_n, tiles, work;
     int vector_stores;
     int stream_stores;
-    int scales_packed;          // Xs, Ws are the re-tiled copies (mx_scales_retile_kernel<2>, blocks of this launch's tile height)
+    int scales_packed;          // Xs, Ws are the re-tiled copies (mx_scales_retile_kernel<2>, blocks of 128 rows)
     int stages_total;           // K / 256
 };
 
@@ -171,8 +171,8 @@ void gemm_mxfp4_tiled_kernel(const Mx4Params p) {
         b_ptr = uniform_pointer(reinterpret_cast<const char *>(p.Wt + (int64_t)n0 * p.ldw + kbase / 2) - LANE_BIAS);
         if (p.scales_packed) {                         // a stage's scale bytes of a row block are consecutive: two cache lines per load
             const int64_t stage0 = kbase / 256;
-            xs_ptr = uniform_pointer(reinterpret_cast<const char *>(p.Xs) + ((int64_t)(m0 / BM) * p.stages_total + stage0) * (BM * 8));
-            ws_ptr = uniform_pointer(reinterpret_cast<const char *>(p.Ws) + ((int64_t)(n0 / BN) * p.stages_total + stage0) * (BN * 8) - 1024);
+            xs_ptr = uniform_pointer(reinterpret_cast<const char *>(p.Xs) + ((int64_t)(m0 / 128) * p.stages_total + stage0) * 1024 + m0 % 128 * 8);
+            ws_ptr = uniform_pointer(reinterpret_cast<const char *>(p.Ws) + ((int64_t)(n0 / BN) * p.stages_total + stage0) * 1024 - 1024);
         } else {                                       // straight from the caller's [rows, K / 32] arrays: a cache line per row
             xs_ptr = uniform_pointer(reinterpret_cast<const char *>(p.Xs + (int64_t)m0 * p.ldxs + kbase / 32));
             ws_ptr = uniform_pointer(reinterpret_cast<const char *>(p.Ws + (int64_t)n0 * p.ldws + kbase / 32) - 1024);
@@ -203,7 +203,7 @@ void gemm_mxfp4_tiled_kernel(const Mx4Params p) {
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     const unsigned m0_in_stage = smem_lds + wave_u * REGION4 + A_LOADS4 * 1024;
     const unsigned m0_scales = smem_lds + SCALES_AT + wave_u * 256;
-    const int xs_step = p.scales_packed ? BM * 8 : 8, ws_step = p.scales_packed ? BN * 8 : 8;   // scale bytes per stage
+    const int xs_step = p.scales_packed ? 1024 : 8, ws_step = xs_step;   // scale bytes per stage
     auto issue_part = [&](int slot, auto part_c) __attribute__((always_inline)) {
         constexpr int PART = decltype(part_c)::value;
         if (PART == 0 && __builtin_expect(issue_stage == stages_per_item, 0)) {
@@ -564,20 +564,17 @@ static hipError_t launch_mx4_shape(const GemmArgs &a, const Mxfp4Scales &sc, hip
 
 size_t mxfp4_retiled_scales_bytes(int M, int N, int K) { return mx_retiled_scales_bytes<2>(M, N, K / 256); }
 
-// packed_ws: nullptr, or mxfp4_retiled_scales_bytes(M, N, K) bytes (4-byte aligned) into which the scales are re-tiled
-// first (one short launch), after which every scale load of the GEMM touches two cache lines instead of 32.
-hipError_t launch_gemm_mxfp4_tiled(const GemmArgs &a, const Mxfp4Scales &sc, int rows, void *packed_ws, hipStream_t s) {
+hipError_t launch_mxfp4_retile(const Mxfp4Scales &raw, int M, int N, int K, void *out, Mxfp4Scales *packed, hipStream_t s) {
+    return launch_mx_scales_retile<2>(raw, M, N, K / 256, out, packed, s);
+}
+
+// Re-tiled scales make every scale load touch two cache lines instead of 32.
+hipError_t launch_gemm_mxfp4_tiled(const GemmArgs &a, const Mxfp4Scales &sc, int rows, hipStream_t s) {
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
     if (!gemm_mxfp4_tiled_supports(a, sc) || (rows != 32 && rows != 64 && rows != 128)) return hipErrorInvalidValue;
-    Mxfp4Scales use = sc;
-    if (packed_ws) {
-        hipError_t e = launch_mx_scales_retile<2>(sc.Xs, sc.ldxs, a.M, rows, sc.Ws, sc.ldws, a.N, a.K / 256, packed_ws, &use.Xs, &use.Ws, s);
-        if (e != hipSuccess) return e;
-        use.packed = 1;
-    }
-    if (rows == 32) return launch_mx4_shape<1, 4, 1, 1, 7>(a, use, s);     // 7 x 22 KiB slots
-    if (rows == 64) return launch_mx4_shape<1, 4, 2, 1, 6>(a, use, s);     // 6 x 26 KiB
-    return launch_mx4_shape<2, 2, 2, 2, 4>(a, use, s);                     // 4 x 34 KiB
+    if (rows == 32) return launch_mx4_shape<1, 4, 1, 1, 7>(a, sc, s);     // 7 x 22 KiB slots
+    if (rows == 64) return launch_mx4_shape<1, 4, 2, 1, 6>(a, sc, s);     // 6 x 26 KiB
+    return launch_mx4_shape<2, 2, 2, 2, 4>(a, sc, s);                     // 4 x 34 KiB
 }
 
 }  // namespace tbik

@@ -564,18 +564,14 @@ bool gemm_mxfp6_tiled_supports(const GemmArgs &a, const Mxfp4Scales &sc) {
 
 size_t mxfp6_retiled_scales_bytes(int M, int N, int K) { return mx_retiled_scales_bytes<1>(M, N, K / BK6); }
 
-// packed_ws: nullptr, or mxfp6_retiled_scales_bytes(M, N, K) bytes (4-byte aligned) into which the scales are re-tiled
-// first (one short launch).
-hipError_t launch_gemm_mxfp6_tiled(const GemmArgs &a, const Mxfp4Scales &sc, void *packed_ws, hipStream_t s) {
+hipError_t launch_mxfp6_retile(const Mxfp4Scales &raw, int M, int N, int K, void *out, Mxfp4Scales *packed, hipStream_t s) {
+    return launch_mx_scales_retile<1>(raw, M, N, K / BK6, out, packed, s);
+}
+
+hipError_t launch_gemm_mxfp6_tiled(const GemmArgs &a, const Mxfp4Scales &sc, hipStream_t s) {
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
     if (!gemm_mxfp6_tiled_supports(a, sc)) return hipErrorInvalidValue;
-    Mxfp4Scales use = sc;
-    if (packed_ws) {
-        hipError_t e = launch_mx_scales_retile<1>(sc.Xs, sc.ldxs, a.M, 128, sc.Ws, sc.ldws, a.N, a.K / BK6, packed_ws, &use.Xs, &use.Ws, s);
-        if (e != hipSuccess) return e;
-        use.packed = 1;
-    }
-    return a.x_dtype == TBIK_FP6_E3M2 ? launch_mx6<3>(a, use, s) : launch_mx6<2>(a, use, s);
+    return a.x_dtype == TBIK_FP6_E3M2 ? launch_mx6<3>(a, sc, s) : launch_mx6<2>(a, sc, s);
 }
 
 hipError_t launch_gemm_mxfp6_reference(const GemmArgs &a, const Mxfp4Scales &sc, hipStream_t s) {

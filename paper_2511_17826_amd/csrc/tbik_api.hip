@@ -215,8 +215,10 @@ TimedPlan tile_plan(Operands kind, int M, int N, int K, int ns, int only_split, 
 // Rows of a batch that are better computed by a call of their own (last_rows, 0: none): a launch whose last round of tiles is
 // nearly empty is cut behind its last full round, and the remaining rows get the height and split of a small batch.  1100
 // rows of 4096 x 4096 in bf16 are 288 tiles of 128 rows, two rounds, 72 us; as 1024 rows and 76 rows 54 us.  (The rows of
-// a result do not depend on each other, so neither do their bits.)
+// a result do not depend on each other, so neither do their bits.)  Microscaling formats re-tile the scales of both pieces in one
+// launch, so a cut pays for it once: at K = 12288 and 1300 rows MXFP8 90.5 -> 82.3 us, MXFP4 59.6 -> 57.0, MXFP6 99.8 -> 95.2.
 constexpr double kPieceUs = 2.0;        // what a launch behind another costs
+constexpr double kCutUs = 1.9;          // (1300 .. 1536 rows of 4096 x 4096 in MXFP4 promise 1.8 and lose 0.5)
 struct BatchPlan {
     int last_rows;
     TilePlan first, last;               // of the rows before the last ones, of the last ones
@@ -232,7 +234,9 @@ BatchPlan batch_plan(Operands kind, int M, int N, int K, int ns, size_t room) {
     const int rest = M % (per_round * 128), full = M - rest;
     if (rest == 0) return plan;
     const TimedPlan first = tile_plan(kind, full, N, K, ns, 0, room), last = tile_plan(kind, rest, N, K, ns, 0, room);
-    if (first.us + last.us + kPieceUs >= 0.95 * whole.us) return plan;
+    const double shared_us = rest >= 128 ? kTileModels[kind].retile : 0.0;      // the pieces' scales are re-tiled once
+    const double saved_us = whole.us - (first.us + last.us - shared_us + kPieceUs);
+    if (saved_us <= 0.05 * whole.us || saved_us < kCutUs) return plan;
     plan.planes = std::max(split_planes_bytes(full, N, first.plan.split), split_planes_bytes(rest, N, last.plan.split));
     plan.last_rows = rest;
     plan.first = first.plan;
@@ -609,9 +613,35 @@ static int mxfp4_checks(const void *X, int64_t ldx, const void *Xs, int64_t ldxs
 }
 
 // From 128 rows on the microscaling GEMMs re-tile their scales first (a launch of its own, which a small batch would
-// feel): the workspace is the fp32 planes of the K split, rounded up to 256 bytes, then the re-tiled scales.
+// feel): the workspace is the fp32 planes of the K split, rounded up to 256 bytes, then the re-tiled scales.  The pieces of a
+// cut batch share one re-tiling.
 static bool mx_retiles(int M) { return M >= 128; }
 static size_t round_256(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
+using RetileScales = hipError_t (*)(const Mxfp4Scales &, int M, int N, int K, void *out, Mxfp4Scales *packed, hipStream_t s);
+struct CallScales {
+    Mxfp4Scales raw;                    // of the whole call
+    int M, N, K;
+    RetileScales retile;
+    void *area;                         // room for the copies, or nullptr: none are made
+    Mxfp4Scales packed{};
+    // The scales of the rows from m0 on for the reference kernel and the slices; for the tiled kernels (m0 a multiple of 128).
+    Mxfp4Scales plain(int m0) const {
+        Mxfp4Scales sc = raw;
+        sc.Xs += (int64_t)m0 * raw.ldxs;
+        return sc;
+    }
+    hipError_t for_tiles(int m0, Mxfp4Scales *sc, hipStream_t s) {
+        *sc = plain(m0);
+        if (!area || (m0 & 127)) return hipSuccess;
+        if (!packed.packed) {
+            hipError_t e = retile(raw, M, N, K, area, &packed, s);
+            if (e != hipSuccess) return e;
+        }
+        *sc = packed;
+        sc->Xs += (int64_t)m0 * (K / 32);
+        return hipSuccess;
+    }
+};
 static size_t mxfp4_scales_room(int M, int N, int K) { return mx_retiles(M) && K % 256 == 0 ? mxfp4_retiled_scales_bytes(M, N, K) : 0; }
 size_t tbik_gemm_mxfp4_workspace_bytes(int M, int N, int K, int leaf, int k_first) {
     int sl, ns;
@@ -637,22 +667,25 @@ int tbik_gemm_mxfp4(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)hip_stream;
     const size_t room = workspace && workspace_bytes > scales_room ? (workspace_bytes - scales_room) & ~(size_t)255 : 0;      // planes are rounded up to 256 bytes
+    CallScales scales{{(const uint8_t *)Xs, ldxs, (const uint8_t *)Ws, ldws}, M, N, K, launch_mxfp4_retile,
+                      scales_room ? static_cast<char *>(workspace) + room : nullptr};
     hipError_t e = in_pieces(OPERANDS_MXFP4, M, N, K, ns, room, [&](int m0, int m, TilePlan plan) {
         void *y = static_cast<char *>(Y) + (int64_t)m0 * ldy * (y_dtype == TBIK_F32 ? 4 : 2);
         GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
                    (int)y_dtype, m, N, K, sl, ns, 1, TBIK_MXFP4, 0};
-        const Mxfp4Scales sc{static_cast<const uint8_t *>(Xs) + (int64_t)m0 * ldxs, ldxs, (const uint8_t *)Ws, ldws};
+        const Mxfp4Scales sc = scales.plain(m0);
         if (takes_slices(a, &sc)) return launch_gemm_slice(a, &sc, s);
         GemmArgs probe = a;
         probe.P = plan.split;
         if (g_forced_variant.load() == VARIANT_REFERENCE || !gemm_mxfp4_tiled_supports(probe, sc)) return launch_gemm_mxfp4_reference(a, sc, s);
-        // (the second piece's re-tiled scales may take the first one's place: the stream has passed the first by then)
-        void *retiled = mx_retiles(m) ? static_cast<char *>(workspace) + round_256(split_planes_bytes(m, N, plan.split)) : nullptr;
-        if (plan.split == 1) return launch_gemm_mxfp4_tiled(a, sc, plan.rows, retiled, s);
+        Mxfp4Scales tiled;
+        hipError_t pe = scales.for_tiles(m0, &tiled, s);
+        if (pe != hipSuccess) return pe;
+        if (plan.split == 1) return launch_gemm_mxfp4_tiled(a, tiled, plan.rows, s);
         a.partials = reinterpret_cast<float *>(workspace);
         a.Y = nullptr;
         a.P = plan.split;
-        hipError_t pe = launch_gemm_mxfp4_tiled(a, sc, plan.rows, retiled, s);
+        pe = launch_gemm_mxfp4_tiled(a, tiled, plan.rows, s);
         return pe == hipSuccess ? launch_tree_combine(a.partials, plan.split, y, ldy, (int)y_dtype, m, N, s) : pe;
     });
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
@@ -672,9 +705,12 @@ int tbik_gemm_shard_partials_mxfp4(const void *X, int64_t ldx, const void *Xs, i
     const Mxfp4Scales sc{(const uint8_t *)Xs, ldxs, (const uint8_t *)Ws, ldws};
     const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_mxfp4_tiled_supports(a, sc);
     // a workspace as tbik_gemm_mxfp4 takes it has room for the re-tiled scales
-    void *retiled = (tiled && mx_retiles(M) && workspace && aligned(workspace, 256) && workspace_bytes >= mxfp4_scales_room(M, N, K)) ? workspace : nullptr;
-    hipError_t e = tiled ? launch_gemm_mxfp4_tiled(a, sc, tile_plan(OPERANDS_MXFP4, M, N, K, ns, P, 0).plan.rows, retiled, (hipStream_t)hip_stream)
-                         : launch_gemm_mxfp4_reference(a, sc, (hipStream_t)hip_stream);
+    const bool room = mx_retiles(M) && workspace && aligned(workspace, 256) && workspace_bytes >= mxfp4_scales_room(M, N, K);
+    CallScales scales{sc, M, N, K, launch_mxfp4_retile, room ? workspace : nullptr};
+    Mxfp4Scales use;
+    hipError_t e = tiled ? scales.for_tiles(0, &use, (hipStream_t)hip_stream) : hipSuccess;
+    if (e == hipSuccess) e = tiled ? launch_gemm_mxfp4_tiled(a, use, tile_plan(OPERANDS_MXFP4, M, N, K, ns, P, 0).plan.rows, (hipStream_t)hip_stream)
+                                   : launch_gemm_mxfp4_reference(a, sc, (hipStream_t)hip_stream);
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
 
@@ -732,22 +768,25 @@ int tbik_gemm_mxfp8(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)hip_stream;
     const size_t room = workspace && workspace_bytes > scales_room ? (workspace_bytes - scales_room) & ~(size_t)255 : 0;      // planes are rounded up to 256 bytes
+    CallScales scales{{(const uint8_t *)Xs, ldxs, (const uint8_t *)Ws, ldws}, M, N, K, launch_mxfp8_retile,
+                      scales_room ? static_cast<char *>(workspace) + room : nullptr};
     hipError_t e = in_pieces(OPERANDS_MXFP8, M, N, K, ns, room, [&](int m0, int m, TilePlan plan) {
         void *y = static_cast<char *>(Y) + (int64_t)m0 * ldy * (y_dtype == TBIK_F32 ? 4 : 2);
         GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
                    (int)y_dtype, m, N, K, sl, ns, 1, (int)x_dtype, 0};
-        const Mxfp4Scales sc{static_cast<const uint8_t *>(Xs) + (int64_t)m0 * ldxs, ldxs, (const uint8_t *)Ws, ldws};
+        const Mxfp4Scales sc = scales.plain(m0);
         if (takes_slices(a, &sc)) return launch_gemm_slice(a, &sc, s);
         GemmArgs probe = a;
         probe.P = plan.split;
         if (g_forced_variant.load() == VARIANT_REFERENCE || !gemm_mxfp8_tiled_supports(probe, sc)) return launch_gemm_mxfp8_reference(a, sc, s);
-        // (the second piece's re-tiled scales may take the first one's place: the stream has passed the first by then)
-        void *retiled = mx_retiles(m) ? static_cast<char *>(workspace) + round_256(split_planes_bytes(m, N, plan.split)) : nullptr;
-        if (plan.split == 1) return launch_gemm_mxfp8_tiled(a, sc, plan.rows, retiled, s);
+        Mxfp4Scales tiled;
+        hipError_t pe = scales.for_tiles(m0, &tiled, s);
+        if (pe != hipSuccess) return pe;
+        if (plan.split == 1) return launch_gemm_mxfp8_tiled(a, tiled, plan.rows, s);
         a.partials = reinterpret_cast<float *>(workspace);
         a.Y = nullptr;
         a.P = plan.split;
-        hipError_t pe = launch_gemm_mxfp8_tiled(a, sc, plan.rows, retiled, s);
+        pe = launch_gemm_mxfp8_tiled(a, tiled, plan.rows, s);
         return pe == hipSuccess ? launch_tree_combine(a.partials, plan.split, y, ldy, (int)y_dtype, m, N, s) : pe;
     });
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
@@ -767,9 +806,12 @@ int tbik_gemm_shard_partials_mxfp8(const void *X, int64_t ldx, const void *Xs, i
     const Mxfp4Scales sc{(const uint8_t *)Xs, ldxs, (const uint8_t *)Ws, ldws};
     const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_mxfp8_tiled_supports(a, sc);
     // a workspace as tbik_gemm_mxfp8 takes it has room for the re-tiled scales
-    void *retiled = (tiled && mx_retiles(M) && workspace && aligned(workspace, 256) && workspace_bytes >= mxfp8_scales_room(M, N, K)) ? workspace : nullptr;
-    hipError_t e = tiled ? launch_gemm_mxfp8_tiled(a, sc, tile_plan(OPERANDS_MXFP8, M, N, K, ns, P, 0).plan.rows, retiled, (hipStream_t)hip_stream)
-                         : launch_gemm_mxfp8_reference(a, sc, (hipStream_t)hip_stream);
+    const bool room = mx_retiles(M) && workspace && aligned(workspace, 256) && workspace_bytes >= mxfp8_scales_room(M, N, K);
+    CallScales scales{sc, M, N, K, launch_mxfp8_retile, room ? workspace : nullptr};
+    Mxfp4Scales use;
+    hipError_t e = tiled ? scales.for_tiles(0, &use, (hipStream_t)hip_stream) : hipSuccess;
+    if (e == hipSuccess) e = tiled ? launch_gemm_mxfp8_tiled(a, use, tile_plan(OPERANDS_MXFP8, M, N, K, ns, P, 0).plan.rows, (hipStream_t)hip_stream)
+                                   : launch_gemm_mxfp8_reference(a, sc, (hipStream_t)hip_stream);
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
 
@@ -830,22 +872,25 @@ int tbik_gemm_mxfp6(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
     if (workspace && !aligned(workspace, 256)) return TBIK_ERR_ALIGN;
     hipStream_t s = (hipStream_t)hip_stream;
     const size_t room = workspace && workspace_bytes > scales_room ? (workspace_bytes - scales_room) & ~(size_t)255 : 0;      // planes are rounded up to 256 bytes
+    CallScales scales{{(const uint8_t *)Xs, ldxs, (const uint8_t *)Ws, ldws}, M, N, K, launch_mxfp6_retile,
+                      scales_room ? static_cast<char *>(workspace) + room : nullptr};
     hipError_t e = in_pieces(OPERANDS_MXFP6, M, N, K, ns, room, [&](int m0, int m, TilePlan plan) {
         void *y = static_cast<char *>(Y) + (int64_t)m0 * ldy * (y_dtype == TBIK_F32 ? 4 : 2);
         GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
                    (int)y_dtype, m, N, K, sl, ns, 1, (int)x_dtype, 0};
-        const Mxfp4Scales sc{static_cast<const uint8_t *>(Xs) + (int64_t)m0 * ldxs, ldxs, (const uint8_t *)Ws, ldws};
+        const Mxfp4Scales sc = scales.plain(m0);
         if (takes_slices(a, &sc)) return launch_gemm_slice(a, &sc, s);
         GemmArgs probe = a;
         probe.P = plan.split;
         if (g_forced_variant.load() == VARIANT_REFERENCE || !gemm_mxfp6_tiled_supports(probe, sc)) return launch_gemm_mxfp6_reference(a, sc, s);
-        // (the second piece's re-tiled scales may take the first one's place: the stream has passed the first by then)
-        void *retiled = mx_retiles(m) ? static_cast<char *>(workspace) + round_256(split_planes_bytes(m, N, plan.split)) : nullptr;
-        if (plan.split == 1) return launch_gemm_mxfp6_tiled(a, sc, retiled, s);
+        Mxfp4Scales tiled;
+        hipError_t pe = scales.for_tiles(m0, &tiled, s);
+        if (pe != hipSuccess) return pe;
+        if (plan.split == 1) return launch_gemm_mxfp6_tiled(a, tiled, s);
         a.partials = reinterpret_cast<float *>(workspace);
         a.Y = nullptr;
         a.P = plan.split;
-        hipError_t pe = launch_gemm_mxfp6_tiled(a, sc, retiled, s);
+        pe = launch_gemm_mxfp6_tiled(a, tiled, s);
         return pe == hipSuccess ? launch_tree_combine(a.partials, plan.split, y, ldy, (int)y_dtype, m, N, s) : pe;
     });
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
@@ -865,9 +910,12 @@ int tbik_gemm_shard_partials_mxfp6(const void *X, int64_t ldx, const void *Xs, i
     const Mxfp4Scales sc{(const uint8_t *)Xs, ldxs, (const uint8_t *)Ws, ldws};
     const bool tiled = g_forced_variant.load() != VARIANT_REFERENCE && gemm_mxfp6_tiled_supports(a, sc);
     // a workspace as tbik_gemm_mxfp6 takes it has room for the re-tiled scales
-    void *retiled = (tiled && mx_retiles(M) && workspace && aligned(workspace, 256) && workspace_bytes >= mxfp6_scales_room(M, N, K)) ? workspace : nullptr;
-    hipError_t e = tiled ? launch_gemm_mxfp6_tiled(a, sc, retiled, (hipStream_t)hip_stream)
-                         : launch_gemm_mxfp6_reference(a, sc, (hipStream_t)hip_stream);
+    const bool room = mx_retiles(M) && workspace && aligned(workspace, 256) && workspace_bytes >= mxfp6_scales_room(M, N, K);
+    CallScales scales{sc, M, N, K, launch_mxfp6_retile, room ? workspace : nullptr};
+    Mxfp4Scales use;
+    hipError_t e = tiled ? scales.for_tiles(0, &use, (hipStream_t)hip_stream) : hipSuccess;
+    if (e == hipSuccess) e = tiled ? launch_gemm_mxfp6_tiled(a, use, (hipStream_t)hip_stream)
+                                   : launch_gemm_mxfp6_reference(a, sc, (hipStream_t)hip_stream);
     return e == hipSuccess ? TBIK_OK : hip_fail(e);
 }
 

@@ -62,26 +62,31 @@ struct Mxfp4Scales {
     int64_t ldxs;
     const uint8_t *Ws;   // [N, ldws]
     int64_t ldws;
-    int packed = 0;      // set by the tiled launchers only: Xs, Ws point at their re-tiled copies
+    int packed = 0;      // Xs, Ws point at copies re-tiled by launch_mx*_retile (the tiled kernels only)
 };
 hipError_t launch_gemm_mxfp4_reference(const GemmArgs &a, const Mxfp4Scales &sc, hipStream_t s);
-// rows: 128, 64 or 32.  packed_ws: nullptr or mxfp4_retiled_scales_bytes(M, N, K) bytes of device memory for re-tiled scales.
-hipError_t launch_gemm_mxfp4_tiled(const GemmArgs &a, const Mxfp4Scales &sc, int rows, void *packed_ws, hipStream_t s);
+// rows: 128, 64 or 32.
+hipError_t launch_gemm_mxfp4_tiled(const GemmArgs &a, const Mxfp4Scales &sc, int rows, hipStream_t s);
+// Copies the scales of all M and N rows into `out` (mxfp4_retiled_scales_bytes(M, N, K) bytes) in the order of the tiled kernels.
+hipError_t launch_mxfp4_retile(const Mxfp4Scales &raw, int M, int N, int K, void *out, Mxfp4Scales *packed, hipStream_t s);
 size_t mxfp4_retiled_scales_bytes(int M, int N, int K);
 bool gemm_mxfp4_tiled_supports(const GemmArgs &a, const Mxfp4Scales &sc);
 
 // The same for MXFP8 operands: the 8-bit kernels with one E8M0 scale per block of 32 k beside each operand (a.x_dtype
 // names the element format, TBIK_FP8_E4M3 or TBIK_FP8_E5M2; X [M, ldx] bytes, W the transposed weight [N, ldw] bytes).
 hipError_t launch_gemm_mxfp8_reference(const GemmArgs &a, const Mxfp4Scales &sc, hipStream_t s);
-// rows: 128, 64 or 32.  packed_ws: nullptr or mxfp8_retiled_scales_bytes(M, N, K) bytes of device memory for re-tiled scales.
-hipError_t launch_gemm_mxfp8_tiled(const GemmArgs &a, const Mxfp4Scales &sc, int rows, void *packed_ws, hipStream_t s);
+// rows: 128, 64 or 32.
+hipError_t launch_gemm_mxfp8_tiled(const GemmArgs &a, const Mxfp4Scales &sc, int rows, hipStream_t s);
+// Copies the scales of all M and N rows into `out` (mxfp8_retiled_scales_bytes(M, N, K) bytes) in the order of the tiled kernels.
+hipError_t launch_mxfp8_retile(const Mxfp4Scales &raw, int M, int N, int K, void *out, Mxfp4Scales *packed, hipStream_t s);
 size_t mxfp8_retiled_scales_bytes(int M, int N, int K);
 bool gemm_mxfp8_tiled_supports(const GemmArgs &a, const Mxfp4Scales &sc);
 
 // The same for MXFP6 operands (a.x_dtype TBIK_FP6_E2M3 or TBIK_FP6_E3M2): X [M, ldx] bytes of packed 6-bit elements
 // (ldx >= 3 K / 4), W the transposed weight [N, ldw] bytes; one tile shape, 128 x 128.
 hipError_t launch_gemm_mxfp6_reference(const GemmArgs &a, const Mxfp4Scales &sc, hipStream_t s);
-hipError_t launch_gemm_mxfp6_tiled(const GemmArgs &a, const Mxfp4Scales &sc, void *packed_ws, hipStream_t s);
+hipError_t launch_gemm_mxfp6_tiled(const GemmArgs &a, const Mxfp4Scales &sc, hipStream_t s);
+hipError_t launch_mxfp6_retile(const Mxfp4Scales &raw, int M, int N, int K, void *out, Mxfp4Scales *packed, hipStream_t s);
 bool gemm_mxfp6_tiled_supports(const GemmArgs &a, const Mxfp4Scales &sc);
 size_t mxfp6_retiled_scales_bytes(int M, int N, int K);
 
