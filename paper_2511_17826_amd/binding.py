@@ -152,29 +152,40 @@ def _check(status: int, where: str):
         raise TbikError(status, where)
 
 
+# A small call is over on the GPU before Python has issued it (one token of 4096 x 4096: 7 us there, 11 here; 10 so), so what every
+# call does below asks a tensor once and takes the cheapest way to an answer.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
 
 
 def _stream() -> int:
-    """Handle of torch's current stream on the current device (the raw getter saves about a microsecond per call)."""
+    """Handle of torch's current stream on the current device (the raw getters save about a microsecond per call)."""
     if _raw_stream is not None:
-        return _raw_stream(torch.cuda.current_device())
+        return _raw_stream(_current_device())
     return torch.cuda.current_stream().cuda_stream
 
 
+_DTYPES = {torch.float32: TBIK_F32, torch.bfloat16: TBIK_BF16, torch.float16: TBIK_F16}
+
+
 def _dt(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return TBIK_F32
-    if t.dtype == torch.bfloat16:
-        return TBIK_BF16
-    if t.dtype == torch.float16:
-        return TBIK_F16
-    raise TypeError("only float32, bfloat16 and float16 tensors are supported, got %s" % t.dtype)
+    code = _DTYPES.get(t.dtype)
+    if code is None:
+        raise TypeError("only float32, bfloat16 and float16 tensors are supported, got %s" % t.dtype)
+    return code
 
 
-def _rowmajor(t: torch.Tensor, name: str):
-    if t.dim() != 2 or t.stride(1) != 1 or not t.is_cuda:
+def _rowmajor(t: torch.Tensor, name: str) -> int:
+    """Checks a matrix operand; its leading dimension."""
+    strides = t.stride()
+    if len(strides) != 2 or strides[1] != 1 or not t.is_cuda:
         raise ValueError("%s must be a 2-D row-major GPU tensor" % name)
+    return strides[0]
+
+
+def _room(workspace):
+    """Address and bytes of a workspace that may be None."""
+    return (None, 0) if workspace is None else (workspace.data_ptr(), workspace.numel() * workspace.element_size())
 
 
 _ws_cache = {}
@@ -185,7 +196,7 @@ def _workspace(nbytes: int, device) -> torch.Tensor:
     workspace must not overlap in time, which only calls on one stream guarantee.  A tensor that is replaced by a larger
     one stays alive until the kernels already queued on its stream are done (torch's allocator frees a block for reuse
     by the stream it was allocated on).  Callers that run one call's kernels on several streams pass their own."""
-    key = (str(device), _stream())
+    key = (device.index, _stream())
     w = _ws_cache.get(key)
     if w is None or w.numel() < nbytes:
         w = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
@@ -206,22 +217,22 @@ def gemm_f32_workspace_bytes(M, N, K, leaf, k_first=1) -> int:
 
 
 def _gemm(entry: str, in_dtype, X, W, leaf, k_first, out_dtype, out, workspace):
-    _rowmajor(X, "X"); _rowmajor(W, "W")
+    ldx, ldw = _rowmajor(X, "X"), _rowmajor(W, "W")
     assert X.dtype == in_dtype and W.dtype == in_dtype
     M, K = X.shape
     K2, N = W.shape
     assert K == K2
     if out is None:
-        out = torch.empty((M, N), dtype=out_dtype, device=X.device)
-    _rowmajor(out, "out")
+        out = X.new_empty((M, N), dtype=out_dtype)
+    ldo = _rowmajor(out, "out")
+    L = lib()
     if workspace is None:
-        need = gemm_16bit_workspace_bytes(M, N, K, leaf, k_first)
+        need = L.tbik_gemm_16bit_workspace_bytes(M, N, K, leaf, k_first)
         if need:
             workspace = _workspace(need, X.device)
-    st = getattr(lib(), entry)(X.data_ptr(), X.stride(0), W.data_ptr(), W.stride(0), out.data_ptr(), out.stride(0),
-                               _dt(out), M, N, K, leaf, k_first,
-                               workspace.data_ptr() if workspace is not None else None,
-                               workspace.numel() * workspace.element_size() if workspace is not None else 0, _stream())
+    room, room_bytes = _room(workspace)
+    st = getattr(L, entry)(X.data_ptr(), ldx, W.data_ptr(), ldw, out.data_ptr(), ldo, _dt(out), M, N, K, leaf, k_first,
+                           room, room_bytes, _stream())
     _check(st, entry)
     return out
 
@@ -247,7 +258,7 @@ def tbik_gemm_f32(X: torch.Tensor, W: torch.Tensor, leaf: int, k_first: int = 1,
     K2, N = W.shape
     assert K == K2
     if out is None:
-        out = torch.empty((M, N), dtype=torch.float32, device=X.device)
+        out = X.new_empty((M, N))
     _rowmajor(out, "out")
     assert out.dtype == torch.float32 and out.shape == (M, N)
     if workspace is None:
@@ -268,7 +279,7 @@ def _gemm_shard_partials(entry: str, in_dtype, X, W, leaf, k_first, P, out, work
     N = W.shape[1]
     assert W.shape[0] == K
     if out is None:
-        out = torch.empty((max(P, 1), M, N), dtype=torch.float32, device=X.device)
+        out = X.new_empty((max(P, 1), M, N), dtype=torch.float32)
     assert out.is_contiguous() and out.dtype == torch.float32
     need = (gemm_f32_workspace_bytes if in_dtype == torch.float32 else gemm_16bit_workspace_bytes)(M, N, K, leaf, k_first)
     if workspace is None and need:
@@ -325,7 +336,7 @@ def tbik_gemm_fp8(X: torch.Tensor, Wt: torch.Tensor, leaf: int, k_first: int = 1
     M, K = X.shape
     N = Wt.shape[0]
     if out is None:
-        out = torch.empty((M, N), dtype=out_dtype, device=X.device)
+        out = X.new_empty((M, N), dtype=out_dtype)
     _rowmajor(out, "out")
     assert out.shape == (M, N)
     if workspace is None:
@@ -345,7 +356,7 @@ def tbik_gemm_shard_partials_fp8(X: torch.Tensor, Wt: torch.Tensor, leaf: int, k
     M, K = X.shape
     N = Wt.shape[0]
     if out is None:
-        out = torch.empty((max(P, 1), M, N), dtype=torch.float32, device=X.device)
+        out = X.new_empty((max(P, 1), M, N), dtype=torch.float32)
     assert out.is_contiguous() and out.dtype == torch.float32
     st = lib().tbik_gemm_shard_partials_fp8(X.data_ptr(), X.stride(0), Wt.data_ptr(), Wt.stride(0), out.data_ptr(), dt,
                                             M, N, K, leaf, k_first, P, None, 0, _stream())
@@ -389,7 +400,7 @@ def tbik_gemm_mxfp4(X, Xs, Wt, Ws, leaf: int, k_first: int = 1, out_dtype=torch.
     transposed, Wt [N, K/2] with Ws [N, K/32]."""
     M, N, K = _mx_operands(X, Xs, Wt, Ws)
     if out is None:
-        out = torch.empty((M, N), dtype=out_dtype, device=X.device)
+        out = X.new_empty((M, N), dtype=out_dtype)
     _rowmajor(out, "out")
     assert out.shape == (M, N)
     if workspace is None:
@@ -407,7 +418,7 @@ def tbik_gemm_mxfp4(X, Xs, Wt, Ws, leaf: int, k_first: int = 1, out_dtype=torch.
 def tbik_gemm_shard_partials_mxfp4(X, Xs, Wt, Ws, leaf: int, k_first: int, P: int, out: torch.Tensor | None = None):
     M, N, K = _mx_operands(X, Xs, Wt, Ws)
     if out is None:
-        out = torch.empty((max(P, 1), M, N), dtype=torch.float32, device=X.device)
+        out = X.new_empty((max(P, 1), M, N), dtype=torch.float32)
     assert out.is_contiguous() and out.dtype == torch.float32
     need = gemm_mxfp4_workspace_bytes(M, N, K, leaf, k_first)
     ws = _workspace(need, X.device) if need else None
@@ -451,7 +462,7 @@ def tbik_gemm_mxfp8(X, Xs, Wt, Ws, leaf: int, k_first: int = 1, fmt: str = "e4m3
     the weight transposed, Wt [N, K] with Ws [N, K/32]."""
     X, Wt, dt, M, N, K = _mx8_operands(X, Xs, Wt, Ws, fmt)
     if out is None:
-        out = torch.empty((M, N), dtype=out_dtype, device=X.device)
+        out = X.new_empty((M, N), dtype=out_dtype)
     _rowmajor(out, "out")
     assert out.shape == (M, N)
     if workspace is None:
@@ -470,7 +481,7 @@ def tbik_gemm_shard_partials_mxfp8(X, Xs, Wt, Ws, leaf: int, k_first: int, P: in
                                    out: torch.Tensor | None = None):
     X, Wt, dt, M, N, K = _mx8_operands(X, Xs, Wt, Ws, fmt)
     if out is None:
-        out = torch.empty((max(P, 1), M, N), dtype=torch.float32, device=X.device)
+        out = X.new_empty((max(P, 1), M, N), dtype=torch.float32)
     assert out.is_contiguous() and out.dtype == torch.float32
     need = gemm_mxfp8_workspace_bytes(M, N, K, leaf, k_first)
     ws = _workspace(need, X.device) if need else None
@@ -519,7 +530,7 @@ def tbik_gemm_mxfp6(X, Xs, Wt, Ws, leaf: int, k_first: int = 1, fmt: str = "e2m3
     Xs [M, K/32]; the weight transposed, Wt [N, 3K/4] with Ws [N, K/32]."""
     dt, M, N, K = _mx6_operands(X, Xs, Wt, Ws, fmt)
     if out is None:
-        out = torch.empty((M, N), dtype=out_dtype, device=X.device)
+        out = X.new_empty((M, N), dtype=out_dtype)
     _rowmajor(out, "out")
     assert out.shape == (M, N)
     if workspace is None:
@@ -538,7 +549,7 @@ def tbik_gemm_shard_partials_mxfp6(X, Xs, Wt, Ws, leaf: int, k_first: int, P: in
                                    out: torch.Tensor | None = None):
     dt, M, N, K = _mx6_operands(X, Xs, Wt, Ws, fmt)
     if out is None:
-        out = torch.empty((max(P, 1), M, N), dtype=torch.float32, device=X.device)
+        out = X.new_empty((max(P, 1), M, N), dtype=torch.float32)
     assert out.is_contiguous() and out.dtype == torch.float32
     need = gemm_mxfp6_workspace_bytes(M, N, K, leaf, k_first)
     ws = _workspace(need, X.device) if need else None
@@ -599,7 +610,7 @@ def tbik_gemm_swiglu(X: torch.Tensor, W_gu: torch.Tensor, leaf: int, k_first: in
     assert W_gu.shape[0] == K and W_gu.shape[1] % 2 == 0
     I = W_gu.shape[1] // 2
     if out is None:
-        out = torch.empty((M, I), dtype=X.dtype, device=X.device)
+        out = X.new_empty((M, I))
     _rowmajor(out, "out")
     assert out.dtype == X.dtype and out.shape == (M, I)
     if workspace is None:
@@ -618,7 +629,7 @@ def tbik_tree_combine(partials: torch.Tensor, out_dtype=torch.bfloat16, out: tor
     assert partials.dim() == 3 and partials.is_contiguous() and partials.dtype == torch.float32
     P, M, N = partials.shape
     if out is None:
-        out = torch.empty((M, N), dtype=out_dtype, device=partials.device)
+        out = partials.new_empty((M, N), dtype=out_dtype)
     _rowmajor(out, "out")
     st = lib().tbik_tree_combine(partials.data_ptr(), P, out.data_ptr(), out.stride(0), _dt(out), M, N, _stream())
     _check(st, "tbik_tree_combine")
