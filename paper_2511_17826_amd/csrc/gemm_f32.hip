@@ -79,7 +79,12 @@ __global__ __launch_bounds__(64) void gemm_f32_reference_kernel(
 // wavefront's own vector ALU between MFMAs, so the K-loop is kept free of them.
 //   Slot = [X tile: 128 rows x 32 k, 128 B per row][W tile: 32 k x 128 columns, 512 B per row], no padding (a direct
 //   load writes 1 KiB of consecutive LDS); bank conflicts are kept low by swizzles applied on the global side:
-//   X: the 16-byte chunk c of row r sits at position c ^ (r & 7)             (4-byte fragment reads: 4 lanes per bank)
+//   X: in blocks of 8 rows (1 KiB), pairs of 16-byte chunks one after the other, 32 bytes of each row in a pair; chunk c of
+//      row r sits at place (c & 1) ^ ((r >> 2) & 1) of its 32 bytes           (4-byte fragment reads: 4 lanes per bank)
+//      The pair is an immediate of the read, so a row's fragments take two address registers.  With rows of 128 bytes and
+//      chunk c at c ^ (r & 7), which has the same conflicts, they take eight, each moved to the next slot by an add of its own
+//      (1500 x 4096 x 4096 405.7 -> 401.3 us).  Single chunks instead of pairs take one register, but spread a load over 64
+//      pieces of 16 bytes, and gain no more.
 //   W: chunk c of row k sits at position c ^ (8 (k & 1))                     (the two k-slots of a step: other banks)
 // Wavefront w loads X rows 32 w .. 32 w + 31 (4 loads of 8 rows) and W rows 8 w .. 8 w + 7 (4 loads of 2 rows).
 // Rows past M repeat row M - 1 and column chunks past N repeat the last chunk (such outputs are never stored).
@@ -114,8 +119,7 @@ __device__ __forceinline__ void f32_wait_loads_and_barrier() {
 // The small tile leaves room for a second workgroup on the compute unit (80 KiB of LDS, at most 112 registers), which fills
 // its pipeline fill and the gaps between its MFMAs: 240 tiles at K = 6144 split in two 121 -> 103 us.
 template <int LEVELS, int MT, int NT, int WN>
-__global__ __launch_bounds__(256, MT == 1 ? 2 : 1)
-void gemm_f32_tiled_kernel(const F32Params p) {
+__device__ __forceinline__ void gemm_f32_item(const F32Params &p, const int id) {
     constexpr int WM = 4 / WN;
     constexpr int BM = 32 * MT * WM;
     static_assert(32 * NT * WN == F32_BN && (BM == 128 || BM == 32), "tile shape");
@@ -124,6 +128,8 @@ void gemm_f32_tiled_kernel(const F32Params p) {
     constexpr int A_LOADS = BM / 32;                       // per wavefront and K-step: BM / 4 rows, 8 rows per load
     constexpr int LOADS = A_LOADS + 4;
     extern __shared__ __attribute__((aligned(16))) float smem_f32[];
+
+    auto swizzle = [](int r) { return (r >> 2) & 1; };
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -139,7 +145,7 @@ void gemm_f32_tiled_kernel(const F32Params p) {
         // 8 x 4 tiles dealt to the XCDs left them unevenly loaded where the rows are not a multiple of eight tiles:
         // 1200 x 2048 at K = 6144, split in four, four rounds on four XCDs and one on the others, 391 us.)
         const int per_xcd = gridDim.x >> 3;
-        const int item = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+        const int item = (id & 7) * per_xcd + (id >> 3);
         const int tiles = p.tiles_m * p.tiles_n;
         if (item >= tiles * p.shards) return;              // uniform
         shard = item / tiles;
@@ -148,8 +154,7 @@ void gemm_f32_tiled_kernel(const F32Params p) {
         tile_m = 8 * group + in_group % height;
         tile_n = in_group / height;
     } else {
-        // Few rows: every workgroup streams its own panel of W; the grid is exactly tiles x shards.
-        const int id = blockIdx.x;
+        // Few rows: every item streams its own panel of W; the items are exactly tiles x shards.
         tile_n = id % p.tiles_n;
         tile_m = (id / p.tiles_n) % p.tiles_m;
         shard = id / (p.tiles_n * p.tiles_m);
@@ -162,9 +167,9 @@ void gemm_f32_tiled_kernel(const F32Params p) {
     unsigned a_lo[A_LOADS], b_lo[4];
 #pragma unroll
     for (int i = 0; i < A_LOADS; ++i) {
-        const int r = (BM / 4) * wave + 8 * i + (lane >> 3);                 // row of the X tile
+        const int r = (BM / 4) * wave + 8 * i + (lane >> 1) % 8;             // row of the X tile
         const int rg = min(m0 + r, p.M - 1) - m0;                            // row fetched into its place; >= 0 since m0 < M
-        const int c = (lane & 7) ^ (r & 7);                                  // chunk that belongs at this lane's position
+        const int c = (lane >> 4) * 2 + ((lane & 1) ^ swizzle(r));           // chunk that belongs at this lane's position
         a_lo[i] = (unsigned)((int64_t)rg * p.ldx * 4 + c * 16 + (int64_t)F32_BIAS) - 1024u * i;
     }
 #pragma unroll
@@ -216,14 +221,15 @@ void gemm_f32_tiled_kernel(const F32Params p) {
     // the K-loop holds none but the address updates, once per K-step: every read address is a register prepared here
     // (the swizzle included) plus an immediate offset, and the registers move from ring slot to ring slot by one add each.
     // X: lane (row li, slot lg) reads k = 2 ks + lg of its row, i.e. element 2 (ks & 1) + lg of chunk ks / 2: one
-    // two-address read per chunk and row block serves MFMA steps 2 c and 2 c + 1.  (4 lanes share a bank: with rows of 32
-    // floats and 16-byte placement no better is possible; the reads run a group ahead and are not waited for.)
-    unsigned a_at[MT][F32_BK / 4], b_at[NT];               // LDS byte addresses, of the slot that is read next
+    // two-address read per chunk and row block serves MFMA steps 2 c and 2 c + 1.  (4 lanes share a bank; the reads run a group
+    // ahead and are not waited for.)
+    unsigned a_at[MT][2], b_at[NT];                        // LDS byte addresses, of the slot that is read next
 #pragma unroll
     for (int x = 0; x < MT; ++x) {
         const int r = wm * (32 * MT) + x * 32 + li;
 #pragma unroll
-        for (int c = 0; c < F32_BK / 4; ++c) a_at[x][c] = smem_lds + (unsigned)(r * 32 + 4 * (c ^ (r & 7)) + lg) * 4u;
+        for (int c = 0; c < 2; ++c)                        // + 256 per pair of chunks
+            a_at[x][c] = smem_lds + (unsigned)((r >> 3) * 1024 + (r & 7) * 32 + 16 * (c ^ swizzle(r)) + 4 * lg);
     }
 #pragma unroll
     for (int y = 0; y < NT; ++y) {
@@ -244,8 +250,9 @@ void gemm_f32_tiled_kernel(const F32Params p) {
     auto read_one = [&](int set, int g, int r) __attribute__((always_inline)) {
         if (r < 2 * MT) {
             const int h = r / MT, x = r % MT;
-            fa[set][2 * h][x] = lds_f32(a_at[x][g * (GROUP / 2) + h]);
-            fa[set][2 * h + 1][x] = lds_f32(a_at[x][g * (GROUP / 2) + h] + 8);
+            const int c = g * (GROUP / 2) + h, pair = 256 * (c / 2);
+            fa[set][2 * h][x] = lds_f32(a_at[x][c % 2] + pair);
+            fa[set][2 * h + 1][x] = lds_f32(a_at[x][c % 2] + pair + 8);
         } else {
             const int q = 2 * ((r - 2 * MT) / NT), y = (r - 2 * MT) % NT, ks = g * GROUP + q;
             fb[set][q][y] = lds_f32(b_at[y] + 1024 * ks);
@@ -258,7 +265,7 @@ void gemm_f32_tiled_kernel(const F32Params p) {
 #pragma unroll
         for (int x = 0; x < MT; ++x)
 #pragma unroll
-            for (int c = 0; c < F32_BK / 4; ++c) a_at[x][c] += step;
+            for (int c = 0; c < 2; ++c) a_at[x][c] += step;
 #pragma unroll
         for (int y = 0; y < NT; ++y) b_at[y] += step;
     };
@@ -351,6 +358,28 @@ void gemm_f32_tiled_kernel(const F32Params p) {
         }
 }
 
+// LOOP (small tile, more than 512 items): two workgroups per compute unit, and each goes on with every 512th item, so that the
+// items behind the last whole round lie on different compute units.  As workgroups of their own they went in pairs to the
+// units that were free first, on which they shared the matrix pipes while other units stood still: 77 x 4096 at K = 4096, 768
+// items, 43 -> 36 us; 600 x 2048 at K = 6144, 1216 items, 137 -> 134 us.  Up to 512 items the loop only costs (one row of
+// 4096 x 4096 19.0 -> 19.4 us), so those launches are compiled without it, as is the large tile.
+constexpr int F32_SMALL_GRID = 2 * 256;
+
+template <int LEVELS, int MT, int NT, int WN, bool LOOP>
+__global__ __launch_bounds__(256, MT == 1 ? 2 : 1)
+void gemm_f32_tiled_kernel(const F32Params p) {
+    if (LOOP) {
+        const unsigned items = (unsigned)(p.tiles_m * p.tiles_n * p.shards);
+        for (unsigned id = blockIdx.x; id < items; id += gridDim.x) {
+            if (id != blockIdx.x)                          // no wavefront still reads the slots that are loaded next
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            gemm_f32_item<LEVELS, MT, NT, WN>(p, (int)id);
+        }
+    } else {
+        gemm_f32_item<LEVELS, MT, NT, WN>(p, (int)blockIdx.x);
+    }
+}
+
 bool gemm_f32_tiled_supports(const GemmArgs &a) {
     const int per = a.ns / a.P;
     // Whole 16-byte chunks of a row of W are fetched, so N has to be a multiple of 4; a lane's byte offset inside a
@@ -368,20 +397,34 @@ hipError_t launch_gemm_f32_reference(const GemmArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int LEVELS, int MT, int NT, int WN>
+template <int LEVELS, int MT, int NT, int WN, bool LOOP>
 static hipError_t launch_f32_levels(const F32Params &p, unsigned grid, hipStream_t s) {
     constexpr int LDS_BYTES = F32_RING * (32 * MT * (4 / WN) * F32_BK * 4 + F32_B_BYTES);
     static std::atomic<unsigned> done{0};                 // bit d: the LDS attribute is set on device d
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 32) dev = 32;
     if (dev >= 32 || !((done.load(std::memory_order_relaxed) >> dev) & 1u)) {
-        hipError_t e = hipFuncSetAttribute((const void *)gemm_f32_tiled_kernel<LEVELS, MT, NT, WN>,
+        hipError_t e = hipFuncSetAttribute((const void *)gemm_f32_tiled_kernel<LEVELS, MT, NT, WN, LOOP>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
         if (e != hipSuccess) return e;
         if (dev < 32) done.fetch_or(1u << dev, std::memory_order_relaxed);
     }
-    hipLaunchKernelGGL((gemm_f32_tiled_kernel<LEVELS, MT, NT, WN>), dim3(grid), dim3(256), LDS_BYTES, s, p);
+    hipLaunchKernelGGL((gemm_f32_tiled_kernel<LEVELS, MT, NT, WN, LOOP>), dim3(grid), dim3(256), LDS_BYTES, s, p);
     return hipGetLastError();
+}
+
+template <int MT, int NT, int WN, bool LOOP>
+static hipError_t launch_f32_grid(const F32Params &p, unsigned grid, hipStream_t s) {
+    int levels = 0;
+    while ((1 << levels) < p.ns_per_shard) ++levels;
+    switch (levels) {
+        case 0: return launch_f32_levels<0, MT, NT, WN, LOOP>(p, grid, s);
+        case 1: return launch_f32_levels<1, MT, NT, WN, LOOP>(p, grid, s);
+        case 2: return launch_f32_levels<2, MT, NT, WN, LOOP>(p, grid, s);
+        case 3: return launch_f32_levels<3, MT, NT, WN, LOOP>(p, grid, s);
+        case 4: return launch_f32_levels<4, MT, NT, WN, LOOP>(p, grid, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 template <int MT, int NT, int WN>
@@ -403,16 +446,8 @@ static hipError_t launch_f32_shape(const GemmArgs &a, hipStream_t s) {
     int64_t work = (int64_t)p.tiles_m * p.tiles_n * a.P;
     if (BM == 128) work = (work + 7) / 8 * 8;              // an eighth per XCD
     if (work > 0x7fffffff) return hipErrorInvalidValue;
-    int levels = 0;
-    while ((1 << levels) < p.ns_per_shard) ++levels;
-    switch (levels) {
-        case 0: return launch_f32_levels<0, MT, NT, WN>(p, (unsigned)work, s);
-        case 1: return launch_f32_levels<1, MT, NT, WN>(p, (unsigned)work, s);
-        case 2: return launch_f32_levels<2, MT, NT, WN>(p, (unsigned)work, s);
-        case 3: return launch_f32_levels<3, MT, NT, WN>(p, (unsigned)work, s);
-        case 4: return launch_f32_levels<4, MT, NT, WN>(p, (unsigned)work, s);
-        default: return hipErrorInvalidValue;
-    }
+    if (BM == 32 && work > F32_SMALL_GRID) return launch_f32_grid<MT, NT, WN, BM == 32>(p, F32_SMALL_GRID, s);
+    return launch_f32_grid<MT, NT, WN, false>(p, (unsigned)work, s);
 }
 
 // variant: VARIANT_T128 asks for the 128-row tile, VARIANT_T32 / VARIANT_T64 for the 32-row tile.
