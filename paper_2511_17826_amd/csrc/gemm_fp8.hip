@@ -570,7 +570,7 @@ hipError_t launch_tiled_fmt(const GemmArgs &a, const Mxfp4Scales *sc, hipStream_
     const size_t lds = (size_t)RING8 * STAGE8;
     const void *out = p.partials ? (const void *)p.partials : p.Y;
     const int64_t ld_bytes = p.partials ? (int64_t)a.N * 4 : a.ldy * (p.y_bf16 ? 2 : 4);
-    p.vector_stores = ((reinterpret_cast<uintptr_t>(out) & 15) == 0) && (ld_bytes % 16 == 0);
+    p.vector_stores = ((reinterpret_cast<uintptr_t>(out) & 15) == 0) && (ld_bytes % 16 == 0) && ld_bytes < kMaxVectorRowBytes;
     p.stream_stores = a.partials != nullptr && (int64_t)a.P * a.M * a.N * 4 > ((int64_t)192 << 20);
     const int levels = levels_for(p.ns_per_shard);
     int dev = 0;

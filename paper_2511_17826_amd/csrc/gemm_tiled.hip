@@ -546,7 +546,7 @@ static hipError_t launch_shape(const GemmArgs &a, hipStream_t s) {
     {
         const void *out = p.partials ? (const void *)p.partials : p.Y;
         const int64_t ld_bytes = p.partials ? (int64_t)a.N * 4 : a.ldy * (p.y_bf16 ? 2 : 4);   // act: 16-byte chunks of 8 channels
-        p.vector_stores = ((reinterpret_cast<uintptr_t>(out) & 15) == 0) && (ld_bytes % 16 == 0);
+        p.vector_stores = ((reinterpret_cast<uintptr_t>(out) & 15) == 0) && (ld_bytes % 16 == 0) && ld_bytes < kMaxVectorRowBytes;
         // Partials of many shards exceed the 256 MiB memory-side cache before the combine reads them: written around
         // the caches they do not evict the operands (P = 8 at 4096^2: 257 -> 170 us).  Fewer planes stay cached for
         // their reader, so those keep ordinary stores.

@@ -12,6 +12,10 @@ namespace tbik {
 // aligned.  Stored value by value instead, two or four bytes a lane, the last row tile held a call up by 3 to 4 us:
 // 1000 x 4096 x 4096 in 8 bits 25.0 us, 21.1 so; in bf16 42.1 and 39.3.
 // (Full tiles keep code of their own: one copy of the two, with the rows clamped or with the choice inside, cost them 1 %.)
+// A lane's offset inside a block row is 32 bits: with rows further apart than this (31 of them reach 2^31 bytes) a tile is
+// stored value by value, with 64-bit addresses.
+constexpr int64_t kMaxVectorRowBytes = (int64_t)1 << 26;
+
 typedef unsigned int tile_u32x4 __attribute__((ext_vector_type(4)));
 
 template <int MT, int NT>

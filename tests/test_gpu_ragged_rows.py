@@ -94,3 +94,30 @@ def test_low_bit(kind, height):
             gemm(view)
             assert _equal(view, want.to(out_dtype)) and _guards_untouched(t), (M, out_dtype)
         tb.tbik_set_gemm_variant(tb.VARIANT_AUTO)
+
+
+@pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("kind", ["bf16", "fp8", "mxfp8", "mxfp6", "mxfp4"])
+def test_output_rows_far_apart(kind, out_dtype):
+    """Output rows so far apart that an offset inside the tile passes 32 bits."""
+    M = 31
+    ld = 72_000_000 if out_dtype == torch.bfloat16 else 36_000_000                  # the last row begins 4.32 GB on
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M)
+    out = torch.empty((M - 1) * ld + N, dtype=out_dtype, device="cuda").as_strided((M, N), (ld, 1))
+    out.fill_(-7.0)
+    if kind == "bf16":
+        X = torch.randn((M, K), generator=g, device="cuda").to(torch.bfloat16)
+        W = torch.randn((K, N), generator=g, device="cuda").to(torch.bfloat16)
+        want = tb.tbik_gemm_reference(X, W, LEAF, 1, 1, out_dtype=torch.float32)[1]
+        gemm = lambda: tb.tbik_gemm(X, W, LEAF, 1, out=out)
+    else:
+        (X, Xs), (W, Ws) = _low_bit(kind, M, g), _low_bit(kind, N, g)
+        args = (X, W) if kind == "fp8" else (X, Xs, W, Ws)
+        want = getattr(tb, "tbik_gemm_reference_" + kind)(*args, LEAF, 1)[0]
+        gemm = lambda: getattr(tb, "tbik_gemm_" + kind)(*args, LEAF, 1, out=out)
+    for variant in (tb.VARIANT_T32, tb.VARIANT_T64, tb.VARIANT_T128, tb.VARIANT_AUTO):
+        tb.tbik_set_gemm_variant(variant)
+        out.fill_(-7.0)
+        gemm()
+        assert _equal(out, want.to(out_dtype)), variant
