@@ -115,6 +115,11 @@ int internal_split(int M, int N, int K, int ns) {
 // the best plan's in one piece 0.996 .. 1.008 from HBM, up to 1.29.  The rules' choice stays where the model promises less than
 // the margin.  A tile of 64 rows that the model took too cheap was split where the rule is quicker by a tenth (768 rows of
 // 4096 x 6144 from HBM 79 against 71 us, 64 now, cut behind 640).
+// 65 .. 96 rows of 16-bit operands may also be one tile of 96 rows, which multiplies a quarter less padding than one of 128 and
+// is split like it.  From HBM / from the cache, 77 rows: 4096 x 6144 21.0 -> 18.3 / 16.8 -> 15.6 us, K = 12288 27.9 -> 26.6 /
+// 25.1 -> 24.4, 5120 x 7168 23.0 -> 21.9 / 19.8 -> 19.1; 65 rows at K = 14336 36.4 -> 29.0 / 26.8 -> 26.1 (two tiles of 64 before).
+// Its step is what keeps 4096 x 4096 with two tiles of 64 split in four (from the cache 13.2 us, 14.0 as 96; equal from HBM).
+// More than one tile of 96 was not measured and is not offered.
 enum Operands { OPERANDS_16BIT, OPERANDS_FP8, OPERANDS_MXFP8, OPERANDS_MXFP4, OPERANDS_MXFP6 };
 struct TilePlan {
     int rows, split;
@@ -122,18 +127,18 @@ struct TilePlan {
 struct TileModel {
     int stage_k;                        // k of an LDS stage
     double bytes_per_k;
-    double step[3], fill;               // us: a stage of a 32-, 64-, 128-row tile; pipeline fill and epilogue of an item
+    double step[4], fill;               // us: a stage of a 32-, 64-, 96- (16-bit only), 128-row tile; pipeline fill and epilogue of an item
     double intake;                      // bytes of W per us and compute unit, in thousands
     double combine, rate;               // us; bytes of planes per us, in millions
     double retile;                      // us: the scales' re-tiling from 128 rows on
     double margin;                      // the rules' choice stays where the model promises less than this
 };
 constexpr TileModel kTileModels[] = {
-    {64, 2.0, {0.005, 0.25, 0.525}, 5.9, 38.5, 3.95, 12.0, 0.0, 1.04},
-    {128, 1.0, {0.01, 0.24, 0.33}, 3.1, 51.0, 2.7, 1.2, 0.0, 1.04},
-    {128, 1.0, {0.0, 0.185, 0.356}, 3.6, 42.0, 4.8, 2.5, 4.0, 1.08},
-    {256, 0.5, {0.325, 0.335, 0.574}, 4.1, 31.4, 2.64, 2.7, 4.0, 1.04},
-    {128, 0.75, {0.0, 0.0, 0.61}, 3.6, 36.0, 3.84, 2.5, 4.0, 1.0},       // one height; MXFP8's with its stage
+    {64, 2.0, {0.005, 0.25, 0.46, 0.525}, 5.9, 38.5, 3.95, 12.0, 0.0, 1.04},
+    {128, 1.0, {0.01, 0.24, 0.0, 0.33}, 3.1, 51.0, 2.7, 1.2, 0.0, 1.04},
+    {128, 1.0, {0.0, 0.185, 0.0, 0.356}, 3.6, 42.0, 4.8, 2.5, 4.0, 1.08},
+    {256, 0.5, {0.325, 0.335, 0.0, 0.574}, 4.1, 31.4, 2.64, 2.7, 4.0, 1.04},
+    {128, 0.75, {0.0, 0.0, 0.0, 0.61}, 3.6, 36.0, 3.84, 2.5, 4.0, 1.0},       // one height; MXFP8's with its stage
 };
 
 // Bytes of the fp32 planes of a K split.
@@ -149,13 +154,13 @@ struct PlanTimes {
         : m(model), M(rows_in_all), cols(((int64_t)N + 127) / 128), stages((double)K / m.stage_k),
           weights_us(128.0 * K * m.bytes_per_k / (m.intake * 1e3)), planes_us((double)M * N * 4.0 / (m.rate * 1e6)),
           retile_us(M >= 128 ? m.retile : 0.0) {}
-    int64_t row_tiles(int rows) const { return rows == 32 ? (M + 31) >> 5 : rows == 64 ? (M + 63) >> 6 : (M + 127) >> 7; }
+    int64_t row_tiles(int rows) const { return rows == 32 ? (M + 31) >> 5 : rows == 64 ? (M + 63) >> 6 : rows == 96 ? (M + 95) / 96 : (M + 127) >> 7; }
     double us(int64_t tiles, double step, int split, double per_split) const {      // per_split: 1 / split
         const double rounds = (double)((tiles * split + 255) >> 8);
         const double item = std::max(stages * per_split * step + m.fill, weights_us * per_split);
         return retile_us + rounds * item + (split > 1 ? m.combine + planes_us * split : 0.0);
     }
-    double step(int rows) const { return m.step[rows == 32 ? 0 : rows == 64 ? 1 : 2]; }
+    double step(int rows) const { return m.step[rows == 32 ? 0 : rows == 64 ? 1 : rows == 96 ? 2 : 3]; }
     double us(TilePlan p) const { return us(row_tiles(p.rows) * cols, step(p.rows), p.split, 1.0 / p.split); }
 };
 
@@ -196,8 +201,9 @@ TimedPlan tile_plan(Operands kind, int M, int N, int K, int ns, int only_split, 
     int first_split = only_split > 0 ? only_split : 1;
     while (only_split <= 0 && ns > 16 * (int64_t)first_split) first_split *= 2;         // a tile walks at most 16 superleaves
     const int last_split = only_split <= 0 ? std::min(ns, 16) : only_split <= 16 && ns / only_split <= 16 ? only_split : 0;
+    const bool one_tile_of_96 = kind == OPERANDS_16BIT && M > 64 && M <= 96;
     int64_t shorter = 0;
-    for (int rows = one_height ? 128 : 32; rows <= 128; rows *= 2) {
+    for (int rows = one_height ? 128 : 32; rows <= 128; rows += rows == 64 && !one_tile_of_96 ? 64 : 32) {
         const int64_t row_tiles = times.row_tiles(rows);
         if (row_tiles == shorter) break;                // a taller tile that does not save one costs more
         shorter = row_tiles;
@@ -320,6 +326,7 @@ int pick_variant(const GemmArgs &a, int rows) {      // rows: tile height for 16
     if (a.x_dtype == TBIK_F32)
         return !gemm_f32_tiled_supports(a) ? VARIANT_REFERENCE : f32_plan_at(a.M, a.N, a.K, a.P).rows == 32 ? VARIANT_T32 : VARIANT_T128;
     if (rows == 128 && gemm_tiled_supports(a, VARIANT_T128)) return VARIANT_T128;
+    if (rows == 96 && gemm_tiled_supports(a, VARIANT_T96)) return VARIANT_T96;
     if (rows >= 64 && gemm_tiled_supports(a, VARIANT_T64)) return VARIANT_T64;
     if (gemm_tiled_supports(a, VARIANT_T32)) return VARIANT_T32;
     if (gemm_tiled_supports(a, VARIANT_T128)) return VARIANT_T128;

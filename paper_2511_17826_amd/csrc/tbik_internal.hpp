@@ -138,6 +138,7 @@ int set_row_wait_limit(int polls);   // returns the previous limit
 // allocation.  The first call on a device looks the array's address up.  The caller has checked that the shape fits.
 hipError_t launch_row_reduce_static(const void *x, int x_dtype, void *out, int op, int M, int64_t V, hipStream_t s);
 
-enum { VARIANT_AUTO = 0, VARIANT_REFERENCE = 1, VARIANT_T128 = 2, VARIANT_T32 = 3, VARIANT_T64 = 4, VARIANT_COUNT = 5 };
+enum { VARIANT_AUTO = 0, VARIANT_REFERENCE = 1, VARIANT_T128 = 2, VARIANT_T32 = 3, VARIANT_T64 = 4, VARIANT_COUNT = 5,
+       VARIANT_T96 = 6 };                 // (the plan's choice only)
 
 }  // namespace tbik
