@@ -132,13 +132,14 @@ struct TileModel {
     double combine, rate;               // us; bytes of planes per us, in millions
     double retile;                      // us: the scales' re-tiling from 128 rows on
     double margin;                      // the rules' choice stays where the model promises less than this
+    double cut;                         // us: a batch stays whole where the model promises less than this from a cut (below)
 };
 constexpr TileModel kTileModels[] = {
-    {64, 2.0, {0.005, 0.25, 0.46, 0.525}, 5.9, 38.5, 3.95, 12.0, 0.0, 1.04},
-    {128, 1.0, {0.01, 0.24, 0.0, 0.33}, 3.1, 51.0, 2.7, 1.2, 0.0, 1.04},
-    {128, 1.0, {0.0, 0.185, 0.0, 0.356}, 3.6, 42.0, 4.8, 2.5, 4.0, 1.08},
-    {256, 0.5, {0.325, 0.335, 0.0, 0.574}, 4.1, 31.4, 2.64, 2.7, 4.0, 1.04},
-    {128, 0.75, {0.0, 0.0, 0.0, 0.61}, 3.6, 36.0, 3.84, 2.5, 4.0, 1.0},       // one height; MXFP8's with its stage
+    {64, 2.0, {0.005, 0.25, 0.46, 0.525}, 5.9, 38.5, 3.95, 12.0, 0.0, 1.04, 0.0},
+    {128, 1.0, {0.01, 0.24, 0.0, 0.33}, 3.1, 51.0, 2.7, 1.2, 0.0, 1.04, 1.375},
+    {128, 1.0, {0.0, 0.185, 0.0, 0.356}, 3.6, 42.0, 4.8, 2.5, 4.0, 1.08, 1.4},
+    {256, 0.5, {0.325, 0.335, 0.0, 0.574}, 4.1, 31.4, 2.64, 2.7, 4.0, 1.04, 1.9},
+    {128, 0.75, {0.0, 0.0, 0.0, 0.61}, 3.6, 36.0, 3.84, 2.5, 4.0, 1.0, 1.9},       // one height; MXFP8's with its stage
 };
 
 // Bytes of the fp32 planes of a K split.
@@ -223,8 +224,12 @@ TimedPlan tile_plan(Operands kind, int M, int N, int K, int ns, int only_split, 
 // rows of 4096 x 4096 in bf16 are 288 tiles of 128 rows, two rounds, 72 us; as 1024 rows and 76 rows 54 us.  (The rows of
 // a result do not depend on each other, so neither do their bits.)  Microscaling formats re-tile the scales of both pieces in one
 // launch, so a cut pays for it once: at K = 12288 and 1300 rows MXFP8 90.5 -> 82.3 us, MXFP4 59.6 -> 57.0, MXFP6 99.8 -> 95.2.
+// A cut that promises less than 5 % or less than the format's `cut` is not made.  Where those lines lie, promised / gained from
+// HBM, from the cache, us: 8-bit 1.37 / -1.2, -0.8 (1064 rows at K = 3072), 1.38 / +0.7 .. 4.0, +0.5 .. 2.2 (1152 .. 1280 rows of
+// 4096 x 4096, 838 .. 928 at N = 5120; at N = 6144 -0.7, +1.9); MXFP8 1.19 / -2.0, -1.2 (K = 1536), 1.61 / +1.0, +1.5 (K = 3072), 1.78 /
+// +4.3, +5.6 (674 rows of 4096 x 6144); MXFP4 1.82 / -0.2, -0.4 (1320 .. 1500 rows), 1.98 / +1.4, +1.7; MXFP6 2.44 /
+// +0.4, +1.1 (1029 rows at K = 2048).  For 16-bit operands 5 % is more than 2.1.
 constexpr double kPieceUs = 2.0;        // what a launch behind another costs
-constexpr double kCutUs = 1.9;          // (1300 .. 1536 rows of 4096 x 4096 in MXFP4 promise 1.8 and lose 0.5)
 struct BatchPlan {
     int last_rows;
     TilePlan first, last;               // of the rows before the last ones, of the last ones
@@ -242,7 +247,7 @@ BatchPlan batch_plan(Operands kind, int M, int N, int K, int ns, size_t room) {
     const TimedPlan first = tile_plan(kind, full, N, K, ns, 0, room), last = tile_plan(kind, rest, N, K, ns, 0, room);
     const double shared_us = rest >= 128 ? kTileModels[kind].retile : 0.0;      // the pieces' scales are re-tiled once
     const double saved_us = whole.us - (first.us + last.us - shared_us + kPieceUs);
-    if (saved_us <= 0.05 * whole.us || saved_us < kCutUs) return plan;
+    if (saved_us <= 0.05 * whole.us || saved_us < kTileModels[kind].cut) return plan;
     plan.planes = std::max(split_planes_bytes(full, N, first.plan.split), split_planes_bytes(rest, N, last.plan.split));
     plan.last_rows = rest;
     plan.first = first.plan;
