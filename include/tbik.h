@@ -500,6 +500,12 @@ int tbik_combine_residual_rmsnorm_f16(const float *partials, int P, const void *
  * 0 = choose from the shape (default); other values are listed in tbik_variant_name(). */
 int tbik_set_gemm_variant(int variant);
 const char *tbik_variant_name(int variant);      /* NULL past the last variant */
+/* What the GEMM calls launch for a shape (testing and tuning only; pure, no device is needed): for dense operands aligned to 16
+ * bytes and a workspace of the size advertised.  x_dtype names the operands; `scaled` tells tbik_gemm_mxfp8 from tbik_gemm_fp8.
+ * route holds four numbers for each of the one or two pieces that a batch is computed in (zeros: no second piece): its rows; the
+ * kernel, 0 the reference, 1 tiles, 2 slices (up to 32 rows of low-bit operands in one launch); rows of a tile and K split (tiles).
+ * Errors: NULL, SHAPE, DTYPE. */
+int tbik_gemm_route(tbik_dtype x_dtype, int scaled, int M, int N, int K, int leaf, int k_first, int route[8]);
 
 /* Forces one of the two attention kernels (testing and tuning only; the bits never depend on it):
  * 0 = default, 1 = two independent workgroups per compute unit, 2 = one workgroup whose two groups of wavefronts take

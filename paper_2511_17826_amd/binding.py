@@ -17,6 +17,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("TBIK_LIB_PATH") or os.path.join(_HERE, "libtbik.so")
 
 TBIK_F32, TBIK_BF16, TBIK_F16 = 0, 1, 2
+TBIK_MXFP4 = 5
 TBIK_SUM, TBIK_MAX, TBIK_LOGSOFTMAX = 0, 1, 2
 OK = 0
 
@@ -111,6 +112,7 @@ SIGNATURES = {
                                  C.c_float, C.c_int, C.c_void_p, C.c_size_t, C.c_void_p]),
     "tbik_attention_workspace_bytes": (C.c_size_t, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int]),
     "tbik_set_gemm_variant": (C.c_int, [C.c_int]),
+    "tbik_gemm_route": (C.c_int, [C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]),
     "tbik_set_attention_variant": (C.c_int, [C.c_int]),
     "tbik_set_row_wait_limit": (C.c_int, [C.c_int]),
     "tbik_variant_name": (C.c_char_p, [C.c_int]),
@@ -828,6 +830,16 @@ def tbik_set_attention_variant(variant: int):
 
 def tbik_set_gemm_variant(variant: int):
     _check(lib().tbik_set_gemm_variant(variant), "tbik_set_gemm_variant")
+
+
+def gemm_route(kind: str, M, N, K, leaf, k_first=1):
+    """What the GEMM calls of a shape launch, one (rows, "reference" | "tiles" | "slices", rows of a tile, K split) per piece of the
+    batch (testing and tuning; needs no GPU).  kind: "f32", "bf16", "fp16", "fp8", "mxfp8", "mxfp6" or "mxfp4"."""
+    dtype = {"f32": TBIK_F32, "bf16": TBIK_BF16, "fp16": TBIK_F16, "fp8": TBIK_FP8_E4M3, "mxfp8": TBIK_FP8_E4M3,
+             "mxfp6": TBIK_FP6_E2M3, "mxfp4": TBIK_MXFP4}[kind]
+    r = (C.c_int * 8)()
+    _check(lib().tbik_gemm_route(dtype, int(kind == "mxfp8"), M, N, K, leaf, k_first, r), "tbik_gemm_route")
+    return [(r[i], ("reference", "tiles", "slices")[r[i + 1]], r[i + 2], r[i + 3]) for i in (0, 4) if r[i]]
 
 
 def variant_names():

@@ -338,8 +338,20 @@ int pick_variant(const GemmArgs &a, int rows) {      // rows: tile height for 16
     return VARIANT_REFERENCE;
 }
 
-// A small batch of a low-bit format goes to the kernel that needs one launch, unless a variant is forced.
-bool takes_slices(const GemmArgs &a, const Mxfp4Scales *sc) { return g_forced_variant.load() == VARIANT_AUTO && gemm_slice_takes(a, sc); }
+// The kernel for a piece of a low-bit call (split: its plan's).  A small batch goes to the one that needs one launch, unless a
+// variant is forced.
+enum { KERNEL_REFERENCE, KERNEL_TILED, KERNEL_SLICES };
+int low_bit_kernel(const GemmArgs &a, const Mxfp4Scales *sc, int split) {
+    const int forced = g_forced_variant.load();
+    if (forced == VARIANT_AUTO && gemm_slice_takes(a, sc)) return KERNEL_SLICES;
+    GemmArgs probe = a;
+    probe.P = split;
+    const bool tiled = a.x_dtype == TBIK_MXFP4                                   ? gemm_mxfp4_tiled_supports(probe, *sc)
+                       : a.x_dtype == TBIK_FP6_E2M3 || a.x_dtype == TBIK_FP6_E3M2 ? gemm_mxfp6_tiled_supports(probe, *sc)
+                       : sc                                                       ? gemm_mxfp8_tiled_supports(probe, *sc)
+                                                                                  : gemm_fp8_tiled_supports(probe);
+    return forced != VARIANT_REFERENCE && tiled ? KERNEL_TILED : KERNEL_REFERENCE;
+}
 
 // 16-bit output type that goes with an operand format.
 inline bool legal_y_dtype(int y_dtype, int x_dtype) { return y_dtype == TBIK_F32 || y_dtype == x_dtype; }
@@ -563,10 +575,9 @@ int tbik_gemm_fp8(const void *X, int64_t ldx, const void *Wt, int64_t ldwt, void
         void *y = static_cast<char *>(Y) + (int64_t)m0 * ldy * (y_dtype == TBIK_F32 ? 4 : 2);
         GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
                    (int)y_dtype, m, N, K, sl, ns, 1, (int)x_dtype, 0};
-        if (takes_slices(a, nullptr)) return launch_gemm_slice(a, nullptr, s);
-        GemmArgs probe = a;
-        probe.P = plan.split;
-        if (g_forced_variant.load() == VARIANT_REFERENCE || !gemm_fp8_tiled_supports(probe)) return launch_gemm_fp8_reference(a, s);
+        const int kernel = low_bit_kernel(a, nullptr, plan.split);
+        if (kernel == KERNEL_SLICES) return launch_gemm_slice(a, nullptr, s);
+        if (kernel == KERNEL_REFERENCE) return launch_gemm_fp8_reference(a, s);
         if (plan.split == 1) return launch_gemm_fp8_tiled(a, plan.rows, s);
         a.partials = reinterpret_cast<float *>(workspace);
         a.Y = nullptr;
@@ -686,10 +697,9 @@ int tbik_gemm_mxfp4(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
         GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
                    (int)y_dtype, m, N, K, sl, ns, 1, TBIK_MXFP4, 0};
         const Mxfp4Scales sc = scales.plain(m0);
-        if (takes_slices(a, &sc)) return launch_gemm_slice(a, &sc, s);
-        GemmArgs probe = a;
-        probe.P = plan.split;
-        if (g_forced_variant.load() == VARIANT_REFERENCE || !gemm_mxfp4_tiled_supports(probe, sc)) return launch_gemm_mxfp4_reference(a, sc, s);
+        const int kernel = low_bit_kernel(a, &sc, plan.split);
+        if (kernel == KERNEL_SLICES) return launch_gemm_slice(a, &sc, s);
+        if (kernel == KERNEL_REFERENCE) return launch_gemm_mxfp4_reference(a, sc, s);
         Mxfp4Scales tiled;
         hipError_t pe = scales.for_tiles(m0, &tiled, s);
         if (pe != hipSuccess) return pe;
@@ -787,10 +797,9 @@ int tbik_gemm_mxfp8(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
         GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
                    (int)y_dtype, m, N, K, sl, ns, 1, (int)x_dtype, 0};
         const Mxfp4Scales sc = scales.plain(m0);
-        if (takes_slices(a, &sc)) return launch_gemm_slice(a, &sc, s);
-        GemmArgs probe = a;
-        probe.P = plan.split;
-        if (g_forced_variant.load() == VARIANT_REFERENCE || !gemm_mxfp8_tiled_supports(probe, sc)) return launch_gemm_mxfp8_reference(a, sc, s);
+        const int kernel = low_bit_kernel(a, &sc, plan.split);
+        if (kernel == KERNEL_SLICES) return launch_gemm_slice(a, &sc, s);
+        if (kernel == KERNEL_REFERENCE) return launch_gemm_mxfp8_reference(a, sc, s);
         Mxfp4Scales tiled;
         hipError_t pe = scales.for_tiles(m0, &tiled, s);
         if (pe != hipSuccess) return pe;
@@ -891,10 +900,9 @@ int tbik_gemm_mxfp6(const void *X, int64_t ldx, const void *Xs, int64_t ldxs, co
         GemmArgs a{(const uint16_t *)(static_cast<const char *>(X) + (int64_t)m0 * ldx), ldx, (const uint16_t *)Wt, ldwt, nullptr, y, ldy,
                    (int)y_dtype, m, N, K, sl, ns, 1, (int)x_dtype, 0};
         const Mxfp4Scales sc = scales.plain(m0);
-        if (takes_slices(a, &sc)) return launch_gemm_slice(a, &sc, s);
-        GemmArgs probe = a;
-        probe.P = plan.split;
-        if (g_forced_variant.load() == VARIANT_REFERENCE || !gemm_mxfp6_tiled_supports(probe, sc)) return launch_gemm_mxfp6_reference(a, sc, s);
+        const int kernel = low_bit_kernel(a, &sc, plan.split);
+        if (kernel == KERNEL_SLICES) return launch_gemm_slice(a, &sc, s);
+        if (kernel == KERNEL_REFERENCE) return launch_gemm_mxfp6_reference(a, sc, s);
         Mxfp4Scales tiled;
         hipError_t pe = scales.for_tiles(m0, &tiled, s);
         if (pe != hipSuccess) return pe;
@@ -1181,6 +1189,47 @@ int tbik_set_row_wait_limit(int polls) { return set_row_wait_limit(polls); }
 int tbik_set_gemm_variant(int variant) {
     if (variant < 0 || variant >= VARIANT_COUNT) return TBIK_ERR_UNSUPPORTED;
     g_forced_variant.store(variant);
+    return TBIK_OK;
+}
+
+int tbik_gemm_route(tbik_dtype x_dtype, int scaled, int M, int N, int K, int leaf, int k_first, int route[8]) {
+    int sl, ns;
+    int rc = check_tree(M, N, K, leaf, k_first, 1, &sl, &ns);
+    if (rc != TBIK_OK) return rc;
+    const int t = (int)x_dtype;
+    const bool wide = t == TBIK_F32 || t == TBIK_BF16 || t == TBIK_F16;
+    if (!route) return TBIK_ERR_NULL;
+    if (!wide && !is_fp8(t) && t != TBIK_MXFP4 && t != TBIK_FP6_E2M3 && t != TBIK_FP6_E3M2) return TBIK_ERR_DTYPE;
+    if (!wide && sl % 64 != 0) return TBIK_ERR_SHAPE;
+    std::fill(route, route + 8, 0);
+    if (M == 0 || N == 0) return TBIK_OK;
+    const bool mx = !wide && (scaled || !is_fp8(t));
+    const int64_t ld = wide ? K : t == TBIK_MXFP4 ? K / 2 : is_fp8(t) ? K : (int64_t)K * 3 / 4;     // dense rows of X
+    uint8_t *const dense = reinterpret_cast<uint8_t *>((uintptr_t)256);                             // asked for its alignment only
+    const Mxfp4Scales sc{dense, (K / 32 + 3) / 4 * 4, dense, (K / 32 + 3) / 4 * 4};
+    int *out = route;
+    auto note = [&](int, int m, TilePlan plan) {
+        GemmArgs a{reinterpret_cast<const uint16_t *>(dense), ld, reinterpret_cast<const uint16_t *>(dense), wide ? N : ld, nullptr, dense, N,
+                   t, m, N, K, sl, ns, 1, t, 0};
+        out[0] = m;
+        if (wide) {
+            GemmArgs probe = a;
+            probe.P = plan.split;
+            const int v = pick_variant(probe, plan.rows);
+            out[1] = v == VARIANT_REFERENCE ? KERNEL_REFERENCE : KERNEL_TILED;
+            out[2] = v == VARIANT_T128 ? 128 : v == VARIANT_T96 ? 96 : v == VARIANT_T64 && t != TBIK_F32 ? 64 : 32;
+        } else {
+            out[1] = low_bit_kernel(a, mx ? &sc : nullptr, plan.split);
+            out[2] = plan.rows;
+        }
+        out[3] = plan.split;
+        if (out[1] != KERNEL_TILED) out[2] = out[3] = 0;
+        out += 4;
+        return hipSuccess;
+    };
+    if (t == TBIK_F32) (void)note(0, M, {0, f32_plan(M, N, K, ns).split});
+    else (void)in_pieces(wide ? OPERANDS_16BIT : t == TBIK_MXFP4 ? OPERANDS_MXFP4 : !is_fp8(t) ? OPERANDS_MXFP6 : mx ? OPERANDS_MXFP8 : OPERANDS_FP8,
+                         M, N, K, ns, SIZE_MAX, note);
     return TBIK_OK;
 }
 

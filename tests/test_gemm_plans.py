@@ -1,5 +1,5 @@
 """The plans that GEMM calls follow, seen on the host (no device is needed): which batches are cut into two pieces, by the planes
-that a call asks for."""
+that a call asks for, and which kernel, tile and split each piece gets."""
 import os
 
 import pytest
@@ -32,3 +32,39 @@ def test_mxfp8_batches_are_cut(L, M, N):
 
 def test_batches_that_a_cut_does_not_pay_for_stay_whole(L):
     assert L.tbik_gemm_fp8_workspace_bytes(1064, 4096, 3072, 768, 1) == 0
+
+
+def route(*shape):
+    from paper_2511_17826_amd import binding
+    return binding.gemm_route(*shape)
+
+
+def test_routes(L):
+    assert route("bf16", 77, 4096, 12288, 256, 3) == [(77, "tiles", 96, 8)]
+    assert route("bf16", 97, 4096, 12288, 256, 3) == [(97, "tiles", 128, 8)]
+    assert route("fp16", 1100, 4096, 4096, 256, 1) == [(1024, "tiles", 128, 1), (76, "tiles", 64, 4)]
+    assert route("bf16", 5, 12, 256, 256, 1) == [(5, "reference", 0, 0)]
+    assert route("f32", 600, 2048, 6144, 128, 3) == [(600, "tiles", 32, 4)]
+    assert route("fp8", 16, 4096, 12288, 256, 3) == [(16, "slices", 0, 0)]
+    assert route("fp8", 33, 4096, 4096, 256, 1) == [(33, "tiles", 32, 4)]
+    assert route("fp8", 16, 4096, 4096, 64, 1) == [(16, "reference", 0, 0)]          # superleaves shorter than a stage
+    assert route("mxfp6", 4097, 1024, 2048, 256, 1) == [(4096, "tiles", 128, 1), (1, "slices", 0, 0)]
+    assert route("mxfp4", 0, 1024, 2048, 256, 1) == []
+
+
+def test_a_forced_variant_is_what_the_route_tells(L):
+    from paper_2511_17826_amd import binding as tb
+    try:
+        tb.tbik_set_gemm_variant(tb.VARIANT_T64)
+        assert route("fp8", 16, 4096, 4096, 256, 1)[0][1:3] == ("tiles", 64) and route("bf16", 77, 4096, 12288, 256, 3)[0][2] == 64
+        tb.tbik_set_gemm_variant(tb.VARIANT_REFERENCE)
+        assert route("mxfp4", 16, 4096, 4096, 256, 1)[0][1] == "reference"
+    finally:
+        tb.tbik_set_gemm_variant(tb.VARIANT_AUTO)
+
+
+def test_route_arguments(L):
+    import ctypes as C
+    r = (C.c_int * 8)()
+    assert L.tbik_gemm_route(1, 0, 4, 256, 500, 64, 1, r) == 2 and L.tbik_gemm_route(9, 0, 4, 256, 512, 64, 1, r) == 4
+    assert L.tbik_gemm_route(1, 0, 4, 256, 512, 64, 1, None) == 1 and L.tbik_gemm_route(3, 0, 4, 256, 512, 32, 1, r) == 2

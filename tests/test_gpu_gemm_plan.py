@@ -53,9 +53,11 @@ def test_low_bit(kind, M):
 
 @pytest.mark.parametrize("M", [4097, 4100, 4224, 4300])
 def test_last_rows_as_a_call_of_their_own(M):
-    """A batch a little above full rounds of 128-row tiles, which 16-bit operands (MXFP8 and MXFP6 at 1 and 4 rows more, MXFP4
-    never) compute in two pieces here: rows equal those of other batch sizes."""
+    """A batch a little above full rounds of 128-row tiles, which 16-bit operands (and MXFP6 at 1 and 4 rows more, whose last
+    piece goes to slices) compute in two pieces here: rows equal those of other batch sizes."""
     Kp, Np = 2048, 1024                                           # 8 column tiles: 32 row tiles fill a round
+    pieces = {kind: len(tb.gemm_route(kind, M, Np, Kp, LEAF, 1)) for kind in ("bf16", "mxfp8", "mxfp4", "mxfp6")}
+    assert pieces == {"bf16": 2, "mxfp8": 1, "mxfp4": 1, "mxfp6": 2 if M <= 4100 else 1}
     g = torch.Generator(device="cuda:0")
     g.manual_seed(M)
     X = torch.randn((M, Kp), generator=g, device="cuda:0").to(torch.bfloat16)

@@ -50,6 +50,7 @@ def test_few_rows_equal_the_reference_kernel(name, tree):
     g = torch.Generator(device="cuda")
     g.manual_seed(1000 * tree + len(name))
     for M, N, pad in ((1, 16, 0), (15, 40, 16), (16, 4104, 0), (17, 8, 32), (31, 131, 0), (32, 272, 16)):
+        assert tb.gemm_route(kind, M, N, K, leaf, k_first) == [(M, "slices", 0, 0)]
         X, Xs = _operands(kind, fmt, M, K, pad, g)
         W, Ws = _operands(kind, fmt, N, K, pad, g)
         for out_dtype in (torch.float32, torch.bfloat16):
@@ -57,3 +58,39 @@ def test_few_rows_equal_the_reference_kernel(name, tree):
             y, want = _both(kind, fmt, X, Xs, W, Ws, leaf, k_first, out_dtype, out[1:M + 1, :N])
             assert torch.equal(y.contiguous().view(torch.uint8), want.view(torch.uint8)), (M, N, out_dtype)
             assert bool((out[0] == -7).all()) and bool((out[M + 1] == -7).all()) and bool((out[:, N:] == -7).all()), (M, N)
+
+
+# (kind, K, leaf, rows): 64 and 128 superleaves, eight and sixteen per wavefront: every level of a wavefront's own tree
+DEEP = [("fp8 e4m3", 8192, 128, (1, 16, 17, 32)), ("fp8 e4m3", 16384, 128, (1, 16, 17, 32)), ("fp8 e5m2", 16384, 128, (16, 17)),
+        ("mxfp8 e4m3", 8192, 128, (1, 16, 17, 32)), ("mxfp8 e4m3", 16384, 128, (1, 16)), ("mxfp6 e2m3", 16384, 256, (16, 17)),
+        ("mxfp6 e3m2", 32768, 256, (1, 16, 17)), ("mxfp4 e2m1", 16384, 256, (16, 17)), ("mxfp4 e2m1", 32768, 256, (1, 16, 17))]
+
+
+@pytest.mark.parametrize("name,K,leaf,rows", DEEP)
+def test_many_superleaves_equal_the_reference_kernel(name, K, leaf, rows):
+    kind, fmt = name.split()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K + len(name))
+    N = 4093
+    W, Ws = _operands(kind, fmt, N, K, 0, g)
+    X, Xs = _operands(kind, fmt, max(rows), K, 0, g)
+    for M in rows:
+        assert tb.gemm_route(kind, M, N, K, leaf) == [(M, "slices", 0, 0)]
+        out = torch.full((M + 2, N + 3), -7.0, dtype=torch.float32, device="cuda")
+        y, want = _both(kind, fmt, X[:M], Xs[:M], W, Ws, leaf, 1, torch.float32, out[1:M + 1, :N])
+        assert torch.equal(y.contiguous().view(torch.uint8), want.view(torch.uint8)), M
+        assert bool((out[0] == -7).all()) and bool((out[M + 1] == -7).all()) and bool((out[:, N:] == -7).all()), M
+
+
+@pytest.mark.parametrize("name,K,leaf", [("fp8 e4m3", 32768, 128), ("mxfp8 e5m2", 32768, 128), ("mxfp6 e2m3", 65536, 256), ("mxfp4 e2m1", 65536, 256)])
+def test_more_superleaves_than_a_wavefront_holds_go_to_tiles(name, K, leaf):
+    """256 superleaves would be 32 per wavefront."""
+    kind, fmt = name.split()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K)
+    M, N = 5, 264
+    assert tb.gemm_route(kind, M, N, K, leaf)[0][1] == "tiles"
+    (W, Ws), (X, Xs) = _operands(kind, fmt, N, K, 0, g), _operands(kind, fmt, M, K, 0, g)
+    out = torch.full((M, N), -7.0, dtype=torch.float32, device="cuda")
+    y, want = _both(kind, fmt, X, Xs, W, Ws, leaf, 1, torch.float32, out)
+    assert torch.equal(y.view(torch.uint8), want.view(torch.uint8))

@@ -14,6 +14,8 @@ pytestmark = pytest.mark.gpu
     ("mxfp4", 1300, 12288, 4096, 256, 3), ("mxfp4", 1500, 12288, 4096, 256, 3), ("mxfp4", 1100, 4096, 4096, 256, 1),
     ("mxfp4", 800, 4096, 6144, 256, 1), ("mxfp6", 2200, 4096, 4096, 256, 1), ("mxfp6", 1300, 12288, 4096, 256, 3)])
 def test_pieces_equal_the_reference_kernel(kind, M, K, N, leaf, k_first):
+    pieces = tb.gemm_route(kind, M, N, K, leaf, k_first)
+    assert len(pieces) == 2 and all(p[1] == "tiles" for p in pieces)
     g = torch.Generator(device="cuda")
     g.manual_seed(M)
     per = {"mxfp8": 32, "mxfp6": 24, "mxfp4": 16}[kind] * (K // 32)

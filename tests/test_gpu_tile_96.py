@@ -21,6 +21,7 @@ def test_bits(dtype, K, N, leaf, k_first):
     X = torch.randn((97, K), generator=g, device="cuda").to(dtype)
     want = ref(X, W, leaf, k_first, 1, out_dtype=torch.float32)[1]
     for M in (64, 65, 79, 95, 96, 97):
+        assert (tb.gemm_route("fp16" if f16 else "bf16", M, N, K, leaf, k_first)[0][2] == 96) == (65 <= M <= 96), M
         for out_dtype in (dtype, torch.float32):
             t = torch.full((M + 2, N), -7.0, dtype=out_dtype, device="cuda")
             gemm(X[:M], W, leaf, k_first, out=t[1:M + 1])
