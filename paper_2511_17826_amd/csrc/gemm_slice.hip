@@ -9,6 +9,7 @@
 // Eight wavefronts: with sixteen a wavefront's ring holds one or two steps, and 32 rows lose up to half (MXFP6).
 // The matrix instruction, the lanes' bytes and the scales are those of the tiled kernels (v_mfma_scale_f32_32x32x64_f8f6f4;
 // columns 16 .. 31 repeat 0 .. 15), so the bits are.
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -304,26 +305,64 @@ hipError_t launch_slice_rows(const GemmArgs &a, const Mxfp4Scales &sc, hipStream
 
 // Where slices are the quicker way.  What bounds them is what a compute unit takes in: its 16 weight rows and the whole batch
 // (and, for 8-bit elements, a cache line per row and 128 k for the scales); the tiled kernels read less of the batch per
-// compute unit but pay a second launch and the planes' round trip where they split K.  Device time of a call in a HIP graph,
-// tiled kernel (with its combine) / slices, weights from HBM and from the memory-side cache, us:
-//   1 x 4096 x 4096    8-bit 9.4 / 6.2, 6.5 / 4.0   MXFP8 9.8 / 6.6, 6.9 / 4.7   MXFP6 11.0 / 5.8, 8.7 / 4.7   MXFP4 7.9 / 4.4, 6.7 / 3.6
-//   16 rows, K = 12288 8-bit 15.1 / 12.6, 13.4 / 9.8   MXFP8 17.5 / 16.0, 14.3 / 10.9   MXFP6 18.1 / 13.2   MXFP4 13.0 / 9.6
-//   32 rows, K = 12288 8-bit 15.5 / 15.9, 13.8 / 10.6   MXFP8 18.2 / 20.8, 14.9 / 14.3   MXFP6 19.5 / 16.6   MXFP4 14.4 / 12.1
-//   32 rows, K = 4096  8-bit 10.2 / 7.3   MXFP8 12.9 / 8.4, N = 6144 14.0 / 14.3, 9.7 / 10.5
-//   N = 12288          16 rows 8-bit 14.6 / 12.6, MXFP8 18.7 / 17.5; 32 rows 8-bit 17.6 / 18.3, 11.9 / 13.9, MXFP6 22.3 / 18.8, MXFP4 17.1 / 14.4
-//   N = 24576 (the tiled kernels do not split there): 16 rows 8-bit 24.6 / 22.3, 17.8 / 17.0, MXFP8 30.0 / 31.3, 18.9 / 25.0, MXFP4 17.4 / 21.0
+// compute unit and spread K over up to 16 workgroups, but pay a second launch and the planes' round trip where they do.  So
+// slices begin ahead by that launch and lose with K:
+//   ahead = launch + K / 4096 (k + narrow min(N, 4096) / 4096 - (N > 4096 ? wide : 0) - rows M / 16)      us
+// More channels up to 4096 are free for slices (a workgroup per compute unit) and cost the tiles; above, workgroups share compute
+// units or wait for one.  The constants are those with which wrong choices cost least over 1868 timed pairs (1 .. 32 rows, K = 2048 ..
+// 24576, 256 .. 12288 channels; the geometric mean of weights from HBM and from the memory-side cache): the route takes at most 1.11 of
+// the quicker one's time, 1.001 in the mean (profiles/slices_or_tiles.csv).  Device time of a call in a HIP graph, tiled kernel
+// (with its combine) / slices, weights from HBM and from the cache, us:
+//   1 x 4096 x 4096       8-bit 9.4 / 6.0, 6.8 / 3.8      MXFP8 10.1 / 6.3, 7.4 / 4.7    MXFP6 10.2 / 5.8, 7.8 / 4.8     MXFP4 8.8 / 4.5, 6.9 / 3.5
+//   16 rows, K = 12288    8-bit 15.4 / 12.6, 15.1 / 9.2   MXFP8 17.8 / 16.4, 14.1 / 10.9 MXFP6 17.6 / 13.5, 13.4 / 10.1  MXFP4 13.0 / 9.6, 9.6 / 6.6
+//   32 rows, K = 12288    8-bit 16.1 / 16.4, 14.0 / 10.4                                 MXFP6 18.4 / 16.5, 14.3 / 11.7  MXFP4 14.7 / 11.9, 11.2 / 8.0
+//   with N = 6144 (tiles) 8-bit 20.9 / 28.6, 17.2 / 18.1                                                                 MXFP4 18.6 / 20.6, 13.7 / 14.8
+//   16 rows, K = 8192, N = 1024  8-bit 8.9 / 7.3, 7.3 / 4.7      MXFP8 10.7 / 9.0, 8.2 / 6.9       MXFP6 10.9 / 8.6, 8.5 / 6.8
+//   K = 24576 there (tiles)      8-bit 12.8 / 17.6, 9.5 / 10.5   MXFP8 16.5 / 27.3, 11.9 / 17.1    MXFP6 16.9 / 21.6, 11.7 / 12.9
+struct SliceGain {
+    double launch, k, narrow, wide, rows;
+};
+constexpr SliceGain kSliceGains[4][2] = {                                         // [format][17 .. 32 rows]
+    {{4.46, -0.87, 0.68, 0.44, 0.16}, {4.22, -1.01, 1.00, 2.14, 0.35}},           // 8-bit
+    {{3.05, -0.75, 1.08, 0.64, 0.82}, {7.21, -3.14, 1.02, 0.0, 0.39}},            // MXFP8
+    {{3.51, -0.55, 0.44, 0.34, 0.26}, {4.83, -0.88, 0.39, 1.09, 0.16}},           // MXFP4
+    {{3.74, -0.78, 0.60, 0.34, 0.19}, {4.80, -1.13, 0.82, 0.44, 0.26}},           // MXFP6
+};
+
+static bool slices_are_quicker(const GemmArgs &a, bool eight_bits, bool scaled) {
+    const bool second_group = a.M > 16, six_bits = a.x_dtype == TBIK_FP6_E2M3 || a.x_dtype == TBIK_FP6_E3M2;
+    const int64_t slices = slices_of(a.N);
+    // Not measured beyond these.
+    if (slices > (!second_group || !eight_bits ? 768 : scaled ? 256 : 384)) return false;
+    if (second_group && eight_bits && scaled && a.K > 8192) return false;
+    if (a.ns < 8) {
+        // Fewer superleaves than wavefronts: the other wavefronts idle, but the tiled kernels cannot spread K either.  One superleaf, 16
+        // rows, K = 4096: N = 4096 8-bit 14.3 / 8.3, 8.8 / 6.8, MXFP8 24.1 / 8.9, MXFP4 14.4 / 5.9; N = 12288 8-bit 16.4 / 24.6, 10.5 / 16.5,
+        // MXFP8 26.0 / 36.4, MXFP4 15.2 / 20.4.  Short K bears twice as many slices (N = 8192, K = 2048 in 8 bits 9.2 / 8.0, 6.3 / 4.7),
+        // and so do 17 .. 32 rows of MXFP4 (16.2 / 12.0, 9.9 / 9.6 at K = 4096).  MXFP6's tiles have 128 rows only: 26.9 / 20.3, 18.3 / 18.4 at
+        // N = 12288; at K = 512 6.4 / 7.2, 4.9 / 6.0.
+        if (slices <= 256) return true;
+        const bool four_bits = !eight_bits && !six_bits;
+        const int short_k = second_group ? (four_bits ? 4096 : 0) : four_bits ? 2048 : scaled ? 512 : 8192;
+        if (six_bits ? slices > 512 && a.K < 2048 && a.ns < 4
+                     : slices > std::max((a.K <= short_k ? 512 : 256) * a.ns, four_bits && second_group ? 512 : 0)) return false;
+        if (a.ns < 4) return true;
+    }
+    const SliceGain &g = kSliceGains[eight_bits ? (scaled ? 1 : 0) : six_bits ? 3 : 2][second_group];
+    const double ahead = g.launch + a.K * (1.0 / 4096) * (g.k + g.narrow * std::min(a.N, 4096) * (1.0 / 4096) - (a.N > 4096 ? g.wide : 0.0) - g.rows * a.M * (1.0 / 16));
+    return ahead > 0.0;
+}
+
 bool gemm_slice_takes(const GemmArgs &a, const Mxfp4Scales *sc) {
     const bool eight_bits = a.x_dtype == TBIK_FP8_E4M3 || a.x_dtype == TBIK_FP8_E5M2;
     if (a.M > 32 || a.P != 1 || !a.Y) return false;
-    if (slices_of(a.N) > (a.M <= 16 || !eight_bits ? 768 : sc ? 256 : 384)) return false;
-    if (a.M > 16 && eight_bits && sc && a.K > 8192) return false;
     if (a.superleaf % (eight_bits ? 128 : 256) != 0 || a.ns > 16 * SLICE_WAVES) return false;      // whole steps; four levels per wavefront
     if (a.ldx >= (1 << 22) || a.ldw >= (1 << 22)) return false;                     // 32-bit lane offsets
     if (sc) {
         auto a4 = [](const void *q) { return (reinterpret_cast<uintptr_t>(q) & 3) == 0; };
         if (!a4(sc->Xs) || !a4(sc->Ws) || sc->ldxs % 4 != 0 || sc->ldws % 4 != 0 || sc->ldxs >= (1 << 24) || sc->ldws >= (1 << 24)) return false;
     }
-    return true;
+    return slices_are_quicker(a, eight_bits, sc != nullptr);
 }
 
 hipError_t launch_gemm_slice(const GemmArgs &a, const Mxfp4Scales *sc, hipStream_t s) {

@@ -68,3 +68,21 @@ def test_route_arguments(L):
     r = (C.c_int * 8)()
     assert L.tbik_gemm_route(1, 0, 4, 256, 500, 64, 1, r) == 2 and L.tbik_gemm_route(9, 0, 4, 256, 512, 64, 1, r) == 4
     assert L.tbik_gemm_route(1, 0, 4, 256, 512, 64, 1, None) == 1 and L.tbik_gemm_route(3, 0, 4, 256, 512, 32, 1, r) == 2
+
+
+@pytest.mark.parametrize("kind,M,N,K,leaf,k_first,kernel", [
+    # (M, N, K and trees of the layers that the benchmark runs)
+    ("fp8", 1, 4096, 4096, 256, 1, "slices"), ("fp8", 32, 4096, 12288, 256, 3, "slices"), ("fp8", 32, 6144, 4096, 256, 1, "slices"),
+    ("mxfp8", 16, 4096, 12288, 256, 3, "slices"), ("mxfp6", 32, 4096, 12288, 256, 3, "slices"), ("mxfp4", 32, 4096, 12288, 256, 3, "slices"),
+    # long K on few channels: the tiled kernels spread it over more compute units (8-bit 15.1 us as slices, 11.1 as tiles)
+    ("fp8", 32, 1024, 16384, 256, 4, "tiles"), ("fp8", 32, 256, 12288, 256, 3, "tiles"), ("fp8", 16, 256, 24576, 512, 3, "tiles"),
+    ("mxfp8", 16, 1024, 16384, 256, 4, "tiles"), ("mxfp6", 32, 1024, 16384, 256, 4, "tiles"), ("mxfp4", 32, 1024, 24576, 512, 3, "tiles"),
+    ("mxfp4", 16, 1024, 16384, 256, 4, "slices"), ("fp8", 16, 4096, 16384, 256, 4, "slices"),
+    # more slices than compute units and long K: 28.6 us as slices, 20.9 as tiles
+    ("fp8", 32, 6144, 12288, 256, 3, "tiles"), ("mxfp4", 32, 6144, 12288, 256, 3, "tiles"),
+    # one and two superleaves: one and two of a workgroup's wavefronts work
+    ("fp8", 16, 4096, 4096, 4096, 1, "slices"), ("fp8", 16, 12288, 4096, 4096, 1, "tiles"), ("mxfp8", 1, 12288, 4096, 2048, 1, "tiles"),
+    ("mxfp8", 1, 6144, 4096, 2048, 1, "slices"), ("mxfp4", 32, 8192, 4096, 4096, 1, "slices"), ("mxfp6", 16, 12288, 4096, 4096, 1, "slices"),
+    ("fp8", 16, 8192, 2048, 2048, 1, "slices"), ("mxfp6", 16, 12288, 512, 512, 1, "tiles")])
+def test_slices_where_they_are_quicker(L, kind, M, N, K, leaf, k_first, kernel):
+    assert route(kind, M, N, K, leaf, k_first)[0][1] == kernel
