@@ -361,8 +361,9 @@ __device__ __forceinline__ void gemm_f32_item(const F32Params &p, const int id) 
 // LOOP (small tile, more than 512 items): two workgroups per compute unit, and each goes on with every 512th item, so that the
 // items behind the last whole round lie on different compute units.  As workgroups of their own they went in pairs to the
 // units that were free first, on which they shared the matrix pipes while other units stood still: 77 x 4096 at K = 4096, 768
-// items, 43 -> 36 us; 600 x 2048 at K = 6144, 1216 items, 137 -> 134 us.  Up to 512 items the loop only costs (one row of
-// 4096 x 4096 19.0 -> 19.4 us), so those launches are compiled without it, as is the large tile.
+// items, 43 -> 36 us; 600 x 2048 at K = 6144, 1216 items, 134.2 -> 132.7 us, the layout of X above included.
+// Up to 512 items the loop only costs (one row of 4096 x 4096 19.0 -> 19.4 us), so those launches are compiled without it, as is the
+// large tile.
 constexpr int F32_SMALL_GRID = 2 * 256;
 
 template <int LEVELS, int MT, int NT, int WN, bool LOOP>

@@ -286,13 +286,14 @@ hipError_t in_pieces(Operands kind, int M, int N, int K, int ns, size_t room, Pi
 }
 
 // fp32 operands: tile height and K split of a shape (pure), by a model of the time.  The fp32 MFMA is slow (a K-step of 32
-// takes a 128-row tile 1.9 us and a 32-row tile 0.585 us, of which two tiles side by side on a compute unit lose nothing),
-// so what decides is how evenly the work items fill 256 compute units: 600 x 2048 at K = 6144 is 80 tiles of 128 rows,
-// which a split in four turns into 320 items = two rounds, 197 us; as 304 tiles of 32 rows split in four it is 1216 items,
-// 137 us.  A combine costs 3 us and its planes' round trip at 5 TB/s.  (128-row tiles: one per compute unit at a time, whole
-// rounds.  32-row tiles: two, and a ragged last round costs about half.)  Constants fitted to 26 shapes of K = 6144 and 4096.
-// Over 84 shapes of 1 .. 1500 rows, each timed at every split and both heights (profiles/tile_split_plans.csv), the choice
-// takes 0.85 of the older rule's time in the geometric mean and nowhere more, and 1.004 of the best plan's in the mean, up to 1.12.
+// takes a 128-row tile 1.94 us and two 32-row tiles side by side on a compute unit 1.04), so what decides is how evenly the work
+// items fill 256 compute units: 600 x 2048 at K = 6144 is 80 tiles of 128 rows, which a split in four turns into 320 items = two
+// rounds, 198 us; as 304 tiles of 32 rows split in four it is 1216 items, 138 us.  128-row tiles are one per compute unit at a time,
+// whole rounds.  32-row tiles are dealt to 512 workgroups, two per compute unit: a last round of up to 256 of them leaves each a
+// compute unit to itself and takes 0.94 of 0.61 us a K-step, one of more 1.58 and a full one 1.70.  Over 84 shapes of 1 .. 1500 rows,
+// each timed at every split and both heights (profiles/tile_split_plans.csv), the model is within -5 .. +7 % of the chosen plan's
+// time; the choice takes 0.81 of the older rule's in the geometric mean and nowhere more, and 1.006 of the best plan's, 1.07 at most
+// (128 rows at K = 6144 37.1 against 34.6 us; 77 rows, in which the two heights are level, 36.0 before and 31.8 now).
 struct F32Plan {
     int rows, split;
     double us;
@@ -300,10 +301,11 @@ struct F32Plan {
 F32Plan f32_plan_at(int M, int N, int K, int split) {
     const int64_t cols = ((int64_t)N + 127) / 128, items128 = ((int64_t)M + 127) / 128 * cols * split, items32 = ((int64_t)M + 31) / 32 * cols * split;
     const double steps = K / 32.0 / split;
-    const double combine = split > 1 ? 3.0 + (double)split * M * N * 4.0 / 5e6 : 0.0;
-    const double rounds = (double)((items128 + 255) >> 8), load = (double)items32 / 256.0;
-    const double t128 = rounds * (steps * 1.9 + 4.0) + combine;
-    const double t32 = (items32 <= 256 ? 1.0 : 0.5 * (load + (double)((items32 + 255) >> 8))) * steps * 0.585 + 6.0 + combine;
+    const double combine = split > 1 ? 5.4 + (double)split * M * N * 4.0 / 2.8e6 : 0.0;
+    const int64_t last = items32 & 511;
+    const double rounds32 = 1.70 * (double)(items32 >> 9) + (last == 0 ? 0.0 : last <= 256 ? 0.94 : 1.58);
+    const double t128 = (double)((items128 + 255) >> 8) * (steps * 1.94 + 1.4) + combine;
+    const double t32 = rounds32 * steps * 0.61 + 3.4 + combine;
     return t32 < t128 ? F32Plan{32, split, t32} : F32Plan{128, split, t128};
 }
 F32Plan f32_plan(int M, int N, int K, int ns) {
@@ -315,12 +317,12 @@ F32Plan f32_plan(int M, int N, int K, int ns) {
         if (!best.rows || p.us < best.us) best = p;
     }
     if (!best.rows) return F32Plan{128, internal_split(M, N, K, ns), 0.0};
-    // Up to 64 rows the older rule's split of 32-row tiles stays where the model promises less than 4 %: 48 rows of 4096 x 4096
-    // split in eight take 25.0 us, split in four, which the model holds 2 % quicker, 26.5 .. 27.0.  (Above, 128-row tiles were
-    // the rule, and the model's choice is right by more than it says: 77 rows of the same 35.8 us against 43.6.)
+    // Up to 64 rows the older rule's split of 32-row tiles stays where the model promises less than 8 %.  4096 x 4096 from HBM / from
+    // the cache: 64 rows split in eight 28.4 / 25.6 us, in four, held level, 29.3 / 27.0; one row split in eight 19.6 / 16.1, in sixteen,
+    // held 4 % quicker, 20.5 / 18.6.  (Above, 128-row tiles were the rule, which leaves the model more to say.)
     if (M <= 64) {
         const F32Plan rule = f32_plan_at(M, N, K, internal_split(M, N, K, ns));
-        if (rule.rows == 32 && rule.us < 1.04 * best.us) return rule;
+        if (rule.rows == 32 && rule.us < 1.08 * best.us) return rule;
     }
     return best;
 }

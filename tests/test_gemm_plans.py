@@ -86,3 +86,9 @@ def test_route_arguments(L):
     ("fp8", 16, 8192, 2048, 2048, 1, "slices"), ("mxfp6", 16, 12288, 512, 512, 1, "tiles")])
 def test_slices_where_they_are_quicker(L, kind, M, N, K, leaf, k_first, kernel):
     assert route(kind, M, N, K, leaf, k_first)[0][1] == kernel
+
+
+@pytest.mark.parametrize("M,N,K,leaf,k_first", [(77, 2048, 6144, 128, 3), (1100, 2048, 6144, 128, 3), (600, 4096, 4096, 128, 1), (1100, 4096, 4096, 256, 1)])
+def test_fp32_batches_on_two_workgroups_per_compute_unit(L, M, N, K, leaf, k_first):
+    """A ragged last round of 32-row tiles costs what a model of 512 workgroups says, and these batches take them: 4 to 13 % less time."""
+    assert route("f32", M, N, K, leaf, k_first)[0][2] == 32
