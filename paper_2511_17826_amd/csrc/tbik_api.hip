@@ -104,22 +104,24 @@ int internal_split(int M, int N, int K, int ns) {
 //   rounds x max(stages x step[height] + fill, weight bytes of an item / intake) + (split ? combine + planes / rate : 0)
 // with rounds = work items / 256 compute units, rounded up.  What the two rules above miss is how evenly the items fill the
 // compute units and that a lower tile is cheaper than a padded one: 100 rows of 4096 x 4096 in 8-bit operands took 128-row
-// tiles split in eight, 18.9 us, and take 12.4 us as 32-row tiles split in two; 400 rows at K = 12288 in bf16 took 224 tiles
-// of 64 rows, 82 us, and take 61 us as 128-row tiles split in two.  The constants were fitted to measured times; they are not
+// tiles split in eight, 18.2 us from HBM and 15.0 from the cache, and take 14.5 and 10.9 us as unsplit 32-row tiles; 400 rows at K =
+// 12288 in bf16 took 224 tiles of 64 rows, 85 us, and take 61 us as 128-row tiles split in two.  The constants were fitted to measured times; they are not
 // physical rates one by one (the same planes move at 12 TB/s in one row and at 1.2 in another), and the time they give is
-// off by -41 .. +33 % for 16-bit operands, -55 .. +18 % for the others: they rank plans, no more.  Checked over 227 (16-bit)
+// off by -44 .. +33 % for 16-bit operands, -50 .. +20 % for the others: they rank plans, no more.  Checked over 292 (16-bit)
 // and 4 x 99 (low-bit) shapes of the tests' layers, 1 .. 4096 rows, each timed at every height and split, with weights from
 // HBM and with weights from the memory-side cache (profiles/tile_split_plans.csv).  The chosen plan, cuts included, takes of
-// the rules' time, from HBM / from the cache in the geometric mean: 0.940 / 0.943 (16-bit), 0.927 / 0.884 (8-bit), 0.964 / 0.922
-// (MXFP8), 0.924 / 0.890 (MXFP4), 0.949 / 0.936 (MXFP6), from HBM up to 1.08 (two runs of one plan differ by up to 5 %); of
-// the best plan's in one piece 0.996 .. 1.008 from HBM, up to 1.29.  The rules' choice stays where the model promises less than
-// the margin.  A tile of 64 rows that the model took too cheap was split where the rule is quicker by a tenth (768 rows of
-// 4096 x 6144 from HBM 79 against 71 us, 64 now, cut behind 640).
+// the rules' time, from HBM / from the cache in the geometric mean: 0.918 / 0.926 (16-bit), 0.935 / 0.904 (8-bit), 0.973 / 0.932
+// (MXFP8), 0.941 / 0.902 (MXFP4), 0.955 / 0.947 (MXFP6); from the cache nowhere more than 1.04, from HBM up to 1.09, but 1.21 for 77
+// rows of 4096 x 6144 in MXFP8 (32-row tiles unsplit 24.0 us against 19.9, from the cache 13.1 against 18.8) and 1.16 for 64 rows of
+// 4096 x 4096 in MXFP4.  Of the best plan's in one piece it takes 0.996 .. 1.014 in the mean, up to 1.22, 1.43 for those 77 rows (the
+// epilogue of ragged tiles has become quicker since the constants were fitted, most of all for plans of many 128-row items).  The
+// rules' choice stays where the model promises less than the margin.  A tile of 64 rows that the model took too cheap was split
+// where the rule is quicker by a tenth (768 rows of 4096 x 6144 from HBM 79 against 71 us, 64 now, cut behind 640).
 // 65 .. 96 rows of 16-bit operands may also be one tile of 96 rows, which multiplies a quarter less padding than one of 128 and
-// is split like it.  From HBM / from the cache, 77 rows: 4096 x 6144 21.0 -> 18.3 / 16.8 -> 15.6 us, K = 12288 27.9 -> 26.6 /
-// 25.1 -> 24.4, 5120 x 7168 23.0 -> 21.9 / 19.8 -> 19.1; 65 rows at K = 14336 36.4 -> 29.0 / 26.8 -> 26.1 (two tiles of 64 before).
-// Its step is what keeps 4096 x 4096 with two tiles of 64 split in four (from the cache 13.2 us, 14.0 as 96; equal from HBM).
-// More than one tile of 96 was not measured and is not offered.
+// is split like it.  From HBM / from the cache, 77 rows: 4096 x 6144 22.7 -> 19.2 / 17.4 -> 15.8 us, K = 12288 36.1 -> 31.3 /
+// 25.4 -> 24.7, 5120 x 7168 27.0 -> 23.6 / 20.3 -> 19.5; 65 rows at K = 14336 39.1 -> 32.8 / 27.2 -> 26.7.  Over 78 shapes of 65 .. 96 rows
+// (13 layers; HBM and cache together) its step of 0.46 gives 0.934 of the time without it, nowhere more than 1, and 1.001 of the best plan's;
+// 0.42 also takes 2048 x 4096, which loses 8 %, and 0.48 gives 0.950.  More than one tile of 96 was not measured and is not offered.
 enum Operands { OPERANDS_16BIT, OPERANDS_FP8, OPERANDS_MXFP8, OPERANDS_MXFP4, OPERANDS_MXFP6 };
 struct TilePlan {
     int rows, split;
@@ -291,9 +293,9 @@ hipError_t in_pieces(Operands kind, int M, int N, int K, int ns, size_t room, Pi
 // rounds, 198 us; as 304 tiles of 32 rows split in four it is 1216 items, 138 us.  128-row tiles are one per compute unit at a time,
 // whole rounds.  32-row tiles are dealt to 512 workgroups, two per compute unit: a last round of up to 256 of them leaves each a
 // compute unit to itself and takes 0.94 of 0.61 us a K-step, one of more 1.58 and a full one 1.70.  Over 84 shapes of 1 .. 1500 rows,
-// each timed at every split and both heights (profiles/tile_split_plans.csv), the model is within -5 .. +7 % of the chosen plan's
-// time; the choice takes 0.81 of the older rule's in the geometric mean and nowhere more, and 1.006 of the best plan's, 1.07 at most
-// (128 rows at K = 6144 37.1 against 34.6 us; 77 rows, in which the two heights are level, 36.0 before and 31.8 now).
+// each timed at every split and both heights (profiles/tile_split_plans.csv), the model gives the chosen plan's time within
+// -13 .. +4 % (weights from HBM) and -4 .. +11 % (from the cache); the choice takes 0.81 of the older rule's in the geometric mean and
+// nowhere more, and 1.006 of the best plan's, 1.09 at most (100 rows at K = 6144 as 128-row tiles 37.8 / 36.2 us, as 32-row tiles 36.2 / 33.4).
 struct F32Plan {
     int rows, split;
     double us;
