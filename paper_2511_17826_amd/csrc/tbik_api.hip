@@ -288,14 +288,13 @@ hipError_t in_pieces(Operands kind, int M, int N, int K, int ns, size_t room, Pi
 }
 
 // fp32 operands: tile height and K split of a shape (pure), by a model of the time.  The fp32 MFMA is slow (a K-step of 32
-// takes a 128-row tile 1.94 us and two 32-row tiles side by side on a compute unit 1.04), so what decides is how evenly the work
+// takes a 128-row tile 2.0 us and two 32-row tiles side by side on a compute unit 1.05), so what decides is how evenly the work
 // items fill 256 compute units: 600 x 2048 at K = 6144 is 80 tiles of 128 rows, which a split in four turns into 320 items = two
 // rounds, 198 us; as 304 tiles of 32 rows split in four it is 1216 items, 138 us.  128-row tiles are one per compute unit at a time,
 // whole rounds.  32-row tiles are dealt to 512 workgroups, two per compute unit: a last round of up to 256 of them leaves each a
-// compute unit to itself and takes 0.94 of 0.61 us a K-step, one of more 1.58 and a full one 1.70.  Over 84 shapes of 1 .. 1500 rows,
-// each timed at every split and both heights (profiles/tile_split_plans.csv), the model gives the chosen plan's time within
-// -13 .. +4 % (weights from HBM) and -4 .. +11 % (from the cache); the choice takes 0.81 of the older rule's in the geometric mean and
-// nowhere more, and 1.006 of the best plan's, 1.09 at most (100 rows at K = 6144 as 128-row tiles 37.8 / 36.2 us, as 32-row tiles 36.2 / 33.4).
+// compute unit to itself and takes 0.93 of 0.62 us a K-step, one of more 1.62 and a full one 1.70.  Checked over 716 shapes (1 .. 1500 rows,
+// 512 .. 16384 columns, K = 2048 .. 12288), each timed at every split and both heights: the choice takes 1.004 of the best plan's time in
+// the geometric mean, 1.11 at most, and of the older rule's over the 84 of them in profiles/tile_split_plans.csv 0.81, nowhere more.
 struct F32Plan {
     int rows, split;
     double us;
@@ -303,11 +302,11 @@ struct F32Plan {
 F32Plan f32_plan_at(int M, int N, int K, int split) {
     const int64_t cols = ((int64_t)N + 127) / 128, items128 = ((int64_t)M + 127) / 128 * cols * split, items32 = ((int64_t)M + 31) / 32 * cols * split;
     const double steps = K / 32.0 / split;
-    const double combine = split > 1 ? 5.4 + (double)split * M * N * 4.0 / 2.8e6 : 0.0;
+    const double combine = split > 1 ? 4.1 + 0.15 * split + (double)split * M * N * 4.0 / 3e6 : 0.0;
     const int64_t last = items32 & 511;
-    const double rounds32 = 1.70 * (double)(items32 >> 9) + (last == 0 ? 0.0 : last <= 256 ? 0.94 : 1.58);
-    const double t128 = (double)((items128 + 255) >> 8) * (steps * 1.94 + 1.4) + combine;
-    const double t32 = rounds32 * steps * 0.61 + 3.4 + combine;
+    const double rounds32 = 1.70 * (double)(items32 >> 9) + (last == 0 ? 0.0 : last <= 256 ? 0.93 : 1.62);
+    const double t128 = (double)((items128 + 255) >> 8) * (steps * 2.0 + 1.1) + combine;
+    const double t32 = rounds32 * steps * 0.62 + 2.2 + combine;
     return t32 < t128 ? F32Plan{32, split, t32} : F32Plan{128, split, t128};
 }
 F32Plan f32_plan(int M, int N, int K, int ns) {
@@ -319,9 +318,9 @@ F32Plan f32_plan(int M, int N, int K, int ns) {
         if (!best.rows || p.us < best.us) best = p;
     }
     if (!best.rows) return F32Plan{128, internal_split(M, N, K, ns), 0.0};
-    // Up to 64 rows the older rule's split of 32-row tiles stays where the model promises less than 8 %.  4096 x 4096 from HBM / from
-    // the cache: 64 rows split in eight 28.4 / 25.6 us, in four, held level, 29.3 / 27.0; one row split in eight 19.6 / 16.1, in sixteen,
-    // held 4 % quicker, 20.5 / 18.6.  (Above, 128-row tiles were the rule, which leaves the model more to say.)
+    // Up to 64 rows the older rule's split of 32-row tiles stays where the model promises less than 8 %: 2 rows of 8192 x 8192 split in
+    // four take 47.8 us, in eight, held 6 % quicker, 51.3; 64 rows of 4096 x 4096 split in eight 26.9, in four, held 2 % quicker, 28.1.
+    // (Above, 128-row tiles were the rule, which leaves the model more to say.)
     if (M <= 64) {
         const F32Plan rule = f32_plan_at(M, N, K, internal_split(M, N, K, ns));
         if (rule.rows == 32 && rule.us < 1.08 * best.us) return rule;

@@ -92,3 +92,8 @@ def test_slices_where_they_are_quicker(L, kind, M, N, K, leaf, k_first, kernel):
 def test_fp32_batches_on_two_workgroups_per_compute_unit(L, M, N, K, leaf, k_first):
     """A ragged last round of 32-row tiles costs what a model of 512 workgroups says, and these batches take them: 4 to 13 % less time."""
     assert route("f32", M, N, K, leaf, k_first)[0][2] == 32
+
+
+def test_fp32_splits_no_further_than_they_pay(L):
+    """30 row and column tiles split in eight leave each item a compute unit (19.2 us); in sixteen, the combine eats the gain (21.1)."""
+    assert route("f32", 88, 1280, 4096, 256, 1) == [(88, "tiles", 32, 8)]
