@@ -36,6 +36,7 @@
 #include <atomic>
 #include <cstdint>
 #include <type_traits>
+#include <utility>
 
 #include "attention_common.hpp"
 
@@ -181,6 +182,10 @@ __device__ __forceinline__ void attention_store_output(uint16_t *optr, float l, 
         }
 }
 
+// f(0), f(1), ... with the number as a constant.
+template <int... I, class F>
+__device__ __forceinline__ void for_each_slot(std::integer_sequence<int, I...>, F &&f) { (f(std::integral_constant<int, I>{}), ...); }
+
 template <bool CAUSAL, bool F16>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attention_kernel(const AttnParams p) {
@@ -188,8 +193,6 @@ void attention_kernel(const AttnParams p) {
     //   K rows: 16-byte chunk c of key r sits at position c ^ (r & 15): the 16 rows of a fragment read hit all banks.
     //   V rows: chunk c of key r sits at position c ^ (4 (r & 3)): the 4 rows of a transposing read differ in banks.
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    unsigned char *const k_lds = smem;
-    unsigned char *const v_lds = smem + 2 * ATT_TILE_BYTES;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -238,74 +241,10 @@ void attention_kernel(const AttnParams p) {
         for (int ks = 0; ks < ATT_D / 16; ++ks) asm volatile("" ::"v"(bq[ks]));
     }
 
-    // Tile loader: direct global->LDS loads (no staging registers).  Wavefront w fills key rows 16 w .. 16 w + 15 of a
-    // tile with 4 loads for K and 4 for V; load i covers rows 16 w + 4 i .. + 3: lane -> row r = 16 w + 4 i + lane / 16
-    // and chunk POSITION lane % 16 of that row in LDS, which holds chunk (lane % 16) ^ (r & 15) of the key's channels for K
-    // and (lane % 16) ^ 4 (r & 3) for V (the swizzle is applied on the global side).  Keys past the sequence repeat its
-    // last key (they are masked).  Token strides are below 2^24 elements, so a lane's byte offset fits 32 bits.
-    const int ld_pos = lane & 15, ld_sub = lane >> 4;
-    const uint16_t *kbase = p.K + (int64_t)k0 * p.k_stride + (int64_t)hk * ATT_D;     // wave-uniform
-    const uint16_t *vbase = p.V + (int64_t)k0 * p.v_stride + (int64_t)hk * ATT_D;
-    unsigned k_ld[4], v_ld[4];                                   // minus the instruction offset 1024 i, which the load adds back
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const unsigned r = 16 * wave + 4 * i + ld_sub;
-        k_ld[i] = (r * (unsigned)p.k_stride + ((ld_pos ^ (r & 15)) << 3)) * 2u - 1024u * i;
-        v_ld[i] = (r * (unsigned)p.v_stride + ((ld_pos ^ ((r & 3) << 2)) << 3)) * 2u - 1024u * i;
-    }
-    const unsigned smem_lds = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
-    const unsigned k_m0 = smem_lds + wave * 4096;                // + buffer offset
-    const unsigned v_m0 = smem_lds + 2 * ATT_TILE_BYTES + wave * 4096;
-    // Starts the loads of tile t into the K buffer at k_off and the V buffer at v_off; they are complete (for this
-    // wavefront) after an s_waitcnt vmcnt(0).
-    auto fetch = [&](int t, int k_off, int v_off) __attribute__((always_inline)) {
-        const char *kt = uniform_pointer(reinterpret_cast<const char *>(kbase + (int64_t)t * ATT_KV * p.k_stride));
-        const char *vt = uniform_pointer(reinterpret_cast<const char *>(vbase + (int64_t)t * ATT_KV * p.v_stride));
-        const unsigned km = __builtin_amdgcn_readfirstlane(k_m0 + k_off), vm = __builtin_amdgcn_readfirstlane(v_m0 + v_off);
-        if (__builtin_expect(t * ATT_KV + ATT_KV <= Lk, 1)) {      // uniform: the whole tile lies inside the sequence
-            load_16B_per_lane_to_lds<0, true>(kt, k_ld[0], km);
-            load_16B_per_lane_to_lds<1024, false>(kt, k_ld[1], km);
-            load_16B_per_lane_to_lds<2048, false>(kt, k_ld[2], km);
-            load_16B_per_lane_to_lds<3072, false>(kt, k_ld[3], km);
-            load_16B_per_lane_to_lds<0, true>(vt, v_ld[0], vm);
-            load_16B_per_lane_to_lds<1024, false>(vt, v_ld[1], vm);
-            load_16B_per_lane_to_lds<2048, false>(vt, v_ld[2], vm);
-            load_16B_per_lane_to_lds<3072, false>(vt, v_ld[3], vm);
-        } else {
-            const int last = Lk - 1 - t * ATT_KV;                  // >= 0: the tile holds at least one key
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const unsigned r = 16 * wave + 4 * i + ld_sub;
-                const unsigned rg = min((int)r, last);           // row fetched; it still lands in row r's place
-                load_16B_per_lane_to_lds<0, true>(kt, (rg * (unsigned)p.k_stride + ((ld_pos ^ (r & 15)) << 3)) * 2u, km + 1024 * i);
-                load_16B_per_lane_to_lds<0, true>(vt, (rg * (unsigned)p.v_stride + ((ld_pos ^ ((r & 3) << 2)) << 3)) * 2u, vm + 1024 * i);
-            }
-        }
-    };
-
-    // Fragment addresses inside a tile.
-    //   K, block kb, step ks: key 32 kb + li, chunk 2 ks + lg.
-    const int k_rd = li * 256;                                   // + kb * 8192; chunk swizzled per step: (2 ks + lg) ^ (li & 15)
-    //   V^T, channel block db, step s (kb = s / 2, h = s % 2), half hh: rows 32 kb + 16 h + 8 hh + 4 lg + e, e = l16 / 4,
-    //   columns 32 db + 16 ((lane / 16) % 2) + 4 (l16 % 4) .. + 3 before the transpose.
-    const int l16 = lane & 15, e = l16 >> 2;
-    int v_rd[ATT_D / 32];
-#pragma unroll
-    for (int db = 0; db < ATT_D / 32; ++db) {
-        const int col = db * 32 + ((lane >> 4) & 1) * 16 + (l16 & 3) * 4;
-        v_rd[db] = (4 * lg + e) * 256 + ((((col >> 3) ^ (e << 2))) << 4) + ((col >> 2) & 1) * 8;
-    }
-
-    f32x16 o[ATT_D / 32];
-#pragma unroll
-    for (int db = 0; db < ATT_D / 32; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[db][r] = 0.0f;
-    float m = -INFINITY, l = 0.0f;
-
     // Tiles of this workgroup: all of them, or those of its split.
     const int t_begin = one_split_each ? split * ATT_SPLIT : 0;
     const int t_end = one_split_each ? min(n_tiles, t_begin + ATT_SPLIT) : n_tiles;
+    const int w_end = min(t_end, wave_tiles);                     // this wavefront's
     if (t_begin >= t_end) {                                       // uniform: no query of the block sees a key (of this split)
         if (one_split_each) {
             *state_chunk(my_state, 0, tid) = f32x4{-INFINITY, 0.0f, 0.0f, 0.0f};   // an empty state: only m and l are looked at
@@ -316,109 +255,242 @@ void attention_kernel(const AttnParams p) {
         }
         return;
     }
-    fetch(t_begin, 0, 0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-
-    // One key tile out of LDS buffer BUF; the next tile is fetched meanwhile and parked in the other buffer.
-    auto tile = [&](auto buf_tag, int t) {
-        constexpr int BUF = decltype(buf_tag)::value;
-        const bool more = t + 1 < t_end;
-        if (more) fetch(t + 1, (BUF ^ 1) * ATT_TILE_BYTES, (BUF ^ 1) * ATT_TILE_BYTES);   // lands while this tile is multiplied;
-                                                                  // that buffer was last read before the previous barrier
-
-        if (t < wave_tiles) {
-            const unsigned char *kt = k_lds + BUF * ATT_TILE_BYTES;
-            const unsigned char *vt = v_lds + BUF * ATT_TILE_BYTES;
-            // ---- S^T = K Q^T ----
-            f32x16 s[2];
+    // Tile loader: direct global->LDS loads (no staging registers).  Wavefront w fills key rows 16 w .. 16 w + 15 of a
+    // tile with 4 loads for K and 4 for V; load i covers rows 16 w + 4 i .. + 3: lane -> row r = 16 w + 4 i + lane / 16
+    // and chunk POSITION lane % 16 of that row in LDS, which holds chunk (lane % 16) ^ (r & 15) of the key's channels for K
+    // and (lane % 16) ^ 4 (r & 3) for V (the swizzle is applied on the global side).  Keys past the sequence repeat its
+    // last key (they are masked).  Token strides are below 2^24 elements, so a lane's byte offset fits 32 bits; it carries
+    // 3072 - 1024 i (the instruction offset moves both addresses by 1024 i, the base is 3072 lower: no offset is negative).
+    const int ld_pos = lane & 15, ld_sub = lane >> 4;
+    const char *const kbase = reinterpret_cast<const char *>(p.K + (int64_t)k0 * p.k_stride + (int64_t)hk * ATT_D);     // wave-uniform
+    const char *const vbase = reinterpret_cast<const char *>(p.V + (int64_t)k0 * p.v_stride + (int64_t)hk * ATT_D);
+    unsigned k_ld[4], v_ld[4];
+    auto k_offsets = [&](int last) __attribute__((always_inline)) {
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) s[kb][r] = 0.0f;
-#pragma unroll
-            for (int ks = 0; ks < ATT_D / 16; ++ks)               // the two key blocks alternate: consecutive MFMAs are independent
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb) {
-                    const bf16x8 kf = *reinterpret_cast<const bf16x8 *>(kt + kb * 8192 + k_rd + (((2 * ks + lg) ^ (li & 15)) << 4));
-                    s[kb] = mfma_32x32x16<F16>(kf, bq[ks], s[kb]);
-                }
-            // ---- scale, mask, running maximum ----
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) s[kb][r] = s[kb][r] * p.c;
-            if (t * ATT_KV + ATT_KV - 1 > wave_full) {            // uniform: some row of the wavefront does not see the whole tile
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int key = t * ATT_KV + kb * 32 + 8 * (r >> 2) + 4 * lg + (r & 3);
-                        if (key > lim) s[kb][r] = -INFINITY;
-                    }
-            }
-            float tmax = s[0][0];
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, s[kb][r]);
-            {
-                float a, b;
-                both_halves(tmax, a, b);
-                tmax = fmaxf(a, b);                               // with the other half of this query's keys
-            }
-            const float m_new = fmaxf(m, tmax);
-            const float m_use = (m_new == -INFINITY) ? 0.0f : m_new;   // a query that has seen no key yet
-            const float alpha = __builtin_amdgcn_exp2f(m - m_use);
-            float psum = 0.0f;
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    s[kb][r] = __builtin_amdgcn_exp2f(s[kb][r] - m_use);
-                    psum = psum + s[kb][r];
-                }
-            {
-                float a, b;
-                both_halves(psum, a, b);
-                psum = a + b;                                     // lower half's sum + upper half's sum, in both lanes
-            }
-            l = l * alpha + psum;
-            m = m_new;
-            if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {   // uniform: o * 1 is o, so skipping changes no bit
-#pragma unroll
-                for (int db = 0; db < ATT_D / 32; ++db)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) o[db][r] = o[db][r] * alpha;
-            }
-            // ---- O^T += V^T P^T ----
-#pragma unroll
-            for (int st = 0; st < 4; ++st) {
-                const int kb = st >> 1, h = st & 1;
-                union { uint32_t u[4]; bf16x8 v; } pb;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) pb.u[i] = pack_16x2<F16>(s[kb][8 * h + 2 * i], s[kb][8 * h + 2 * i + 1]);
-#pragma unroll
-                for (int db = 0; db < ATT_D / 32; ++db) {
-                    union { att_v4i16 h2[2]; bf16x8 v; } vf;
-#pragma unroll
-                    for (int hh = 0; hh < 2; ++hh)
-                        vf.h2[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                            (__attribute__((address_space(3))) att_v4i16 *)(vt + (32 * kb + 16 * h + 8 * hh) * 256 + v_rd[db]));
-                    o[db] = mfma_32x32x16<F16>(vf.v, pb.v, o[db]);
-                }
-            }
+        for (int i = 0; i < 4; ++i) {
+            const unsigned r = 16 * wave + 4 * i + ld_sub;
+            k_ld[i] = (min((int)r, last) * (unsigned)p.k_stride + ((ld_pos ^ (r & 15)) << 3)) * 2u + (3072u - 1024u * i);
         }
-
-
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // this wavefront's part of the next tile has landed
-        __syncthreads();
     };
+    auto v_offsets = [&](int last) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const unsigned r = 16 * wave + 4 * i + ld_sub;
+            v_ld[i] = (min((int)r, last) * (unsigned)p.v_stride + ((ld_pos ^ ((r & 3) << 2)) << 3)) * 2u + (3072u - 1024u * i);
+        }
+    };
+    const unsigned smem_lds = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+    const unsigned k_m0 = smem_lds + wave * 4096;                // + buffer offset
+    const unsigned v_m0 = smem_lds + 2 * ATT_TILE_BYTES + wave * 4096;
+    // Tile t goes to K or V buffer t % 2.  Tiles past the workgroup's last are that one again, in a buffer nobody reads.
+    const char *k_src = nullptr, *v_src = nullptr;
+    unsigned k_dst = 0, v_dst = 0;
+    auto aim_k = [&](int t) __attribute__((always_inline)) {
+        k_src = uniform_pointer(kbase + (int64_t)min(t, t_end - 1) * ATT_KV * 2 * p.k_stride - 3072);
+        k_dst = __builtin_amdgcn_readfirstlane(k_m0 + (t & 1) * ATT_TILE_BYTES);
+        if (__builtin_expect(t == t_end - 1 && t * ATT_KV + ATT_KV > Lk, 0)) k_offsets(Lk - 1 - t * ATT_KV);
+    };
+    auto aim_v = [&](int t) __attribute__((always_inline)) {
+        v_src = uniform_pointer(vbase + (int64_t)min(t, t_end - 1) * ATT_KV * 2 * p.v_stride - 3072);
+        v_dst = __builtin_amdgcn_readfirstlane(v_m0 + (t & 1) * ATT_TILE_BYTES);
+        if (__builtin_expect(t == t_end - 1 && t * ATT_KV + ATT_KV > Lk, 0)) v_offsets(Lk - 1 - t * ATT_KV);
+    };
+    auto load_k = [&](auto i_tag) __attribute__((always_inline)) {
+        constexpr int I = decltype(i_tag)::value;
+        load_16B_per_lane_to_lds<1024 * I, true>(k_src, k_ld[I], k_dst);
+    };
+    auto load_v = [&](auto i_tag) __attribute__((always_inline)) {
+        constexpr int I = decltype(i_tag)::value;
+        load_16B_per_lane_to_lds<1024 * I, true>(v_src, v_ld[I], v_dst);
+    };
+    typedef std::integral_constant<int, 0> I0;
+    typedef std::integral_constant<int, 1> I1;
+    typedef std::integral_constant<int, 2> I2;
+    typedef std::integral_constant<int, 3> I3;
+    auto all_k = [&]() __attribute__((always_inline)) { load_k(I0{}); load_k(I1{}); load_k(I2{}); load_k(I3{}); };
+    auto all_v = [&]() __attribute__((always_inline)) { load_v(I0{}); load_v(I1{}); load_v(I2{}); load_v(I3{}); };
+
+    // Fragment addresses inside a tile.
+    //   K, block kb, step ks: key 32 kb + li, chunk 2 ks + lg.
+    //   V^T, channel block db, step s (kb = s / 2, h = s % 2), half hh: rows 32 kb + 16 h + 8 hh + 4 lg + e, e = l16 / 4,
+    //   columns 32 db + 16 ((lane / 16) % 2) + 4 (l16 % 4) .. + 3 before the transpose.
+    const unsigned k_rd = smem_lds + li * 256 + ((lg ^ (li & 15)) << 4);     // ^ 32 ks
+    unsigned v_rd[ATT_D / 32];
+    const int l16 = lane & 15, e4 = l16 >> 2;
+#pragma unroll
+    for (int db = 0; db < ATT_D / 32; ++db) {
+        const int col = db * 32 + ((lane >> 4) & 1) * 16 + (l16 & 3) * 4;
+        v_rd[db] = smem_lds + 2 * ATT_TILE_BYTES + (4 * lg + e4) * 256 + ((((col >> 3) ^ (e4 << 2))) << 4) + ((col >> 2) & 1) * 8;
+    }
+    typedef union { att_v4i16 h2[2]; bf16x8 v; } vfrag;
+    constexpr int K_AHEAD = 2, V_AHEAD = 4;                       // k-steps of scores, products
+    bf16x8 kf[K_AHEAD + 1][2];                                    // K fragments: k-step ks of both key blocks in kf[ks % 3]
+    vfrag vf[V_AHEAD + 1];                                        // V^T fragments: of product j = 4 st + db in vf[j % 5]
+    auto read_k = [&](int buf, int ks) __attribute__((always_inline)) {
+        unsigned at = k_rd;
+        asm volatile("" : "+v"(at));                          // formed where it is used: eight addresses are eight registers
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+            kf[ks % (K_AHEAD + 1)][kb] = *(const __attribute__((address_space(3))) bf16x8 *)(uintptr_t)((at ^ (ks << 5)) + buf * ATT_TILE_BYTES + kb * 8192);
+    };
+    auto read_v = [&](int buf, int j) __attribute__((always_inline)) {
+        const int kb = j >> 3, h = (j >> 2) & 1;
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+            vf[j % (V_AHEAD + 1)].h2[hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (__attribute__((address_space(3))) att_v4i16 *)(uintptr_t)(v_rd[j & 3] + buf * ATT_TILE_BYTES + (32 * kb + 16 * h + 8 * hh) * 256));
+    };
+
+    f32x16 o[ATT_D / 32];
+#pragma unroll
+    for (int db = 0; db < ATT_D / 32; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[db][r] = 0.0f;
+    float m = -INFINITY, l = 0.0f;
+
+    // A body: the softmax step of tile t beside S = K Q^T of tile t + 1 (NEXT) and O += V^T P^T of tile t, in slots of one
+    // matrix instruction with its share of the vector work and of the LDS reads to come.  The product needs the weights
+    // eight keys of a half at a time, so the second half of them is formed beside its first half.
+    // What bounds it: a tile is 1024 cycles of the matrix pipe and about 1150 of the vector ALU's issue port, and the wavefront
+    // has to offer both at the same time for the SIMD's two wavefronts to keep both busy.  Run one after the other, with each
+    // pair of K fragments read just before its use, they took 2346 cycles a tile and wavefront (matrix pipe busy 44 %); so
+    // they take 2130 (48 %), at a clock that falls from 2.03 to 1.89 GHz: the chip's power is what is left.  4 x 4096 tokens,
+    // 32 heads over 8: 594 -> 572 us, 1 x 16384 2210 -> 2133, 1000 tokens 29.2 -> 25.3, four prompts of 1531 .. 4096 369 -> 349.
+    // (One wavefront per SIMD with two such sets of queries in 512 registers issues an instruction every five cycles
+    // whatever it is, 930 of them for two tiles: 690 us.)  Masked tiles and a wavefront's last one run without NEXT: a copy
+    // of the body with both spills 600 registers.
+    typedef f32x16 scores[2];
+    constexpr int EXP_SLOT = 7, EXP_SLOTS = 17;                   // matrix instructions beside which the weights are formed
+    static_assert(32 * (24 - EXP_SLOT) / EXP_SLOTS == 32 && 32 * (16 - EXP_SLOT) / EXP_SLOTS >= 8 && 32 * (20 - EXP_SLOT) / EXP_SLOTS >= 16, "weights are there when the product takes them");
+    auto scale_and_mask = [&](scores &s, auto mask_tag, int i, int rel, float &tmax) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 4 * i; e < 4 * i + 4; ++e) {
+            float v = s[e >> 4][e & 15] * p.c;
+            if constexpr (decltype(mask_tag)::value)
+                if (32 * (e >> 4) + 8 * ((e & 15) >> 2) + (e & 3) > rel) v = -INFINITY;
+            s[e >> 4][e & 15] = v;
+        }
+        const int r = 4 * (i & 3);
+        tmax = fmaxf(fmaxf(tmax, s[i >> 2][r]), s[i >> 2][r + 1]);
+        tmax = fmaxf(fmaxf(tmax, s[i >> 2][r + 2]), s[i >> 2][r + 3]);
+    };
+    // The maximum of a tile is known: new running maximum, rescaling factor.
+    auto new_maximum = [&](float tmax, float &m_use, float &alpha) __attribute__((always_inline)) {
+        float a, b;
+        both_halves(tmax, a, b);                                  // with the other half of this query's keys
+        const float m_new = fmaxf(m, fmaxf(a, b));
+        m_use = (m_new == -INFINITY) ? 0.0f : m_new;              // a query that has seen no key yet
+        alpha = __builtin_amdgcn_exp2f(m - m_use);
+        m = m_new;
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {     // uniform: o * 1 is o, so skipping changes no bit
+#pragma unroll
+            for (int db = 0; db < ATT_D / 32; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[db][r] = o[db][r] * alpha;
+        }
+    };
+    auto add_sum = [&](float psum, float alpha) __attribute__((always_inline)) {
+        float a, b;
+        both_halves(psum, a, b);
+        l = l * alpha + (a + b);                                  // lower half's sum + upper half's sum, in both lanes
+    };
+    union weights { uint32_t u[16]; bf16x8 v[4]; };               // rounded to 16 bits, k-step by k-step of the product
+    auto body = [&](auto buf_tag, auto next_tag, auto mask_tag, scores &s, scores &next, int t) __attribute__((always_inline)) {
+        constexpr int BUF = decltype(buf_tag)::value;
+        constexpr bool NEXT = decltype(next_tag)::value;
+        const f32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        if constexpr (NEXT) {
+#pragma unroll
+            for (int ks = 0; ks < K_AHEAD; ++ks) read_k(BUF ^ 1, ks);
+        }
+        const int rel = lim - (t * ATT_KV + 4 * lg);              // element (kb, r) is masked where 32 kb + 8 (r / 4) + r % 4 exceeds it
+        float tmax = -INFINITY, m_use, alpha, psum = 0.0f, even = 0.0f;
+        weights w;
+        scale_and_mask(s, mask_tag, 0, rel, tmax);
+        scale_and_mask(s, mask_tag, 1, rel, tmax);
+        __builtin_amdgcn_sched_barrier(0);
+        for_each_slot(std::make_integer_sequence<int, 32>{}, [&](auto slot_tag) __attribute__((always_inline)) {
+            constexpr int i = decltype(slot_tag)::value;
+            if constexpr (i < 16 && !NEXT) {
+            } else if constexpr (i < 16) {
+                constexpr int ks = i >> 1, kb = i & 1;
+                next[kb] = mfma_32x32x16<F16>(kf[ks % (K_AHEAD + 1)][kb], bq[ks], ks == 0 ? zero : next[kb]);
+                if (kb == 0 && ks + K_AHEAD < ATT_D / 16) read_k(BUF ^ 1, ks + K_AHEAD);
+            } else {
+                constexpr int j = i - 16;
+                o[j & 3] = mfma_32x32x16<F16>(vf[j % (V_AHEAD + 1)].v, w.v[j >> 2], o[j & 3]);
+            }
+            if (i >= 16 - V_AHEAD && i + V_AHEAD < 32) read_v(BUF, i + V_AHEAD - 16);
+            if constexpr (NEXT && i == 1) load_k(I0{});
+            if constexpr (NEXT && i == 3) load_k(I1{});
+            if constexpr (NEXT && i == 5) load_k(I2{});
+            if constexpr (NEXT && i == 9) load_k(I3{});
+            if constexpr (NEXT && i == 17) load_v(I0{});
+            if constexpr (NEXT && i == 20) load_v(I1{});
+            if constexpr (NEXT && i == 24) load_v(I2{});
+            if constexpr (NEXT && i == 27) load_v(I3{});
+            if constexpr (i < EXP_SLOT - 1) scale_and_mask(s, mask_tag, i + 2, rel, tmax);
+            if constexpr (i == EXP_SLOT - 1) new_maximum(tmax, m_use, alpha);
+            if constexpr (i >= EXP_SLOT && i < EXP_SLOT + EXP_SLOTS) {
+                constexpr int k = i - EXP_SLOT;
+#pragma unroll
+                for (int e = 32 * k / EXP_SLOTS; e < 32 * (k + 1) / EXP_SLOTS; ++e) {
+                    const float x = __builtin_amdgcn_exp2f(s[e >> 4][e & 15] - m_use);
+                    psum = psum + x;
+                    if (e & 1) w.u[e >> 1] = pack_16x2<F16>(even, x);
+                    else even = x;
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        add_sum(psum, alpha);
+    };
+    // The same one step after the other, for the tiles that some row does not see whole and the last ones.
+    auto scores_alone = [&](int buf, scores &s) __attribute__((always_inline)) {
+        const f32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int ks = 0; ks < ATT_D / 16; ++ks) {
+            read_k(buf, ks);
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) s[kb] = mfma_32x32x16<F16>(kf[ks % (K_AHEAD + 1)][kb], bq[ks], ks == 0 ? zero : s[kb]);
+        }
+    };
+    auto next_tile = [&](int t) __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");   // K_{t+1} and V_t are there, K_t and V_{t-1} have been read
+        aim_k(t + 2);
+        aim_v(t + 1);
+    };
+    auto last_body = [&](auto buf_tag, scores &s, scores &next, int t) __attribute__((always_inline)) {
+        next_tile(t);
+        if (t + 2 < t_end) all_k();
+        if (t + 1 < t_end) all_v();
+        if (t < w_end) {
+            if (t + 1 < w_end) scores_alone(decltype(buf_tag)::value ^ 1, next);
+            body(buf_tag, std::false_type{}, std::true_type{}, s, next, t);
+        }
+    };
+
+    k_offsets(ATT_KV - 1);
+    v_offsets(ATT_KV - 1);
+    aim_k(t_begin);
+    all_k();
+    aim_v(t_begin);
+    all_v();
+    if (t_begin + 1 < t_end) {
+        aim_k(t_begin + 1);
+        all_k();
+        asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");      // the first four have landed
+    } else {
+        asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
+    }
+    scores even, odd;                                             // of even and odd tiles (t_begin is even)
+    if (t_begin < w_end) scores_alone(0, even);
+
+    const int n_hot = min(w_end - 1, (wave_full + 1) / ATT_KV);   // tiles before this one have a successor and rows that see all of them
     bool folded = false;                                          // uniform: an accumulated state waits in my_state
-    for (int t = t_begin; t < t_end; t += 2) {
+    for (int t = t_begin; t < t_end;) {
         if (t > t_begin && (t & (ATT_SPLIT - 1)) == 0) {          // uniform: a split ends here (only when one workgroup walks them all)
-            // No direct load is in flight at this point (the tile before waited for its successor), so ordinary
-            // loads and stores, which the compiler counts itself, can be used.
+            // The direct loads in flight are older than the loads and stores here: waiting for these waits for them.
             int me = tid;
             asm volatile("" : "+v"(me));                          // the addresses are formed here, not kept in registers across the tiles
             if (folded) state_fold(my_state, me, m, l, o);
@@ -431,9 +503,19 @@ void attention_kernel(const AttnParams p) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) o[db][r] = 0.0f;
         }
-        tile(std::integral_constant<int, 0>{}, t);
-        if (t + 1 < t_end) tile(std::integral_constant<int, 1>{}, t + 1);
+        const int first = t, hot_end = min(n_hot, (t + ATT_SPLIT) & -ATT_SPLIT);
+        for (; t + 2 <= hot_end; t += 2) {
+            next_tile(t);
+            body(I0{}, std::true_type{}, std::false_type{}, even, odd, t);
+            next_tile(t + 1);
+            body(I1{}, std::true_type{}, std::false_type{}, odd, even, t + 1);
+        }
+        if (t > first && (t & (ATT_SPLIT - 1)) == 0) continue;    // a split ends here
+        last_body(I0{}, even, odd, t);
+        if (t + 1 < t_end) last_body(I1{}, odd, even, t + 1);
+        t += 2;
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // no load may land in LDS that another workgroup owns
 
     int me = tid;
     asm volatile("" : "+v"(me));
