@@ -8,6 +8,8 @@ fallback: if ``libtbik.so`` is missing the import of the library fails loudly.
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
@@ -123,10 +125,58 @@ SIGNATURES = {
 
 _lib = None
 
+# The common calls -- no `out`, no `workspace`, ordinary tensors -- are marshalled by _marshal.so (csrc/marshal.cpp); it answers None
+# to any other, which then takes the way through ctypes below and gets that way's answers and errors.
+# name -> (number there, kind of call, workspace query, operand dtype)
+_NATIVE = {name: (i, *spec) for i, (name, *spec) in enumerate([
+    ("tbik_gemm", 0, "tbik_gemm_16bit_workspace_bytes", torch.bfloat16),
+    ("tbik_gemm_f16", 0, "tbik_gemm_16bit_workspace_bytes", torch.float16),
+    ("tbik_gemm_f32", 1, "tbik_gemm_f32_workspace_bytes", torch.float32),
+    ("tbik_gemm_shard_partials", 2, "tbik_gemm_16bit_workspace_bytes", torch.bfloat16),
+    ("tbik_gemm_shard_partials_f16", 2, "tbik_gemm_16bit_workspace_bytes", torch.float16),
+    ("tbik_gemm_shard_partials_f32", 3, "tbik_gemm_f32_workspace_bytes", torch.float32),
+    ("tbik_gemm_swiglu bf16", 4, "tbik_gemm_swiglu_workspace_bytes", torch.bfloat16),
+    ("tbik_gemm_swiglu fp16", 4, "tbik_gemm_swiglu_workspace_bytes", torch.float16),
+    ("tbik_gemm_fp8", 5, "tbik_gemm_fp8_workspace_bytes", torch.uint8),
+    ("tbik_gemm_mxfp8", 6, "tbik_gemm_mxfp8_workspace_bytes", torch.uint8),
+    ("tbik_gemm_mxfp6", 6, "tbik_gemm_mxfp6_workspace_bytes", torch.uint8),
+    ("tbik_gemm_mxfp4", 7, "tbik_gemm_mxfp4_workspace_bytes", torch.uint8),
+    ("tbik_rmsnorm", 8, None, torch.bfloat16),
+    ("tbik_rmsnorm_f16", 8, None, torch.float16),
+    ("tbik_combine_residual_rmsnorm", 9, None, torch.bfloat16),
+    ("tbik_combine_residual_rmsnorm_f16", 9, None, torch.float16),
+    ("tbik_row_reduce", 10, "tbik_row_reduce_workspace_bytes", torch.float32),
+    ("tbik_attention", 11, "tbik_attention_workspace_bytes", torch.bfloat16),
+    ("tbik_attention_f16", 11, "tbik_attention_workspace_bytes", torch.float16),
+])}
+_NUMBER = {name: spec[0] for name, spec in _NATIVE.items()}
+
+
+class _NotLoaded:
+    """Stands for _marshal.so until the library is loaded: no call is a common one."""
+    product = rmsnorm = combine = row_reduce = attention = staticmethod(lambda *a: None)
+
+
+_native = _NotLoaded
+
+
+def _load_native(L: C.CDLL):
+    path = os.path.join(_HERE, "_marshal.so")
+    if not os.path.exists(path):
+        raise RuntimeError("_marshal.so is not built: run `python -m paper_2511_17826_amd.build`")
+    loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
+    m = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", path, loader=loader))
+    loader.exec_module(m)
+    address = lambda name: C.cast(getattr(L, name), C.c_void_p).value
+    for name, (number, kind, need, dtype) in _NATIVE.items():
+        m.register(number, kind, address(name.split(" ")[0]), address(need) if need else 0, dtype)
+    m.use(_ws_cache, _workspace)
+    return m
+
 
 def lib() -> C.CDLL:
     """Loads libtbik.so (built by ``python -m paper_2511_17826_amd.build``); raises if it is absent."""
-    global _lib
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError("libtbik.so is not built: run `python -m paper_2511_17826_amd.build` "
@@ -136,6 +186,7 @@ def lib() -> C.CDLL:
             fn = getattr(L, name)
             fn.restype = res
             fn.argtypes = args
+        _native = _load_native(L)
         _lib = L
     return _lib
 
@@ -154,8 +205,13 @@ def _check(status: int, where: str):
         raise TbikError(status, where)
 
 
-# A small call is over on the GPU before Python has issued it (one token of 4096 x 4096: 7 us there, 11 here; 10 so), so what every
-# call does below asks a tensor once and takes the cheapest way to an answer.
+def _done(y, entry: str):
+    """What _marshal.so answered to a common call: the output, or the library's status."""
+    if y.__class__ is int:
+        _check(y, entry)
+    return y
+
+
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
 
@@ -219,6 +275,10 @@ def gemm_f32_workspace_bytes(M, N, K, leaf, k_first=1) -> int:
 
 
 def _gemm(entry: str, in_dtype, X, W, leaf, k_first, out_dtype, out, workspace):
+    if out is None and workspace is None:
+        y = _native.product(_NUMBER[entry], X, None, W, None, leaf, k_first, out_dtype, 0)
+        if y is not None:
+            return _done(y, entry)
     ldx, ldw = _rowmajor(X, "X"), _rowmajor(W, "W")
     assert X.dtype == in_dtype and W.dtype == in_dtype
     M, K = X.shape
@@ -254,6 +314,10 @@ def tbik_gemm_f16(X: torch.Tensor, W: torch.Tensor, leaf: int, k_first: int = 1,
 def tbik_gemm_f32(X: torch.Tensor, W: torch.Tensor, leaf: int, k_first: int = 1, out: torch.Tensor | None = None,
                   workspace: torch.Tensor | None = None) -> torch.Tensor:
     """Y = X @ W in the tree order, whole K on this device (fp32 operands, fp32 output)."""
+    if out is None and workspace is None:
+        y = _native.product(_NUMBER["tbik_gemm_f32"], X, None, W, None, leaf, k_first, None, 0)
+        if y is not None:
+            return _done(y, "tbik_gemm_f32")
     _rowmajor(X, "X"); _rowmajor(W, "W")
     assert X.dtype == torch.float32 and W.dtype == torch.float32
     M, K = X.shape
@@ -275,6 +339,10 @@ def tbik_gemm_f32(X: torch.Tensor, W: torch.Tensor, leaf: int, k_first: int = 1,
 
 
 def _gemm_shard_partials(entry: str, in_dtype, X, W, leaf, k_first, P, out, workspace):
+    if out is None and workspace is None:
+        y = _native.product(_NUMBER[entry], X, None, W, None, leaf, k_first, None, P)
+        if y is not None:
+            return _done(y, entry)
     _rowmajor(X, "X"); _rowmajor(W, "W")
     assert X.dtype == in_dtype and W.dtype == in_dtype
     M, K = X.shape
@@ -334,6 +402,10 @@ def gemm_fp8_workspace_bytes(M, N, K, leaf, k_first=1) -> int:
 def tbik_gemm_fp8(X: torch.Tensor, Wt: torch.Tensor, leaf: int, k_first: int = 1, fmt: str = "e4m3",
                   out_dtype=torch.bfloat16, out: torch.Tensor | None = None, workspace: torch.Tensor | None = None):
     """Y = X @ Wt.T in the tree order on 8-bit floating-point operands; Wt is [N, K] (one row per output channel)."""
+    if out is None and workspace is None:
+        y = _native.product(_NUMBER["tbik_gemm_fp8"], X, None, Wt, None, leaf, k_first, out_dtype, _FP8.get(fmt))
+        if y is not None:
+            return _done(y, "tbik_gemm_fp8")
     X, Wt, dt = _fp8_operands(X, Wt, fmt)
     M, K = X.shape
     N = Wt.shape[0]
@@ -400,6 +472,10 @@ def tbik_gemm_mxfp4(X, Xs, Wt, Ws, leaf: int, k_first: int = 1, out_dtype=torch.
                     workspace: torch.Tensor | None = None) -> torch.Tensor:
     """Y = X @ Wt.T in the tree order on MXFP4 operands: X [M, K/2] packed pairs with scales Xs [M, K/32]; the weight
     transposed, Wt [N, K/2] with Ws [N, K/32]."""
+    if out is None and workspace is None:
+        y = _native.product(_NUMBER["tbik_gemm_mxfp4"], X, Xs, Wt, Ws, leaf, k_first, out_dtype, 0)
+        if y is not None:
+            return _done(y, "tbik_gemm_mxfp4")
     M, N, K = _mx_operands(X, Xs, Wt, Ws)
     if out is None:
         out = X.new_empty((M, N), dtype=out_dtype)
@@ -462,6 +538,10 @@ def tbik_gemm_mxfp8(X, Xs, Wt, Ws, leaf: int, k_first: int = 1, fmt: str = "e4m3
                     out: torch.Tensor | None = None, workspace: torch.Tensor | None = None) -> torch.Tensor:
     """Y = X @ Wt.T in the tree order on MXFP8 operands: X [M, K] 8-bit patterns of format `fmt` with scales Xs [M, K/32];
     the weight transposed, Wt [N, K] with Ws [N, K/32]."""
+    if out is None and workspace is None:
+        y = _native.product(_NUMBER["tbik_gemm_mxfp8"], X, Xs, Wt, Ws, leaf, k_first, out_dtype, _FP8.get(fmt))
+        if y is not None:
+            return _done(y, "tbik_gemm_mxfp8")
     X, Wt, dt, M, N, K = _mx8_operands(X, Xs, Wt, Ws, fmt)
     if out is None:
         out = X.new_empty((M, N), dtype=out_dtype)
@@ -530,6 +610,10 @@ def tbik_gemm_mxfp6(X, Xs, Wt, Ws, leaf: int, k_first: int = 1, fmt: str = "e2m3
                     out: torch.Tensor | None = None, workspace: torch.Tensor | None = None) -> torch.Tensor:
     """Y = X @ Wt.T in the tree order on MXFP6 operands: X [M, 3K/4] packed 6-bit elements of format `fmt` with scales
     Xs [M, K/32]; the weight transposed, Wt [N, 3K/4] with Ws [N, K/32]."""
+    if out is None and workspace is None:
+        y = _native.product(_NUMBER["tbik_gemm_mxfp6"], X, Xs, Wt, Ws, leaf, k_first, out_dtype, _FP6.get(fmt))
+        if y is not None:
+            return _done(y, "tbik_gemm_mxfp6")
     dt, M, N, K = _mx6_operands(X, Xs, Wt, Ws, fmt)
     if out is None:
         out = X.new_empty((M, N), dtype=out_dtype)
@@ -606,6 +690,11 @@ def gemm_swiglu_workspace_bytes(M, I, K, leaf, k_first=1) -> int:
 def tbik_gemm_swiglu(X: torch.Tensor, W_gu: torch.Tensor, leaf: int, k_first: int = 1, out: torch.Tensor | None = None,
                      workspace: torch.Tensor | None = None) -> torch.Tensor:
     """act = SiLU(X @ W_gu[:, :I]) * (X @ W_gu[:, I:]) in the tree order; W_gu is [K, 2 I], gate columns first."""
+    if out is None and workspace is None:
+        y = _native.product(_NUMBER["tbik_gemm_swiglu fp16" if X.dtype == torch.float16 else "tbik_gemm_swiglu bf16"], X, None, W_gu, None,
+                            leaf, k_first, None, 0)
+        if y is not None:
+            return _done(y, "tbik_gemm_swiglu")
     _rowmajor(X, "X"); _rowmajor(W_gu, "W_gu")
     assert X.dtype == W_gu.dtype and X.dtype in (torch.bfloat16, torch.float16)
     M, K = X.shape
@@ -639,6 +728,10 @@ def tbik_tree_combine(partials: torch.Tensor, out_dtype=torch.bfloat16, out: tor
 
 
 def _rmsnorm(name, dtype, x, weight, eps, out):
+    if out is None:
+        y = _native.rmsnorm(_NUMBER[name], x, weight, eps)
+        if y is not None:
+            return _done(y, name)
     assert x.dim() == 2 and x.is_contiguous() and x.dtype == dtype
     assert weight.is_contiguous() and weight.dtype == dtype and weight.numel() == x.shape[1]
     if out is None:
@@ -658,6 +751,10 @@ def tbik_rmsnorm_f16(x: torch.Tensor, weight: torch.Tensor, eps: float = 1e-6, o
 
 
 def _combine_residual_rmsnorm(name, dtype, partials, residual, weight, eps, hidden, normed):
+    if hidden is None and normed is None:
+        y = _native.combine(_NUMBER[name], partials, residual, weight, eps)
+        if y is not None:
+            return _done(y, name)
     assert partials.dim() == 3 and partials.is_contiguous() and partials.dtype == torch.float32
     P, M, H = partials.shape
     assert residual.shape == (M, H) and residual.is_contiguous() and residual.dtype == dtype
@@ -700,6 +797,10 @@ def attention_workspace_bytes(batch, max_seqlen_q, max_seqlen_k, heads_q, heads_
 
 def _attention(entry, dtype, Q, K, V, cu_seqlens_q, cu_seqlens_k, max_seqlen_q, scale, causal, out, max_seqlen_k, workspace,
                verify_lengths=False):
+    if out is None and workspace is None and max_seqlen_k is not None and not verify_lengths:
+        y = _native.attention(_NUMBER[entry], Q, K, V, cu_seqlens_q, cu_seqlens_k, max_seqlen_q, scale, causal, max_seqlen_k)
+        if y is not None:
+            return _done(y, entry)
     _token_major(Q, "Q", dtype); _token_major(K, "K", dtype); _token_major(V, "V", dtype)
     Tq, Hq, D = Q.shape
     Tk, Hkv, _ = K.shape
@@ -755,6 +856,10 @@ def tbik_attention_f16(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, cu_seq
 def tbik_row_reduce(x: torch.Tensor, op: int, out: torch.Tensor | None = None,
                     workspace: torch.Tensor | None = None) -> torch.Tensor:
     """op = TBIK_SUM / TBIK_MAX -> fp32 [M]; TBIK_LOGSOFTMAX -> fp32 [M, V]."""
+    if out is None and workspace is None:
+        y = _native.row_reduce(_NUMBER["tbik_row_reduce"], x, op)
+        if y is not None:
+            return _done(y, "tbik_row_reduce")
     assert x.dim() == 2 and x.is_contiguous()
     M, V = x.shape
     if out is None:

@@ -29,6 +29,24 @@ FLAGS = ["--offload-arch=gfx950", "-mllvm", "-amdgpu-mfma-vgpr-form", "-O3", "-s
          "-Wno-unknown-attributes", "-Wno-inline-asm"]
 
 
+MARSHAL = os.path.join(HERE, "_marshal.so")     # the binding's native half (csrc/marshal.cpp): host code against torch's headers
+
+
+def _build_marshal() -> None:
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-w",
+           "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", "/opt/rocm/include",
+           os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL, "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on marshal.cpp:\n%s" % r.stderr)
+
+
 def _hipcc() -> str:
     for c in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", "hipcc"):
         if c and (os.path.sep not in c or os.path.exists(c)):
@@ -75,7 +93,9 @@ def build(save_temps: bool = True, jobs: int = 8, defines=(), lib_path: str = LI
     os.makedirs(BUILD, exist_ok=True)
     extra = (["-save-temps=obj"] if save_temps else []) + ["-D" + d for d in defines]
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        marshal = ex.submit(_build_marshal)
         objs = list(ex.map(lambda s: _compile(s, extra), SOURCES))
+        marshal.result()
     if save_temps:
         check_generated_code(os.path.join(BUILD, "gemm_tiled-hip-amdgcn-amd-amdhsa-gfx950.s"), "gemm_tiled_kernel")
         check_generated_code(os.path.join(BUILD, "attention-hip-amdgcn-amd-amdhsa-gfx950.s"), "attention_")
