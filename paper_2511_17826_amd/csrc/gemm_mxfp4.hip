@@ -292,10 +292,12 @@ void gemm_mxfp4_tiled_kernel(const Mx4Params p) {
         const int nxt = (cur + 1 == RING4) ? 0 : cur + 1;
         constexpr int ALLOW = LOADS_PER_STAGE * (RING4 - 3);
         if (__builtin_expect(stores_in_flight == 0, 1)) {
-            wait_loads_and_barrier<ALLOW>();                  // stage s+1 landed; the slot of stage s-1 is free
-        } else {
-            if (stores_in_flight == STORES_F32) wait_loads_and_barrier<ALLOW + STORES_F32>();
-            else if (stores_in_flight == STORES_BF16) wait_loads_and_barrier<ALLOW + STORES_BF16>();
+            wait_loads_and_barrier<ALLOW>();                         // stage s+1 landed; the slot of stage s-1 is free
+        } else {                                              // first stage after an epilogue
+            int n = stores_in_flight;
+            asm volatile("" : "+s"(n));                       // a value of its own: see stores_in_flight
+            if (n == STORES_F32) wait_loads_and_barrier<ALLOW + STORES_F32>();
+            else if (n == STORES_BF16) wait_loads_and_barrier<ALLOW + STORES_BF16>();
             else wait_loads_and_barrier<0>();
             stores_in_flight = 0;
         }

@@ -254,10 +254,12 @@ void gemm_tiled_kernel(const TiledParams p) {
         constexpr int ALLOW = LOADS_PER_STAGE * (RING - 3);  // loads of stage s+2.. may still be in flight
         if (__builtin_expect(stores_in_flight == 0, 1)) {
             wait_loads_and_barrier<ALLOW>();                         // stage s+1 landed; the slot of stage s-1 is free
-        } else {                                                     // first stage after an epilogue
-            if (stores_in_flight == STORES_F32) wait_loads_and_barrier<ALLOW + STORES_F32>();
-            else if (stores_in_flight == STORES_BF16) wait_loads_and_barrier<ALLOW + STORES_BF16>();
-            else if (stores_in_flight == STORES_ACT) wait_loads_and_barrier<ALLOW + STORES_ACT>();
+        } else {                                              // first stage after an epilogue
+            int n = stores_in_flight;
+            asm volatile("" : "+s"(n));                       // a value of its own: see stores_in_flight
+            if (n == STORES_F32) wait_loads_and_barrier<ALLOW + STORES_F32>();
+            else if (n == STORES_BF16) wait_loads_and_barrier<ALLOW + STORES_BF16>();
+            else if (n == STORES_ACT) wait_loads_and_barrier<ALLOW + STORES_ACT>();
             else wait_loads_and_barrier<0>();
             stores_in_flight = 0;
         }
