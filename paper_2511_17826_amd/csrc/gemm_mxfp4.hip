@@ -295,7 +295,7 @@ void gemm_mxfp4_tiled_kernel(const Mx4Params p) {
             wait_loads_and_barrier<ALLOW>();                         // stage s+1 landed; the slot of stage s-1 is free
         } else {                                              // first stage after an epilogue
             int n = stores_in_flight;
-            asm volatile("" : "+s"(n));                       // a value of its own: see stores_in_flight
+            asm volatile("" : "+s"(n));                       // a value of its own: see the 16-bit kernel
             if (n == STORES_F32) wait_loads_and_barrier<ALLOW + STORES_F32>();
             else if (n == STORES_BF16) wait_loads_and_barrier<ALLOW + STORES_BF16>();
             else wait_loads_and_barrier<0>();

@@ -306,7 +306,7 @@ void gemm_mxfp6_tiled_kernel(const Mx6Params p) {
             wait_loads_and_barrier<ALLOW>();
         } else {                                              // first stage after an epilogue
             int n = stores_in_flight;
-            asm volatile("" : "+s"(n));                       // a value of its own: see stores_in_flight
+            asm volatile("" : "+s"(n));                       // a value of its own: see the 16-bit kernel
             if (n == STORES_F32) wait_loads_and_barrier<ALLOW + STORES_F32>();
             else if (n == STORES_BF16) wait_loads_and_barrier<ALLOW + STORES_BF16>();
             else wait_loads_and_barrier<0>();
