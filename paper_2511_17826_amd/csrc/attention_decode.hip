@@ -18,7 +18,7 @@
 // K (two rounds ahead) and V (one) are fetched into registers, whole rows at a time, and turned around in
 // wavefront-private LDS.  Bound: many sequences, HBM; few, what one compute unit takes in (see plan_decode) and the two
 // barriers of a round (1.1 us per round without any load).  One barrier a round, the next round's scores formed beside this
-// one's weights, was 0.96 .. 1.02 of the time from 4096 keys on and 1 us slower up to 1024: intake it is.  K fragments loaded straight into the matrix instruction's
+// one's weights, was 0.96 .. 1.07 of the time from 4096 keys on and 1 us slower up to 1024: intake it is.  K fragments loaded straight into the matrix instruction's
 // layout (no LDS, 64 bytes of 16 rows per load) were slower: 47 instead of 34 us below.
 // Measured, 32 query heads over 8, bf16, time of a call on the stream, attention_kernel -> this kernel: 1 x 4096 keys
 // 90 -> 28 us, 6 sequences of 96 .. 4001 keys 89 -> 28 us, 16 x 4096 98 -> 56 us (4.8 TB/s of K + V), 64 x 4096
