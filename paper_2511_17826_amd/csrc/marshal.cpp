@@ -117,7 +117,7 @@ typedef void *P;
 typedef int64_t L;
 typedef size_t Z;
 
-// product(entry, X, Xs, W, Ws, leaf, k_first, out dtype or None, format or shards)
+// product(entry, X, Xs, W, Ws, leaf, k_first, out dtype (None where the kind has one of its own), format or shards)
 PyObject *product(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (n != 9) UNCOMMON;
     const Entry *e = entry_of(a[0], GEMM, MXFP4);
@@ -129,7 +129,7 @@ PyObject *product(PyObject *, PyObject *const *a, Py_ssize_t n) {
         if (!X || !W) UNCOMMON;
         const at::Tensor *Xs = nullptr, *Ws = nullptr;
         at::ScalarType out_type = at::kFloat;
-        if (a[7] != Py_None) {
+        if (kind == GEMM || kind >= FP8) {                        // None there is for torch to answer: new_empty takes X's type
             if (!THPDtype_Check(a[7])) UNCOMMON;
             out_type = ((THPDtype *)a[7])->scalar_type;
         }

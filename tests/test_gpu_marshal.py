@@ -101,6 +101,28 @@ def test_errors_are_those_of_the_library():
         torch.vmap(lambda t: tb.tbik_gemm(t, w, 128, 1))(torch.stack([x, x]))
 
 
+@pytest.mark.parametrize("name", ["gemm", "gemm_f16", "fp8", "mxfp8", "mxfp6", "mxfp4"])
+def test_no_output_type_is_answered_as_ctypes_answers_it(name, monkeypatch):
+    """out_dtype=None: torch's new_empty takes the operand's type, which the library has for 16 bits and not for bytes."""
+    f, args = CALLS[name](5)
+    args = args[:-1] if args[-1] is f32 else args
+
+    def answer():
+        try:
+            return f(*args, out_dtype=None)
+        except TypeError as e:
+            return str(e)
+
+    tb.lib()
+    native = answer()
+    monkeypatch.setattr(tb, "_native", tb._NotLoaded)
+    other = answer()
+    if name.startswith("gemm"):
+        assert native.dtype == other.dtype == args[0].dtype and torch.equal(native.view(u8), other.view(u8))
+    else:
+        assert native == other and "uint8" in native
+
+
 def test_another_stream_gets_a_workspace_of_its_own():
     x, w = rnd((33, 8 * K)), rnd((8 * K, N))
     want = tb.tbik_gemm(x, w, 128, 1)
