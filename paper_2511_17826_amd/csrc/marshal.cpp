@@ -74,9 +74,17 @@ at::Tensor output(at::IntArrayRef sizes, const at::Tensor &like, at::ScalarType 
 // torch's current stream on the current device, as the binding passes it.
 void *current_stream() { return (void *)c10::hip::getCurrentHIPStream(c10::hip::current_device()).stream(); }
 
+// Holds its tensor: while the interpreter lock is released another thread may put a larger one into the dict, and the
+// allocator would give this one's memory away before the call's kernels are queued.
 struct Room {
+    at::Tensor held;
     void *at = nullptr;
     size_t bytes = 0;
+    void take(const at::Tensor &ws) {
+        held = ws;
+        at = held.data_ptr();
+        bytes = (size_t)held.numel();
+    }
 };
 // The workspace of `need` bytes for `like`'s device and this stream; false: an error is set.
 bool room_for(size_t need, PyObject *like, const at::Tensor &t, void *stream, Room *room) {
@@ -89,7 +97,7 @@ bool room_for(size_t need, PyObject *like, const at::Tensor &t, void *stream, Ro
     if (w && THPVariable_Check(w)) {
         const at::Tensor &ws = THPVariable_Unpack(w);
         if ((size_t)ws.numel() >= need) {
-            *room = {ws.data_ptr(), (size_t)ws.numel()};
+            room->take(ws);
             return true;
         }
     }
@@ -98,8 +106,7 @@ bool room_for(size_t need, PyObject *like, const at::Tensor &t, void *stream, Ro
     PyObject *made = PyObject_CallFunction(make_workspace, "KO", (unsigned long long)need, device);
     Py_DECREF(device);
     if (!made) return false;
-    const at::Tensor &ws = THPVariable_Unpack(made);              // the dict keeps it
-    *room = {ws.data_ptr(), (size_t)ws.numel()};
+    room->take(THPVariable_Unpack(made));
     Py_DECREF(made);
     return true;
 }

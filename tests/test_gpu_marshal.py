@@ -1,5 +1,8 @@
 """The binding's common calls go through _marshal.so, all others through ctypes: the two give the same bits, and an argument
 that is not one of the common kind is answered (or refused) as ctypes answers it."""
+import ctypes as C
+import threading
+
 import pytest
 import torch
 
@@ -134,3 +137,49 @@ def test_another_stream_gets_a_workspace_of_its_own():
     s.synchronize()
     assert torch.equal(got, want)
     assert tb.gemm_16bit_workspace_bytes(33, N, 8 * K, 128, 1) == 0 or mine is not None
+
+
+FREE = 31                                                             # a number that no call of the library has
+
+
+@pytest.mark.parametrize("cached", [True, False])
+@pytest.mark.parametrize("kind", ["product", "row_reduce", "attention"])
+def test_a_workspace_outlives_the_call_that_uses_it(kind, cached):
+    """While a call is inside the library the interpreter lock is free, and another thread on the same stream may need a larger
+    workspace.  A function that stands for the library plays that thread: the workspace that the call was given is not handed
+    out again before the call is over.  No kernel runs."""
+    tb.lib()
+    need = 48 << 20                                                   # a block of its own in torch's allocator
+    args = {"product": [C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p, C.c_int64] + [C.c_int] * 6,
+            "row_reduce": [C.c_void_p, C.c_int, C.c_void_p, C.c_int, C.c_int, C.c_int64],
+            "attention": [C.c_void_p] * 6 + [C.c_int] * 8 + [C.c_int64] * 4 + [C.c_float, C.c_int]}[kind]
+    sizes = {"product": [C.c_int] * 5, "row_reduce": [C.c_int, C.c_int64, C.c_int], "attention": [C.c_int] * 5}[kind]
+    seen = []
+
+    def other_thread():
+        tb._workspace(2 * need, torch.device("cuda:0"))
+        seen.append({torch.empty(need, dtype=torch.uint8, device="cuda:0").data_ptr() for _ in range(2)})
+
+    @C.CFUNCTYPE(C.c_int, *args, C.c_void_p, C.c_size_t, C.c_void_p)
+    def call(*a):
+        seen.append(a[-3])
+        t = threading.Thread(target=other_thread)
+        t.start()
+        t.join()
+        return 0
+
+    query = C.CFUNCTYPE(C.c_size_t, *sizes)(lambda *a: need)
+    address = lambda f: C.cast(f, C.c_void_p).value
+    tb._native.register(FREE, {"product": 0, "row_reduce": 10, "attention": 11}[kind], address(call), address(query), bf)
+    torch.cuda.synchronize()
+    tb._ws_cache.clear()
+    torch.cuda.empty_cache()
+    if cached:
+        tb._workspace(need, torch.device("cuda:0"))
+    x = rnd((4, K))
+    q = rnd((4, 2, 128))
+    y = {"product": lambda: tb._native.product(FREE, x, None, rnd((K, N)), None, 128, 1, bf, 0),
+         "row_reduce": lambda: tb._native.row_reduce(FREE, x, 0),
+         "attention": lambda: tb._native.attention(FREE, q, q, q, cu(0, 4), cu(0, 4), 4, 0.1, True, 4)}[kind]()
+    assert torch.is_tensor(y) and len(seen) == 2
+    assert seen[0] and seen[0] not in seen[1]
