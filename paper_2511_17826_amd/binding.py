@@ -170,7 +170,7 @@ def _load_native(L: C.CDLL):
     address = lambda name: C.cast(getattr(L, name), C.c_void_p).value
     for name, (number, kind, need, dtype) in _NATIVE.items():
         m.register(number, kind, address(name.split(" ")[0]), address(need) if need else 0, dtype)
-    m.use(_ws_cache, _workspace)
+    m.use(_ws_cache, lambda nbytes, device: _workspace(nbytes, device))      # looked up at the call, as the way through ctypes does
     return m
 
 

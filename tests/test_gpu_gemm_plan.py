@@ -151,8 +151,12 @@ def test_workspace_of_the_older_rule_alone(kind, M, Kl, leaf, kf, rule):
 def test_a_16_bit_call_holds_no_planes_of_the_fp32_plans(monkeypatch):
     """600 rows of 4096 x 4096: no planes in 16 bits, 75 MiB in fp32."""
     asked = []
+    tb.lib()
+    tb._ws_cache.clear()                                              # what is there is taken without asking
     monkeypatch.setattr(tb, "_workspace", lambda nbytes, device, real=tb._workspace: asked.append(nbytes) or real(nbytes, device))
     for dt, call, parts in ((torch.bfloat16, tb.tbik_gemm, tb.tbik_gemm_shard_partials), (torch.float16, tb.tbik_gemm_f16, tb.tbik_gemm_shard_partials_f16)):
         X, W = torch.ones((600, 4096), dtype=dt, device="cuda:0"), torch.ones((4096, 4096), dtype=dt, device="cuda:0")
         assert (call(X, W, 256, 1) == 4096).all() and (parts(X, W, 256, 1, 2) == 2048).all()
     assert asked == []
+    assert (tb.tbik_gemm_f32(torch.ones((600, 4096), device="cuda:0"), torch.ones((4096, 4096), device="cuda:0"), 256, 1) == 4096).all()
+    assert asked and min(asked) >= 600 * 4096 * 4                     # a call that needs planes asks here
