@@ -11,6 +11,8 @@ import ctypes as C
 import importlib.machinery
 import importlib.util
 import os
+import sys
+import warnings
 
 import torch
 
@@ -125,8 +127,10 @@ SIGNATURES = {
 
 _lib = None
 
-# The common calls -- no `out`, no `workspace`, ordinary tensors -- are marshalled by _marshal.so (csrc/marshal.cpp); it answers None
-# to any other, which then takes the way through ctypes below and gets that way's answers and errors.
+# The common calls -- no `out`, no `workspace`, ordinary tensors -- are marshalled by csrc/marshal.cpp; it answers None to any other,
+# which then takes the way through ctypes below and gets that way's answers and errors.  It uses torch's C++ classes, so its
+# name says for which Python and torch it was built; a process of others does not find it and takes ctypes for every call.
+MARSHAL_PATH = os.path.join(_HERE, "_marshal.%s.torch-%s.so" % (sys.implementation.cache_tag, torch.__version__))
 # name -> (number there, kind of call, workspace query, operand dtype)
 _NATIVE = {name: (i, *spec) for i, (name, *spec) in enumerate([
     ("tbik_gemm", 0, "tbik_gemm_16bit_workspace_bytes", torch.bfloat16),
@@ -153,7 +157,7 @@ _NUMBER = {name: spec[0] for name, spec in _NATIVE.items()}
 
 
 class _NotLoaded:
-    """Stands for _marshal.so until the library is loaded: no call is a common one."""
+    """Stands for the native half until the library is loaded, and where it cannot be loaded: no call is a common one."""
     product = rmsnorm = combine = row_reduce = attention = staticmethod(lambda *a: None)
 
 
@@ -161,12 +165,14 @@ _native = _NotLoaded
 
 
 def _load_native(L: C.CDLL):
-    path = os.path.join(_HERE, "_marshal.so")
-    if not os.path.exists(path):
-        raise RuntimeError("_marshal.so is not built: run `python -m paper_2511_17826_amd.build`")
-    loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
-    m = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", path, loader=loader))
-    loader.exec_module(m)
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("_marshal", MARSHAL_PATH)
+        m = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", MARSHAL_PATH, loader=loader))
+        loader.exec_module(m)
+    except ImportError as e:
+        warnings.warn("calls go through ctypes, at 2 to 4 us more each: no native half of the binding for this Python and torch (%s); "
+                      "`python -m paper_2511_17826_amd.build` builds it" % e, RuntimeWarning, stacklevel=3)
+        return _NotLoaded
     address = lambda name: C.cast(getattr(L, name), C.c_void_p).value
     for name, (number, kind, need, dtype) in _NATIVE.items():
         m.register(number, kind, address(name.split(" ")[0]), address(need) if need else 0, dtype)
@@ -206,7 +212,7 @@ def _check(status: int, where: str):
 
 
 def _done(y, entry: str):
-    """What _marshal.so answered to a common call: the output, or the library's status."""
+    """What the native half answered to a common call: the output, or the library's status."""
     if y.__class__ is int:
         _check(y, entry)
     return y

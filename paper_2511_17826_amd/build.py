@@ -3,7 +3,7 @@
     python -m paper_2511_17826_amd.build
 
 hipcc cross-compiles without a GPU.  Object files go to ``paper_2511_17826_amd/_build/``,
-the library to ``paper_2511_17826_amd/libtbik.so``.
+the library to ``paper_2511_17826_amd/libtbik.so``, the binding's native half beside it.
 """
 from __future__ import annotations
 
@@ -29,22 +29,25 @@ FLAGS = ["--offload-arch=gfx950", "-mllvm", "-amdgpu-mfma-vgpr-form", "-O3", "-s
          "-Wno-unknown-attributes", "-Wno-inline-asm"]
 
 
-MARSHAL = os.path.join(HERE, "_marshal.so")     # the binding's native half (csrc/marshal.cpp): host code against torch's headers
-
-
-def _build_marshal() -> None:
+def _build_marshal() -> str:
+    """The binding's native half (csrc/marshal.cpp): host code against the headers of this Python and this torch."""
     import sysconfig
 
     import torch
+
+    from .binding import MARSHAL_PATH
     t = os.path.dirname(torch.__file__)
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-w",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-Wall", "-I" + os.path.join(os.path.dirname(HERE), "include"),
            "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_paths()["include"], "-isystem", "/opt/rocm/include",
-           os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL, "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+           os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL_PATH, "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("g++ failed on marshal.cpp:\n%s" % r.stderr)
+    if r.stderr.strip():
+        print(r.stderr, file=sys.stderr)
+    return MARSHAL_PATH
 
 
 def _hipcc() -> str:
@@ -93,9 +96,8 @@ def build(save_temps: bool = True, jobs: int = 8, defines=(), lib_path: str = LI
     os.makedirs(BUILD, exist_ok=True)
     extra = (["-save-temps=obj"] if save_temps else []) + ["-D" + d for d in defines]
     with ThreadPoolExecutor(max_workers=jobs) as ex:
-        marshal = ex.submit(_build_marshal)
+        marshal = ex.submit(_build_marshal) if lib_path == LIB else None      # it takes any build of the library
         objs = list(ex.map(lambda s: _compile(s, extra), SOURCES))
-        marshal.result()
     if save_temps:
         check_generated_code(os.path.join(BUILD, "gemm_tiled-hip-amdgcn-amd-amdhsa-gfx950.s"), "gemm_tiled_kernel")
         check_generated_code(os.path.join(BUILD, "attention-hip-amdgcn-amd-amdhsa-gfx950.s"), "attention_")
@@ -108,6 +110,8 @@ def build(save_temps: bool = True, jobs: int = 8, defines=(), lib_path: str = LI
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stdout + r.stderr)
+    if marshal:
+        marshal.result()
     return lib_path
 
 

@@ -271,3 +271,22 @@ def test_workspace_sizes_do_not_depend_on_what_was_asked_before(L):
     [ask(s) for s in shapes]
     L.tbik_set_gemm_variant(0)
     assert all(ask(s) == first[s] for s in again)
+
+
+@pytest.mark.parametrize("there", ["nothing", "no library"])
+def test_the_binding_loads_without_its_native_half(there, tmp_path, monkeypatch):
+    """Built for another Python or torch, or not built: every call takes ctypes, which needs the library alone."""
+    import sys
+
+    import torch
+
+    from paper_2511_17826_amd import binding as tb
+    assert sys.implementation.cache_tag in tb.MARSHAL_PATH and torch.__version__ in tb.MARSHAL_PATH
+    if there == "no library":
+        (tmp_path / "_marshal.so").write_text("text")
+    monkeypatch.setattr(tb, "MARSHAL_PATH", str(tmp_path / "_marshal.so"))
+    monkeypatch.setattr(tb, "_lib", None)
+    monkeypatch.setattr(tb, "_native", tb._native)
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        assert tb.lib().tbik_version()
+    assert tb._native is tb._NotLoaded

@@ -1,4 +1,4 @@
-"""The binding's common calls go through _marshal.so, all others through ctypes: the two give the same bits, and an argument
+"""The binding's common calls go through its native half (csrc/marshal.cpp), all others through ctypes: the two give the same bits, and an argument
 that is not one of the common kind is answered (or refused) as ctypes answers it."""
 import ctypes as C
 import threading
