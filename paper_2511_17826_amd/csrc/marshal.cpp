@@ -18,6 +18,8 @@
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include "tbik.h"
+
 namespace {
 
 enum Kind { GEMM, GEMM_F32, PARTIALS, PARTIALS_F32, SWIGLU, FP8, MX, MXFP4, RMSNORM, COMBINE, ROWS, ATTENTION, KINDS };
@@ -30,8 +32,6 @@ constexpr int MAX_ENTRIES = 32;
 Entry entries[MAX_ENTRIES];                     // written while the library is loaded, under the interpreter lock
 PyObject *workspaces = nullptr;                 // the binding's dict: (device index, stream) -> uint8 tensor
 PyObject *make_workspace = nullptr;             // the binding's function that fills it
-
-constexpr int TBIK_F32 = 0, TBIK_BF16 = 1, TBIK_F16 = 2, TBIK_LOGSOFTMAX = 2;
 
 // A plain strided GPU tensor: no subclass, no wrapper of a transform, real sizes and memory.
 const at::Tensor *plain(PyObject *o, int dim) {
@@ -119,10 +119,28 @@ const Entry *entry_of(PyObject *o, int kind_from, int kind_to) {
     return &entries[i];
 }
 
-typedef size_t (*NeedFn)(int, int, int, int, int);
+// Entries are called through the types that tbik.h declares for them; those of one kind have one type.
+#define SAME(a, b) static_assert(std::is_same<decltype(&a), decltype(&b)>::value, #a " and " #b)
+SAME(tbik_gemm, tbik_gemm_f16);
+SAME(tbik_gemm, tbik_gemm_swiglu);
+SAME(tbik_gemm_shard_partials, tbik_gemm_shard_partials_f16);
+SAME(tbik_gemm_shard_partials, tbik_gemm_shard_partials_f32);
+SAME(tbik_gemm_mxfp8, tbik_gemm_mxfp6);
+SAME(tbik_rmsnorm, tbik_rmsnorm_f16);
+SAME(tbik_combine_residual_rmsnorm, tbik_combine_residual_rmsnorm_f16);
+SAME(tbik_attention, tbik_attention_f16);
+SAME(tbik_gemm_16bit_workspace_bytes, tbik_gemm_f32_workspace_bytes);
+SAME(tbik_gemm_16bit_workspace_bytes, tbik_gemm_swiglu_workspace_bytes);
+SAME(tbik_gemm_16bit_workspace_bytes, tbik_gemm_fp8_workspace_bytes);
+SAME(tbik_gemm_16bit_workspace_bytes, tbik_gemm_mxfp8_workspace_bytes);
+SAME(tbik_gemm_16bit_workspace_bytes, tbik_gemm_mxfp6_workspace_bytes);
+SAME(tbik_gemm_16bit_workspace_bytes, tbik_gemm_mxfp4_workspace_bytes);
+SAME(tbik_gemm_16bit_workspace_bytes, tbik_attention_workspace_bytes);
+#undef SAME
+#define CALL(name) ((decltype(&name))e->call)
+#define NEED(name) ((decltype(&name))e->need)
 typedef void *P;
 typedef int64_t L;
-typedef size_t Z;
 
 // product(entry, X, Xs, W, Ws, leaf, k_first, out dtype (None where the kind has one of its own), format or shards)
 PyObject *product(PyObject *, PyObject *const *a, Py_ssize_t n) {
@@ -174,21 +192,21 @@ PyObject *product(PyObject *, PyObject *const *a, Py_ssize_t n) {
         if (!Y.defined()) UNCOMMON;
         void *stream = current_stream();
         Room ws;
-        if (!room_for(e->need ? ((NeedFn)e->need)(M, N, K, leaf, k_first) : 0, a[1], *X, stream, &ws)) return nullptr;
+        if (!room_for(e->need ? NEED(tbik_gemm_16bit_workspace_bytes)(M, N, K, leaf, k_first) : 0, a[1], *X, stream, &ws)) return nullptr;
         P x = X->data_ptr(), w = W->data_ptr(), y = Y.data_ptr(), xs = Xs ? Xs->data_ptr() : nullptr, wsc = Ws ? Ws->data_ptr() : nullptr;
         const L ldx = X->stride(0), ldw = W->stride(0), ldxs = Xs ? Xs->stride(0) : 0, ldws = Ws ? Ws->stride(0) : 0, ldy = partials ? 0 : Y.stride(0);
-        const int yt = type_code(Y.scalar_type());
+        const tbik_dtype yt = (tbik_dtype)type_code(Y.scalar_type());
         int st = 0;
         Py_BEGIN_ALLOW_THREADS
         switch (kind) {
-            case GEMM: st = ((int (*)(P, L, P, L, P, L, int, int, int, int, int, int, P, Z, P))e->call)(x, ldx, w, ldw, y, ldy, yt, M, N, K, leaf, k_first, ws.at, ws.bytes, stream); break;
-            case GEMM_F32: st = ((int (*)(P, L, P, L, P, L, int, int, int, int, int, P, Z, P))e->call)(x, ldx, w, ldw, y, ldy, M, N, K, leaf, k_first, ws.at, ws.bytes, stream); break;
+            case GEMM:
+            case SWIGLU: st = CALL(tbik_gemm)(x, ldx, w, ldw, y, ldy, yt, M, N, K, leaf, k_first, ws.at, ws.bytes, stream); break;
+            case GEMM_F32: st = CALL(tbik_gemm_f32)(x, ldx, w, ldw, y, ldy, M, N, K, leaf, k_first, ws.at, ws.bytes, stream); break;
             case PARTIALS:
-            case PARTIALS_F32: st = ((int (*)(P, L, P, L, P, int, int, int, int, int, int, P, Z, P))e->call)(x, ldx, w, ldw, y, M, N, K, leaf, k_first, extra, ws.at, ws.bytes, stream); break;
-            case SWIGLU: st = ((int (*)(P, L, P, L, P, L, int, int, int, int, int, int, P, Z, P))e->call)(x, ldx, w, ldw, y, ldy, yt, M, N, K, leaf, k_first, ws.at, ws.bytes, stream); break;
-            case FP8: st = ((int (*)(P, L, P, L, P, L, int, int, int, int, int, int, int, P, Z, P))e->call)(x, ldx, w, ldw, y, ldy, yt, extra, M, N, K, leaf, k_first, ws.at, ws.bytes, stream); break;
-            case MX: st = ((int (*)(P, L, P, L, P, L, P, L, P, L, int, int, int, int, int, int, int, P, Z, P))e->call)(x, ldx, xs, ldxs, w, ldw, wsc, ldws, y, ldy, yt, extra, M, N, K, leaf, k_first, ws.at, ws.bytes, stream); break;
-            case MXFP4: st = ((int (*)(P, L, P, L, P, L, P, L, P, L, int, int, int, int, int, int, P, Z, P))e->call)(x, ldx, xs, ldxs, w, ldw, wsc, ldws, y, ldy, yt, M, N, K, leaf, k_first, ws.at, ws.bytes, stream); break;
+            case PARTIALS_F32: st = CALL(tbik_gemm_shard_partials)(x, ldx, w, ldw, (float *)y, M, N, K, leaf, k_first, extra, ws.at, ws.bytes, stream); break;
+            case FP8: st = CALL(tbik_gemm_fp8)(x, ldx, w, ldw, y, ldy, yt, (tbik_dtype)extra, M, N, K, leaf, k_first, ws.at, ws.bytes, stream); break;
+            case MX: st = CALL(tbik_gemm_mxfp8)(x, ldx, xs, ldxs, w, ldw, wsc, ldws, y, ldy, yt, (tbik_dtype)extra, M, N, K, leaf, k_first, ws.at, ws.bytes, stream); break;
+            case MXFP4: st = CALL(tbik_gemm_mxfp4)(x, ldx, xs, ldxs, w, ldw, wsc, ldws, y, ldy, yt, M, N, K, leaf, k_first, ws.at, ws.bytes, stream); break;
         }
         Py_END_ALLOW_THREADS
         return wrapped(std::move(Y), st);
@@ -213,7 +231,7 @@ PyObject *rmsnorm(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const int M = (int)x->size(0), H = (int)x->size(1);
         int st;
         Py_BEGIN_ALLOW_THREADS
-        st = ((int (*)(P, P, P, int, int, float, P))e->call)(px, pw, py, M, H, eps, stream);
+        st = CALL(tbik_rmsnorm)(px, pw, py, M, H, eps, stream);
         Py_END_ALLOW_THREADS
         return wrapped(std::move(y), st);
     } catch (const std::exception &) {
@@ -239,7 +257,7 @@ PyObject *combine(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const int shards = (int)p->size(0), M = (int)r->size(0), H = (int)r->size(1);
         int st;
         Py_BEGIN_ALLOW_THREADS
-        st = ((int (*)(P, int, P, P, float, P, P, int, int, P))e->call)(pp, shards, pr, pw, eps, ph, py, M, H, stream);
+        st = CALL(tbik_combine_residual_rmsnorm)((const float *)pp, shards, pr, pw, eps, ph, py, M, H, stream);
         Py_END_ALLOW_THREADS
         if (st) return PyLong_FromLong(st);
         PyObject *hidden = THPVariable_Wrap(std::move(h));
@@ -275,13 +293,13 @@ PyObject *row_reduce(PyObject *, PyObject *const *a, Py_ssize_t n) {
         void *stream = current_stream();
         Room ws;
         // (the binding always passes a workspace here, of 256 bytes at least)
-        const size_t need = ((size_t (*)(int, L, int))e->need)(M, V, op);
+        const size_t need = NEED(tbik_row_reduce_workspace_bytes)(M, V, (tbik_rowop)op);
         if (!room_for(need ? need : 1, a[1], *x, stream, &ws)) return nullptr;
         P px = x->data_ptr(), py = y.data_ptr();
-        const int t = type_code(x->scalar_type());
+        const tbik_dtype t = (tbik_dtype)type_code(x->scalar_type());
         int st;
         Py_BEGIN_ALLOW_THREADS
-        st = ((int (*)(P, int, P, int, int, L, P, Z, P))e->call)(px, t, py, op, M, V, ws.at, ws.bytes, stream);
+        st = CALL(tbik_row_reduce)(px, t, py, (tbik_rowop)op, M, V, ws.at, ws.bytes, stream);
         Py_END_ALLOW_THREADS
         return wrapped(std::move(y), st);
     } catch (const std::exception &) {
@@ -314,14 +332,14 @@ PyObject *attention(PyObject *, PyObject *const *a, Py_ssize_t n) {
         if (!O.defined()) UNCOMMON;
         void *stream = current_stream();
         Room ws;
-        if (!room_for(((NeedFn)e->need)(batch, max_q, max_k < Tk ? max_k : Tk, Hq, Hkv), a[1], Q, stream, &ws)) return nullptr;
+        if (!room_for(NEED(tbik_attention_workspace_bytes)(batch, max_q, max_k < Tk ? max_k : Tk, Hq, Hkv), a[1], Q, stream, &ws)) return nullptr;
         P q = Q.data_ptr(), k = K.data_ptr(), v = V.data_ptr(), o = O.data_ptr(), pq = cq->data_ptr(), pk = ck->data_ptr();
         const L sq = Q.stride(0), sk = K.stride(0), sv = V.stride(0), so = O.stride(0);
         const int causal = a[8] == Py_True;
         int st;
         Py_BEGIN_ALLOW_THREADS
-        st = ((int (*)(P, P, P, P, P, P, int, int, int, int, int, int, int, int, L, L, L, L, float, int, P, Z, P))e->call)(
-            q, k, v, o, pq, pk, batch, max_q, max_k, Tq, Tk, Hq, Hkv, 128, sq, sk, sv, so, scale, causal, ws.at, ws.bytes, stream);
+        st = CALL(tbik_attention)(
+            q, k, v, o, (const int32_t *)pq, (const int32_t *)pk, batch, max_q, max_k, Tq, Tk, Hq, Hkv, 128, sq, sk, sv, so, scale, causal, ws.at, ws.bytes, stream);
         Py_END_ALLOW_THREADS
         return wrapped(std::move(O), st);
     } catch (const std::exception &) {
