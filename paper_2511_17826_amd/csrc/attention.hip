@@ -351,11 +351,16 @@ void attention_kernel(const AttnParams p) {
     // A body: the softmax step of tile t beside S = K Q^T of tile t + 1 (NEXT) and O += V^T P^T of tile t, in slots of one
     // matrix instruction with its share of the vector work and of the LDS reads to come.  The product needs the weights
     // eight keys of a half at a time, so the second half of them is formed beside its first half.
-    // What bounds it: a tile is 1024 cycles of the matrix pipe and about 1150 of the vector ALU's issue port, and the wavefront
-    // has to offer both at the same time for the SIMD's two wavefronts to keep both busy.  Run one after the other, with each
-    // pair of K fragments read just before its use, they took 2346 cycles a tile and wavefront (matrix pipe busy 44 %); so
-    // they take 2130 (48 %), at a clock that falls from 2.03 to 1.89 GHz: the chip's power is what is left.  4 x 4096 tokens,
-    // 32 heads over 8: 594 -> 572 us, 1 x 16384 2210 -> 2133, 1000 tokens 29.2 -> 25.3, four prompts of 1531 .. 4096 369 -> 349.
+    // What bounds it: a tile is 1024 cycles of the matrix pipe and 1258 of the vector ALU, and a wavefront has to offer both at the
+    // same time for the SIMD's two wavefronts to keep both busy.  Run one after the other, with each pair of K fragments read just
+    // before its use, they took 2363 cycles a tile and SIMD over the launch (matrix pipe busy 43 %); so they take 2075 (49 %): hardly less than
+    // the two together, each is idle half the time, and why two wavefronts overlap so little is not known.  A part of each gain
+    // goes to the clock, which falls from 2.06 to 1.90 GHz.  Device time, one after the other -> here: 4 x 4096 tokens, 32 heads
+    // over 8, 601 -> 574 us, 1 x 16384 2221 -> 2130, 1000 tokens 29.5 -> 25.1, four prompts of 1531 .. 4096 372 -> 353.  Up to 128
+    // tokens a prompt is over before anything overlaps: the same time, but 9 to 16 prompts of 65 .. 112 tokens 1.02 .. 1.08 of it.
+    // The direct loads go first: the next barrier waits for them, and spread over the slots they arrived late where one wavefront
+    // works and HBM is the bound (18 sequences of 2048 keys, 16 heads over 16, one query each: 71 us spread, 64.5 so, 61 one after
+    // the other; 12 decodes beside 512 queries 72 spread, 62 so); all of them before the first slot are 2 to 8 % slower in prefill.
     // (One wavefront per SIMD with two such sets of queries in 512 registers issues an instruction every five cycles
     // whatever it is, 930 of them for two tiles: 690 us.)  Masked tiles and a wavefront's last one run without NEXT: a copy
     // of the body with both spills 600 registers.
@@ -421,14 +426,8 @@ void attention_kernel(const AttnParams p) {
                 o[j & 3] = mfma_32x32x16<F16>(vf[j % (V_AHEAD + 1)].v, w.v[j >> 2], o[j & 3]);
             }
             if (i >= 16 - V_AHEAD && i + V_AHEAD < 32) read_v(BUF, i + V_AHEAD - 16);
-            if constexpr (NEXT && i == 1) load_k(I0{});
-            if constexpr (NEXT && i == 3) load_k(I1{});
-            if constexpr (NEXT && i == 5) load_k(I2{});
-            if constexpr (NEXT && i == 9) load_k(I3{});
-            if constexpr (NEXT && i == 17) load_v(I0{});
-            if constexpr (NEXT && i == 20) load_v(I1{});
-            if constexpr (NEXT && i == 24) load_v(I2{});
-            if constexpr (NEXT && i == 27) load_v(I3{});
+            if constexpr (NEXT && i < 4) load_k(std::integral_constant<int, i & 3>{});
+            if constexpr (NEXT && i >= 4 && i < 8) load_v(std::integral_constant<int, i & 3>{});
             if constexpr (i < EXP_SLOT - 1) scale_and_mask(s, mask_tag, i + 2, rel, tmax);
             if constexpr (i == EXP_SLOT - 1) new_maximum(tmax, m_use, alpha);
             if constexpr (i >= EXP_SLOT && i < EXP_SLOT + EXP_SLOTS) {
@@ -441,29 +440,40 @@ void attention_kernel(const AttnParams p) {
                     else even = x;
                 }
             }
-            __builtin_amdgcn_sched_barrier(0);
-        });
+            if constexpr (NEXT) __builtin_amdgcn_sched_barrier(0);    // without NEXT there is nothing to hold apart: in slots the
+        });                                                           // exponentials waited for each other
         add_sum(psum, alpha);
     };
     // The same one step after the other, for the tiles that some row does not see whole and the last ones.
     auto scores_alone = [&](int buf, scores &s) __attribute__((always_inline)) {
         const f32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
+        for (int ks = 0; ks < K_AHEAD; ++ks) read_k(buf, ks);
+#pragma unroll
         for (int ks = 0; ks < ATT_D / 16; ++ks) {
-            read_k(buf, ks);
+            if (ks + K_AHEAD < ATT_D / 16) read_k(buf, ks + K_AHEAD);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) s[kb] = mfma_32x32x16<F16>(kf[ks % (K_AHEAD + 1)][kb], bq[ks], ks == 0 ? zero : s[kb]);
         }
     };
+    // K_{t+1} and V_t are there, K_t and V_{t-1} have been read (by loads that came back, wherever their uses were scheduled).
+    auto wait_and_barrier = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
     auto next_tile = [&](int t) __attribute__((always_inline)) {
-        asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");   // K_{t+1} and V_t are there, K_t and V_{t-1} have been read
+        wait_and_barrier();
         aim_k(t + 2);
         aim_v(t + 1);
     };
     auto last_body = [&](auto buf_tag, scores &s, scores &next, int t) __attribute__((always_inline)) {
-        next_tile(t);
-        if (t + 2 < t_end) all_k();
-        if (t + 1 < t_end) all_v();
+        wait_and_barrier();
+        if (t + 2 < t_end) {
+            aim_k(t + 2);
+            all_k();
+        }
+        if (t + 1 < t_end) {
+            aim_v(t + 1);
+            all_v();
+        }
         if (t < w_end) {
             if (t + 1 < w_end) scores_alone(decltype(buf_tag)::value ^ 1, next);
             body(buf_tag, std::false_type{}, std::true_type{}, s, next, t);

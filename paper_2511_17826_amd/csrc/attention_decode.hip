@@ -502,15 +502,17 @@ static bool launches(int batch, int max_seqlen_q, int heads_q, int heads_kv) {
 
 // Where attention_kernel is the quicker one although a sequence has few queries: it has two workgroups on a compute unit
 // where this kernel has one, so it is a matter of rounds, and only for groups that it packs into one workgroup (powers of
-// two; the others it reads once per query head).  Times of the two, attention_kernel first, 8800 shapes of 1 .. 10000 keys:
+// two; the others it reads once per query head).  Times of the two, attention_kernel first; the lines were drawn on 8800 shapes
+// of 1 .. 10000 keys.  Since then that kernel overlaps its tiles: over 1500 shapes timed again the choice is 0.3 % above the quicker
+// kernel in the mean, more than 4 % above it at 46 (24 % at most), most of them on this kernel's side of a line.
 //   * More than 16 rows on a key/value head: its keys are read here by two workgroups.  64 heads over 8, 4 queries: 33
-//     sequences of 4096 keys 141 / 177 us, 32 of 64 keys 10.0 / 11.8 (16 of them 8 / 6), 128 of 1024 keys 114 / 151.
-//   * One key tile is over before the rounds overlap.  32 heads over 32: 9 sequences of 64 keys 9.9 / 11.5 us, 200 of them
-//     89 / 113; two query heads per key/value head lose from 3 rounds on, four from 7 (a tenth at most).  (4 heads over 4: 128
-//     sequences 13.6 / 11.4, the neighbours lose as well; left to this kernel.)
+//     sequences of 4096 keys 131 / 174 us, 32 of 64 keys 10.0 / 11.1 (16 of them 8.1 / 6.3), 128 of 1024 keys 112 / 155.
+//   * One key tile is over before the rounds overlap.  32 heads over 32: 9 sequences of 64 keys 9.5 / 10.1 us, 200 of them
+//     91 / 108; two query heads per key/value head lose from 3 rounds on, four from 7 (a tenth at most).  (4 heads over 4: 128
+//     sequences 14.0 / 10.8, the neighbours lose as well; left to this kernel.)
 //   * Sequences of nearly one length and a second round that is nearly empty.  16 heads over 16: 18 sequences of 2048 keys
-//     take 1.19 times the time here, 22 of them 1.08, 28 1.02; 32 heads over 8: 33 of 4096 keys 1.09 .. 1.12, 40 of them
-//     1.02 .. 1.06, 48 1.01.  With lengths spread over a factor of ten this kernel wins there, by 1.1 to 2.5.
+//     take 1.14 times the time here, 22 of them 1.09, 28 1.02; 32 heads over 8: 33 of 4096 keys 1.20, 40 of them 1.11, 48
+//     1.05 (1.01 when the line was drawn).  With lengths spread over a factor of ten this kernel wins there, by 1.1 to 2.5.
 static bool attention_kernel_is_quicker(const AttnArgs &a) {
     const int group = a.heads_q / a.heads_kv;
     if (group & (group - 1)) return false;
