@@ -991,12 +991,19 @@ static AttnPlan plan_attention(int batch, int64_t total_q, int max_seqlen_k, int
                                                                   // workgroups would pair the busy ones up on half the compute units
     pl.nchunks = (pl.nb + pl.chunk - 1) / pl.chunk;
     pl.chunks_per_launch = pl.nchunks;
-    if (pl.splits_max > 1 && pl.n_splits == 1) {
-        const int64_t most = std::max<int64_t>(1, std::min<int64_t>(pl.nchunks, ATT_MAX_STATES / ((int64_t)pl.chunk * pl.ny)));
+    int64_t launch_items = pl.items;
+    auto pieces_of = [&](int64_t states) {
+        const int64_t most = std::max<int64_t>(1, std::min<int64_t>(pl.nchunks, states / ((int64_t)pl.chunk * pl.ny)));
         const int64_t pieces = (pl.nchunks + most - 1) / most;
         pl.chunks_per_launch = (pl.nchunks + pieces - 1) / pieces;
+        launch_items = std::min<int64_t>(pl.items, pl.chunks_per_launch * pl.chunk * pl.ny);
+    };
+    if (pl.splits_max > 1 && pl.n_splits == 1) {
+        pieces_of(ATT_MAX_STATES);
+        // Half of a bound above the limit may be less than all of the call below it: as many pieces as the caller's room asks for.
+        // (One chunk fits always: chunks grow with the items, and the advertised size holds one chunk of the bound or all of it.)
+        if ((size_t)launch_items * state > workspace_bytes) pieces_of((int64_t)(workspace_bytes / state));
     }
-    const int64_t launch_items = std::min<int64_t>(pl.items, pl.chunks_per_launch * pl.chunk * pl.ny);
     pl.state_bytes = pl.splits_max > 1 ? (size_t)(pl.n_splits > 1 ? pl.items * pl.n_splits : launch_items) * state : 0;
     return pl;
 }

@@ -295,6 +295,28 @@ def test_splits_one_workgroup_per_split_or_one_for_all_same_bits():
         assert np.array_equal(run(one)[0], O1[i]), i
 
 
+def test_a_call_well_below_the_bound_its_workspace_was_sized_from():
+    """Long keys and many items: the advertised size holds half of the bound's items (65 blocks of 48 heads are launched in two
+    pieces), which is less than all of this call's (54 blocks, one piece where there is room): it then runs in pieces too."""
+    H, q_lens = 48, [704] + [548] * 8 + [544]
+    k_lens = [4200] + q_lens[1:]
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(5)
+    rnd = lambda n: torch.randn((n, H, 128), generator=g, device="cuda:0").to(torch.bfloat16)
+    Q, K, V = rnd(sum(q_lens)), rnd(sum(k_lens)), rnd(sum(k_lens))
+    cu_q, cu_k = i32(np.cumsum([0] + q_lens)), i32(np.cumsum([0] + k_lens))
+    state, advertised = 68 << 10, tb.attention_workspace_bytes(10, 704, 4200, H, H)
+    items = (sum(q_lens) // 128 + 10) * H
+    assert advertised < items * state
+    ask = lambda ws: tb.tbik_attention(Q, K, V, cu_q, cu_k, 704, 128 ** -0.5, max_seqlen_k=4200, workspace=ws)
+    room = torch.empty(items * state, dtype=torch.uint8, device="cuda:0")
+    want = ask(room)
+    assert torch.equal(ask(room[:advertised]).view(torch.int16), want.view(torch.int16))
+    assert torch.equal(ask(None).view(torch.int16), want.view(torch.int16))
+    with pytest.raises(tb.TbikError, match="workspace"):
+        ask(room[:advertised - 256])
+
+
 def test_ragged_batch_with_sequences_of_different_split_counts():
     """One call with sequences of 1 to 4 splits (and one without keys): the workgroups of splits past a sequence's end
     write the empty state, the fold skips it; every row equals the row of a call with that sequence alone."""
