@@ -354,7 +354,7 @@ void attention_kernel(const AttnParams p) {
     // What bounds it: a tile is 1024 cycles of the matrix pipe and 1258 of the vector ALU, and a wavefront has to offer both at the
     // same time for the SIMD's two wavefronts to keep both busy.  Run one after the other, with each pair of K fragments read just
     // before its use, they took 2363 cycles a tile and SIMD over the launch (matrix pipe busy 43 %); so they take 2075 (49 %): hardly less than
-    // the two together, each is idle half the time, and why two wavefronts overlap so little is not known.  A part of each gain
+    // the two together, and why two wavefronts overlap so little is not known.  A part of each gain
     // goes to the clock, which falls from 2.06 to 1.90 GHz.  Device time, one after the other -> here: 4 x 4096 tokens, 32 heads
     // over 8, 601 -> 574 us, 1 x 16384 2221 -> 2130, 1000 tokens 29.5 -> 25.1, four prompts of 1531 .. 4096 372 -> 353.  Up to 128
     // tokens a prompt is over before anything overlaps: the same time, but 9 to 16 prompts of 65 .. 112 tokens 1.02 .. 1.08 of it.

@@ -16,10 +16,11 @@
 // folds its products in eight consecutive k at a time in ascending order, as two chained 32x32x16 instructions do
 // (0 differing bits in 51 million outputs over operands and accumulators spread over tens of binades, both formats).
 // K (two rounds ahead) and V (one) are fetched into registers, whole rows at a time, and turned around in
-// wavefront-private LDS.  Bound: many sequences, HBM; few, what one compute unit takes in (see plan_decode) and the two
-// barriers of a round (1.1 us per round without any load).  One barrier a round, the next round's scores formed beside this
-// one's weights, was 0.96 .. 1.07 of the time from 4096 keys on and 1 us slower up to 1024: intake it is.  K fragments loaded straight into the matrix instruction's
-// layout (no LDS, 64 bytes of 16 rows per load) were slower: 47 instead of 34 us below.
+// wavefront-private LDS.  Bound: many sequences, HBM; few, what one compute unit takes in (see plan_decode; 48 bytes/ns for a lone
+// sequence of 4096 keys) and the two barriers of a round (1.1 us per round without any load).  One barrier a round, the next
+// round's scores formed beside this one's weights, was 0.96 .. 1.07 of the time from 4096 keys on and 1 us slower up to 1024:
+// intake it is.  K fragments loaded straight into the matrix instruction's layout (no LDS, 64 bytes of 16 rows per load)
+// were slower: 47 instead of 34 us below.
 // Measured, 32 query heads over 8, bf16, time of a call on the stream, attention_kernel -> this kernel: 1 x 4096 keys
 // 90 -> 28 us, 6 sequences of 96 .. 4001 keys 89 -> 28 us, 16 x 4096 98 -> 56 us (4.8 TB/s of K + V), 64 x 4096
 // 202 -> 194 us (5.5 TB/s), 1 x 32768 98 -> 49 us, 80 x 10000 786 -> 606 us; 40 heads over 8 (groups of five, which
@@ -478,8 +479,8 @@ __global__ __launch_bounds__(64 * DEC_PROD_WAVES) void attention_decode_merge_ke
 constexpr size_t DEC_MAX_STATE_BYTES = (size_t)306 << 20;
 
 // One workgroup per split while that leaves the chip short of work; enough sequences walk their splits in registers.  A
-// compute unit takes in about 33 bytes per ns from HBM (61 from the memory-side cache) however many loads are under way,
-// so while compute units are left over an item's value channels are dealt to two or four workgroups, each of which
+// compute unit takes in 53 bytes per ns from HBM while few do and 32 with 192 of them, whether 32 or 256 KiB are under way
+// (plain loads of consecutive rows; from the memory-side cache 150 and 39), so while compute units are left over an item's value channels are dealt to two or four workgroups, each of which
 // forms all scores: K is fetched once per XCD, and a workgroup reads 3/4 or 5/8 of the bytes.
 struct DecodePlan {
     int col_groups, n_splits;

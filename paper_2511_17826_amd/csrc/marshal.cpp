@@ -1,7 +1,8 @@
 // The Python binding's common calls, marshalled natively: tensors in, one C call of libtbik, the new output tensor out.
 //
-// A call on a few rows is over on the GPU before Python has issued it.  Through ctypes a call costs its launches (2.2 us each) and
-// 4.3 us of argument handling; here the handling is under 2 us.  What a function below returns:
+// A call on a few rows is over on the GPU before Python has issued it.  Host time of a call through ctypes -> here, its launches (2.2 us
+// each) included: 1 x 4096 x 4096 in bf16, two launches, 9.95 -> 6.9 us, in 8 bits, one, 8.0 -> 4.0; RMSNorm of a row 5.3 -> 4.0, attention
+// of two short sequences 10.2 -> 4.4.  What a function below returns:
 //   the output tensor(s), or an int: the library's status where it is not TBIK_OK, or None: "not one of the common calls" --
 // an argument of another type, a view it would refuse, a tensor subclass, anything odd.  The caller then takes the way
 // through ctypes, which answers every call as it always did, its errors included.  Nothing is decided here and nothing is kept between calls
